@@ -280,7 +280,45 @@ void run_setup(Plan& plan, System& S, const double* pos) {
   staged(plan, MBD_STAGE_SETUP, [&] {
     launch_setup<R>(S.geo, S.buf, pos, S.src.alpha, S.src.omega, S.src.r_vdw, plan.stream);
     if (S.buf.pg_T) launch_pair_build<R>(S.geo, S.buf, false, plan.stream);
+    if (S.buf.nb_cap > 0) launch_nbr_build<R>(S.geo, S.buf, nullptr, plan.stream);
   });
+}
+
+// Largest neighbour list kept for one system; beyond it (or when its allocation fails) the
+// pairs of a narrow block are summed on the fly, as they are for any target whose count
+// outgrows the list at later positions.
+constexpr size_t kMaxNbrBytes = (size_t)4 << 30;
+
+// Size and build the neighbour list of a narrow block (B <= 8) for the positions set up
+// last: a counting pass, then a capacity of 1.25 x the largest count plus 16, then the build.
+template <typename R>
+void create_nbr_list(Plan& plan, System& S) {
+  SysBuffers& b = S.buf;
+  b.nb_count = dalloc<int>(plan, (size_t)S.geo.n + 1, S.bytes);
+  int* mx_d = b.nb_count + S.geo.n;
+  fill_int(mx_d, 0, 1, plan.stream);
+  launch_nbr_build<R>(S.geo, b, mx_d, plan.stream);
+  check(hipGetLastError(), "neighbour count");
+  int mx = 0;
+  check(hipStreamSynchronize(plan.stream), "neighbour count");
+  check(hipMemcpy(&mx, mx_d, sizeof(int), hipMemcpyDeviceToHost), "neighbour count");
+  const size_t cap = (size_t)mx + mx / 4 + 16;
+  const size_t ents = cap * (size_t)S.geo.n;
+  if (ents * (sizeof(int2) + 2 * sizeof(R)) > kMaxNbrBytes) return;
+  void *h = nullptr, *t = nullptr;
+  if (hipMalloc(&h, ents * sizeof(int2)) != hipSuccess ||
+      hipMalloc(&t, ents * 2 * sizeof(R)) != hipSuccess) {
+    if (h) hipFree(h);
+    (void)hipGetLastError();  // not an error: the plan runs without the list
+    return;
+  }
+  plan.allocations.push_back(h);
+  plan.allocations.push_back(t);
+  S.bytes += ents * (sizeof(int2) + 2 * sizeof(R));
+  b.nb_cap = (int)cap;
+  b.nb_hdr = static_cast<int2*>(h);
+  b.nb_ab = t;
+  launch_nbr_build<R>(S.geo, b, nullptr, plan.stream);
 }
 
 // Size and build the direct-space tensor list (B >= 16) for the positions set up
@@ -1084,10 +1122,12 @@ mbd_status mbd_plan_create(mbd_plan* out, const mbd_system* systems, int32_t n_s
         allocate_system<double>(plan, S, prm.n_probes, prm.n_steps);
         run_setup<double>(plan, S, sy.pos);
         if (plan.B >= 16 || plan.forces) create_pair_list<double>(plan, S);
+        if (plan.B < 16 && g.replica_cut <= 0.0) create_nbr_list<double>(plan, S);
       } else {
         allocate_system<float>(plan, S, prm.n_probes, prm.n_steps);
         run_setup<float>(plan, S, sy.pos);
         if (plan.B >= 16 || plan.forces) create_pair_list<float>(plan, S);
+        if (plan.B < 16 && g.replica_cut <= 0.0) create_nbr_list<float>(plan, S);
       }
       check(hipGetLastError(), "setup launch");
       // launch shape: built in, given, cached or measured on this system

@@ -141,6 +141,11 @@ struct SysBuffers {
   int2* pg_hdr = nullptr;      // [ngroups][pg_cap] (source index, 16-bit target mask)
   void* pg_T = nullptr;        // Real [ngroups][pg_cap][kGroup][kTensorWords]
   void* pg_zero = nullptr;     // Real [kTensorWords] zeros (matrix-core rows past a list)
+  // neighbour list (B <= 8): per sorted target the pairs within r_pair
+  int nb_cap = 0;              // entries per target (0: no list, pairs summed on the fly)
+  int* nb_count = nullptr;     // [n] pairs within r_pair (may exceed nb_cap)
+  int2* nb_hdr = nullptr;      // [n][nb_cap] (source, packed cell offset)
+  void* nb_ab = nullptr;       // Real [n][nb_cap][2] A and B of T_dir = A I - B r r^T
   // Lanczos state for one block of right-hand sides
   double* W = nullptr;         // [m][n][3][B] Krylov vectors, unnormalized
   double* Lt = nullptr;        // [n][3][B] C w_k
@@ -255,6 +260,11 @@ void launch_replica(const Geometry& g, const SysBuffers& b, int B, hipStream_t s
 
 template <typename R>
 void launch_pair_build(const Geometry& g, const SysBuffers& b, bool count_only, hipStream_t st);
+
+// Neighbour list at the current positions: counts, and up to b.nb_cap entries per target;
+// maxcount (device, may be null) receives the largest count.
+template <typename R>
+void launch_nbr_build(const Geometry& g, const SysBuffers& b, int* maxcount, hipStream_t st);
 
 template <typename R>
 long long count_pairs(const Geometry& g, const SysBuffers& b, hipStream_t st);

@@ -10,9 +10,10 @@
 // works for any cell shape and covers several images when r_pair exceeds half the box.
 //
 // Two variants:
-//  - direct: one thread per target atom, all right-hand sides (B <= 8) in
-//    registers, tensors evaluated on the fly;
-//  - list:   for B >= 16. The positions do not change during a Lanczos run, so
+//  - neighbour list: for B <= 8. Per target the sources within r_pair with A and B of
+//    their tensors (k_nbr_build, once per device setup), applied by one to four
+//    wavefronts per target (k_pair_nbr);
+//  - tensor list: for B >= 16. The positions do not change during a Lanczos run, so
 //    the tensors are evaluated once per device setup (k_pair_build) and kept in
 //    device memory, grouped by 16 consecutive sorted target atoms: for every
 //    source image within r_pair of at least one target of the group, a header
@@ -30,68 +31,235 @@ namespace mbd {
 
 namespace {
 
-template <typename R, int NB>
-__global__ void __launch_bounds__(128)
-k_pair_direct(const Geometry geo, const int* __restrict__ cell_start,
-              const int* __restrict__ scell, const R* __restrict__ loc,
-              const R* __restrict__ dv, R* __restrict__ Ed, int B) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= geo.n) return;
-  const int c = scell[s];
+// ---------------------------------------------------------------------------
+// Neighbour list of the narrow blocks (B <= 8): build (once per device setup), apply.
+// ---------------------------------------------------------------------------
+
+// Packed cell offsets (dx, dy, dz) of a list entry, and the shift sum_a o_a h_a they stand
+// for (formed in double, then rounded, as everywhere in this file).
+__device__ __forceinline__ int pack_off(int dx, int dy, int dz) {
+  return ((dx + 512) << 20) | ((dy + 512) << 10) | (dz + 512);
+}
+template <typename R>
+__device__ __forceinline__ void cell_shift(const Geometry& geo, int off, R& sx, R& sy, R& sz) {
+  const int dx = (off >> 20) - 512, dy = ((off >> 10) & 1023) - 512, dz = (off & 1023) - 512;
+  sx = (R)(dx * geo.hv[0][0] + dy * geo.hv[1][0] + dz * geo.hv[2][0]);
+  sy = (R)(dx * geo.hv[0][1] + dy * geo.hv[1][1] + dz * geo.hv[2][1]);
+  sz = (R)(dx * geo.hv[0][2] + dy * geo.hv[1][2] + dz * geo.hv[2][2]);
+}
+
+// Cell ci of the scan around (cx, cy, cz) (x fastest): its packed offset and its index.
+__device__ __forceinline__ int scan_cell(const Geometry& geo, int cx, int cy, int cz, int ci,
+                                         int& off) {
+  const int nx = 2 * geo.nr[0] + 1, ny = 2 * geo.nr[1] + 1;
+  const int dx = ci % nx - geo.nr[0], dy = (ci / nx) % ny - geo.nr[1],
+            dz = ci / (nx * ny) - geo.nr[2];
+  int wx = (cx + dx) % geo.nc[0]; if (wx < 0) wx += geo.nc[0];
+  int wy = (cy + dy) % geo.nc[1]; if (wy < 0) wy += geo.nc[1];
+  int wz = (cz + dz) % geo.nc[2]; if (wz < 0) wz += geo.nc[2];
+  off = pack_off(dx, dy, dz);
+  return cell_index(wx, wy, wz);
+}
+
+template <typename R>
+struct alignas(2 * sizeof(R)) NbrAB {
+  R A, B;
+};
+
+// One wavefront per target. The cells around it are taken 64 at a time, their atom counts
+// prefix-summed, and every lane tests one candidate of a 64-candidate round; the hits are
+// appended in scan order (source atom, packed cell offset), and A and B of T_dir are then
+// evaluated one lane per kept pair, so no lane of the erfc and exp evaluation idles on a
+// candidate out of range (about 3 of 4 are). Every pair is counted, at most cap are kept;
+// with cap == 0 only the counts are produced.
+template <typename R>
+__global__ void __launch_bounds__(256)
+k_nbr_build(const Geometry geo, const int* __restrict__ cell_start,
+            const int* __restrict__ scell, const R* __restrict__ loc, int cap,
+            int2* __restrict__ hdr, NbrAB<R>* __restrict__ ab, int* __restrict__ count,
+            int* __restrict__ maxcount) {
+  __shared__ int pre_all[4][65], first_all[4][64], off_all[4][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int* pre = pre_all[wave];
+  int* first = first_all[wave];
+  int* offs = off_all[wave];
+  const int s = blockIdx.x * 4 + wave;
+  if (s >= geo.n) return;  // the wavefronts are independent: no barrier below
   int cx, cy, cz;
-  cell_coords(c, cx, cy, cz);
-  const R xi = loc[4 * s], yi = loc[4 * s + 1], zi = loc[4 * s + 2], si = loc[4 * s + 3];
-  const R tau = (R)geo.tau, dd = (R)geo.damp_d;
+  cell_coords(scell[s], cx, cy, cz);
+  const R xi = loc[4 * (size_t)s], yi = loc[4 * (size_t)s + 1], zi = loc[4 * (size_t)s + 2],
+          si = loc[4 * (size_t)s + 3];
   const R rp2 = (R)(geo.r_pair * geo.r_pair);
-  R acc[NB][3];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) acc[b][0] = acc[b][1] = acc[b][2] = R(0);
-  for (int oz = -geo.nr[2]; oz <= geo.nr[2]; ++oz) {
-    int wz = (cz + oz) % geo.nc[2];
-    if (wz < 0) wz += geo.nc[2];
-    for (int oy = -geo.nr[1]; oy <= geo.nr[1]; ++oy) {
-      int wy = (cy + oy) % geo.nc[1];
-      if (wy < 0) wy += geo.nc[1];
-      for (int ox = -geo.nr[0]; ox <= geo.nr[0]; ++ox) {
-        int wx = (cx + ox) % geo.nc[0];
-        if (wx < 0) wx += geo.nc[0];
-        const R sx = (R)(ox * geo.hv[0][0] + oy * geo.hv[1][0] + oz * geo.hv[2][0]);
-        const R sy = (R)(ox * geo.hv[0][1] + oy * geo.hv[1][1] + oz * geo.hv[2][1]);
-        const R sz = (R)(ox * geo.hv[0][2] + oy * geo.hv[1][2] + oz * geo.hv[2][2]);
-        const bool zero = (ox == 0 && oy == 0 && oz == 0);
-        const int cc = cell_index(wx, wy, wz);
-        const int j0 = cell_start[cc], j1 = cell_start[cc + 1];
-        for (int j = j0; j < j1; ++j) {
-          if (zero && j == s) continue;
-          const R rx = loc[4 * j] - xi + sx;
-          const R ry = loc[4 * j + 1] - yi + sy;
-          const R rz = loc[4 * j + 2] - zi + sz;
-          const R r2 = rx * rx + ry * ry + rz * rz;
-          if (r2 >= rp2) continue;
-          const R S = loc[4 * j + 3] + si;
-          R A, Bk;
-          direct_kernel<R>(r2, tau, R(1) / S, dd, A, Bk);
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            if (b >= B) break;
-            const R d0 = dv[(j * 3 + 0) * B + b];
-            const R d1 = dv[(j * 3 + 1) * B + b];
-            const R d2 = dv[(j * 3 + 2) * B + b];
-            const R rd = Bk * (rx * d0 + ry * d1 + rz * d2);
-            acc[b][0] += A * d0 - rx * rd;
-            acc[b][1] += A * d1 - ry * rd;
-            acc[b][2] += A * d2 - rz * rd;
-          }
+  const int ncells = (2 * geo.nr[0] + 1) * (2 * geo.nr[1] + 1) * (2 * geo.nr[2] + 1);
+  const int home = pack_off(0, 0, 0);
+  int2* H = hdr + (size_t)s * cap;
+  int cnt = 0;
+  for (int cc0 = 0; cc0 < ncells; cc0 += 64) {
+    int nat = 0;
+    if (cc0 + lane < ncells) {
+      int off;
+      const int cc = scan_cell(geo, cx, cy, cz, cc0 + lane, off);
+      first[lane] = cell_start[cc];
+      nat = cell_start[cc + 1] - cell_start[cc];
+      offs[lane] = off;
+    }
+    int v = nat;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(v, o);
+      if (lane >= o) v += u;
+    }
+    pre[lane + 1] = v;
+    if (lane == 0) pre[0] = 0;
+    const int total = __shfl(v, 63);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int r0 = 0; r0 < total; r0 += 64) {
+      const int c = r0 + lane;
+      bool hit = false;
+      int j = 0, off = home;
+      if (c < total) {
+        int lo = 0, hi = 63;  // the cell of candidate c: largest k with pre[k] <= c
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (pre[mid] <= c) lo = mid; else hi = mid - 1;
         }
+        j = first[lo] + (c - pre[lo]);
+        off = offs[lo];
+        R sx, sy, sz;
+        cell_shift<R>(geo, off, sx, sy, sz);
+        const R rx = loc[4 * (size_t)j] - xi + sx;
+        const R ry = loc[4 * (size_t)j + 1] - yi + sy;
+        const R rz = loc[4 * (size_t)j + 2] - zi + sz;
+        hit = rx * rx + ry * ry + rz * rz < rp2 && !(j == s && off == home);
+      }
+      const unsigned long long bal = __ballot(hit);
+      const int slot = cnt + (int)__builtin_amdgcn_mbcnt_hi(
+                                 (unsigned)(bal >> 32),
+                                 __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+      if (hit && slot < cap) H[slot] = make_int2(j, off);
+      cnt += __popcll(bal);
+    }
+    // the next chunk's tables overwrite this one's
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  // (the fence above also made the headers of other lanes visible to this one)
+  const R tau = (R)geo.tau, dd = (R)geo.damp_d;
+  const int kept = min(cnt, cap);
+  for (int k = lane; k < kept; k += 64) {
+    const int2 h = H[k];
+    R sx, sy, sz;
+    cell_shift<R>(geo, h.y, sx, sy, sz);
+    const R* lj = loc + 4 * (size_t)h.x;
+    const R rx = lj[0] - xi + sx, ry = lj[1] - yi + sy, rz = lj[2] - zi + sz;
+    NbrAB<R> t;
+    direct_kernel<R>(rx * rx + ry * ry + rz * rz, tau, R(1) / (lj[3] + si), dd, t.A, t.B);
+    ab[(size_t)s * cap + k] = t;
+  }
+  if (lane == 0) {
+    count[s] = cnt;
+    if (maxcount) atomicMax(maxcount, cnt);
+  }
+}
+
+// E_dir of B = NB <= 8 right-hand sides: WV wavefronts per target, lane = right-hand side
+// + NB x list entry, so a wavefront takes 64 / NB neighbours at a time and the partial
+// fields are added across lanes (then across the WV wavefronts, in LDS) in a fixed order.
+// One thread per target instead runs one serial chain of several hundred loads per thread
+// and re-evaluates erfc and exp for every candidate in every matvec.
+// A target with more pairs than the list holds (positions far denser than those the plan
+// was sized for, or a list too large to keep) is summed on the fly over the cells.
+template <typename R, int NB, int WV>
+__global__ void __launch_bounds__(256)
+k_pair_nbr(const Geometry geo, const int* __restrict__ cell_start,
+           const int* __restrict__ scell, const R* __restrict__ loc, int cap,
+           const int* __restrict__ count, const int2* __restrict__ hdr,
+           const NbrAB<R>* __restrict__ ab, const R* __restrict__ dv, R* __restrict__ Ed) {
+  constexpr int TPB = 4 / WV;    // targets per work-group
+  constexpr int EW = 64 / NB;    // entries per wavefront and step
+  constexpr int EL = EW * WV;    // entries per target and step
+  __shared__ R red[WV > 1 ? 4 * NB * 3 : 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int b = lane % NB, e = lane / NB + (wave % WV) * EW;
+  // each XCD takes a contiguous range of sorted targets (gridDim.x is a multiple of 8):
+  // their sources' positions and dipoles stay in its L2
+  const int blk = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int s = blk * TPB + wave / WV;
+  if (s >= geo.n) return;  // WV > 1: uniform over the work-group
+  const R xi = loc[4 * (size_t)s], yi = loc[4 * (size_t)s + 1], zi = loc[4 * (size_t)s + 2];
+  R e0 = R(0), e1 = R(0), e2 = R(0);
+  auto add = [&](int j, R rx, R ry, R rz, R A, R Bk) {
+    const R* d = dv + (size_t)j * 3 * NB + b;
+    const R d0 = d[0], d1 = d[NB], d2 = d[2 * NB];
+    const R rd = Bk * (rx * d0 + ry * d1 + rz * d2);
+    e0 += A * d0 - rx * rd;
+    e1 += A * d1 - ry * rd;
+    e2 += A * d2 - rz * rd;
+  };
+  const int cnt = count[s];
+  if (cap > 0 && cnt <= cap) {
+    const int2* H = hdr + (size_t)s * cap;
+    const NbrAB<R>* T = ab + (size_t)s * cap;
+#pragma unroll 2
+    for (int k = e; k < cnt; k += EL) {
+      const int2 h = H[k];
+      const NbrAB<R> t = T[k];
+      R sx, sy, sz;
+      cell_shift<R>(geo, h.y, sx, sy, sz);
+      const R* lj = loc + 4 * (size_t)h.x;
+      add(h.x, lj[0] - xi + sx, lj[1] - yi + sy, lj[2] - zi + sz, t.A, t.B);
+    }
+  } else {
+    const R si = loc[4 * (size_t)s + 3], tau = (R)geo.tau, dd = (R)geo.damp_d;
+    const R rp2 = (R)(geo.r_pair * geo.r_pair);
+    const int ncells = (2 * geo.nr[0] + 1) * (2 * geo.nr[1] + 1) * (2 * geo.nr[2] + 1);
+    int cx, cy, cz;
+    cell_coords(scell[s], cx, cy, cz);
+    for (int ci = 0; ci < ncells; ++ci) {
+      int off;
+      const int cc = scan_cell(geo, cx, cy, cz, ci, off);
+      R sx, sy, sz;
+      cell_shift<R>(geo, off, sx, sy, sz);
+      const int j1 = cell_start[cc + 1];
+      for (int j = cell_start[cc] + e; j < j1; j += EL) {
+        const R* lj = loc + 4 * (size_t)j;
+        const R rx = lj[0] - xi + sx, ry = lj[1] - yi + sy, rz = lj[2] - zi + sz;
+        const R r2 = rx * rx + ry * ry + rz * rz;
+        if (r2 >= rp2 || (j == s && off == pack_off(0, 0, 0))) continue;
+        R A, Bk;
+        direct_kernel<R>(r2, tau, R(1) / (lj[3] + si), dd, A, Bk);
+        add(j, rx, ry, rz, A, Bk);
       }
     }
   }
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    if (b >= B) break;
-    Ed[(s * 3 + 0) * B + b] = acc[b][0];
-    Ed[(s * 3 + 1) * B + b] = acc[b][1];
-    Ed[(s * 3 + 2) * B + b] = acc[b][2];
+  for (int o = NB; o < 64; o <<= 1) {
+    e0 += __shfl_xor(e0, o);
+    e1 += __shfl_xor(e1, o);
+    e2 += __shfl_xor(e2, o);
+  }
+  R* out = Ed + (size_t)s * 3 * NB;
+  if constexpr (WV == 1) {
+    if (lane < NB) {
+      out[b] = e0;
+      out[NB + b] = e1;
+      out[2 * NB + b] = e2;
+    }
+  } else {
+    if (lane < NB) {
+      red[(wave * 3 + 0) * NB + b] = e0;
+      red[(wave * 3 + 1) * NB + b] = e1;
+      red[(wave * 3 + 2) * NB + b] = e2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3 * NB) {
+      R v = red[threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += red[w * 3 * NB + threadIdx.x];
+      out[threadIdx.x] = v;
+    }
   }
 }
 
@@ -999,14 +1167,24 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
   const R* dv = (const R*)b.dv;
   R* Ed = (R*)b.Ed;
   if (B <= 8) {
-    const int blocks = (g.n + 127) / 128;
+    // four wavefronts per target while one each would leave the GPU with fewer than 8
+    // wavefronts per SIMD
+    const bool wide = g.n < 8192;
+    const int blocks = ((wide ? g.n : (g.n + 3) / 4) + 7) / 8 * 8;
+#define MBD_NB(NBV)                                                                        \
+    if (wide)                                                                              \
+      k_pair_nbr<R, NBV, 4><<<blocks, 256, 0, st>>>(g, b.cell_start, b.scell, loc, b.nb_cap, \
+          b.nb_count, b.nb_hdr, (const NbrAB<R>*)b.nb_ab, dv, Ed);                         \
+    else                                                                                   \
+      k_pair_nbr<R, NBV, 1><<<blocks, 256, 0, st>>>(g, b.cell_start, b.scell, loc, b.nb_cap, \
+          b.nb_count, b.nb_hdr, (const NbrAB<R>*)b.nb_ab, dv, Ed)
     switch (B) {
-      case 1: k_pair_direct<R, 1><<<blocks, 128, 0, st>>>(g, b.cell_start, b.scell, loc, dv, Ed, B); break;
-      case 2: k_pair_direct<R, 2><<<blocks, 128, 0, st>>>(g, b.cell_start, b.scell, loc, dv, Ed, B); break;
-      case 3:
-      case 4: k_pair_direct<R, 4><<<blocks, 128, 0, st>>>(g, b.cell_start, b.scell, loc, dv, Ed, B); break;
-      default: k_pair_direct<R, 8><<<blocks, 128, 0, st>>>(g, b.cell_start, b.scell, loc, dv, Ed, B); break;
+      case 1: MBD_NB(1); break;
+      case 2: MBD_NB(2); break;
+      case 4: MBD_NB(4); break;
+      default: MBD_NB(8); break;
     }
+#undef MBD_NB
     return;
   }
   // a multiple of 8 work-groups, so that the XCD remap covers every group
@@ -1070,6 +1248,16 @@ void launch_pair_build(const Geometry& g, const SysBuffers& b, bool count_only, 
       g, b.cell_start, b.scell, (const R*)b.loc, count_only ? 0 : b.pg_cap, b.pg_hdr,
       (R*)b.pg_T, count_only ? nullptr : (R*)b.pg_F, b.pg_count, b.pg_max);
 }
+
+template <typename R>
+void launch_nbr_build(const Geometry& g, const SysBuffers& b, int* maxcount, hipStream_t st) {
+  k_nbr_build<R><<<(g.n + 3) / 4, 256, 0, st>>>(g, b.cell_start, b.scell, (const R*)b.loc,
+                                               b.nb_cap, b.nb_hdr, (NbrAB<R>*)b.nb_ab,
+                                               b.nb_count, maxcount);
+}
+
+template void launch_nbr_build<float>(const Geometry&, const SysBuffers&, int*, hipStream_t);
+template void launch_nbr_build<double>(const Geometry&, const SysBuffers&, int*, hipStream_t);
 
 template <typename R>
 void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) {
