@@ -119,8 +119,9 @@ typedef struct {
 } mbd_shape;
 
 enum {
-  MBD_TUNE_OFF = 0,       /* built-in shape: pair_wg_per_cu 0, size rule, default chunk,
-                             overlap 1                                                    */
+  MBD_TUNE_OFF = 0,       /* built-in shape: pair_wg_per_cu 0, default chunk, overlap 1, and
+                             the matrix-core list kernel (pair_mode 1, widest split) where
+                             it applies                                                   */
   MBD_TUNE_MEASURE = 1,   /* time candidate shapes on each system at plan creation and
                              keep the fastest (reused from tune_cache when it holds one)  */
   MBD_TUNE_GIVEN = 2      /* use params.shape as given, for every system                 */

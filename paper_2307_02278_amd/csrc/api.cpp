@@ -181,7 +181,14 @@ void allocate_system(Plan& plan, System& S, int R_probes, int m) {
   b.W = dalloc<double>(plan, vec * m, by);
   b.Lt = dalloc<double>(plan, vec, by);
   b.dv = dalloc<R>(plan, vec, by);
-  b.Ed = dalloc<R>(plan, vec, by);
+  // small systems split each group's candidates over several work-groups, until a launch
+  // has about 1024 of them (four wavefronts each: 4 per SIMD)
+  const int ngroups = (n + kGroup - 1) / kGroup;
+  const int parts = std::max(1, std::min(16, 1024 / ngroups));
+  b.ed_parts = B >= 16 ? parts : 1;
+  b.fs_parts = parts;
+  b.pg_real = (int)sizeof(R);
+  b.Ed = dalloc<R>(plan, vec * b.ed_parts, by);
   b.grid = dalloc<R>(plan, (size_t)g.K[2] * g.K[1] * (g.K[0] + 2) * B, by);
   b.part = dalloc<double>(plan, (size_t)kRedBlocks * kPartSlots * B, by);
   b.coef = dalloc<double>(plan, (size_t)kMaxSteps * B, by);
@@ -201,7 +208,7 @@ void allocate_system(Plan& plan, System& S, int R_probes, int m) {
     b.adj = dalloc<double>(plan, (size_t)B * 16, by);
     if (plan.prm.store_grids)
       b.phi = dalloc<R>(plan, (size_t)m * g.K[2] * g.K[1] * (g.K[0] + 2) * B, by);
-    b.fsum = dalloc<double>(plan, 6 * (size_t)n, by);
+    b.fsum = dalloc<double>(plan, 3 * (size_t)n * (1 + b.fs_parts), by);
   }
   if (plan.prm.krylov_block > 1) {
     BlockWork& bw = b.blk;
@@ -596,7 +603,19 @@ double* scratch_of(int device) {
 // gather (sub-lanes share a stencil below 64 right-hand sides per chunk), and the
 // matrix-core pair kernel the order of the direct-space sums.
 
-constexpr mbd_shape kBuiltinShape = {0, 0, 0, 1, 0, 0, 0};
+// The built-in shape: every group resident, the default chunk, the side stream, and the
+// matrix-core list kernel with its widest candidate split where it applies (24k atoms, 128
+// right-hand sides, alone: 425 us a launch against 598 us of the vector kernel).
+mbd_shape builtin_shape(const Plan& plan, const System& S) {
+  mbd_shape sh = {0, 0, 0, 1, 0, 0, 0};
+  const int B = plan.B;
+  if (plan.prec == MBD_PREC_MIXED && B % 64 == 0 && B <= 256 && S.buf.pg_T &&
+      S.geo.replica_cut <= 0.0) {
+    sh.pair_mode = 1;
+    sh.pair_subsets = B <= 128 ? 4 : 2;  // at most 4 wavefronts with B / 128 column wavefronts
+  }
+  return sh;
+}
 
 bool valid_shape(const mbd_shape& sh, int B) {
   const bool pow2chunk = sh.grid_chunk == 0 || (sh.grid_chunk > 0 && sh.grid_chunk <= 64 &&
@@ -744,11 +763,7 @@ void tune_system(Plan& plan, System& S, int sys_index) {
   // shares, at most 4 wavefronts per work-group
   const bool mfma = list && plan.prec == MBD_PREC_MIXED && B % 64 == 0 && B <= 256;
   const int mfma_nn = B / (B % 128 == 0 ? 128 : 64);
-  mbd_shape best = kBuiltinShape;
-  if (mfma) {
-    best.pair_mode = 1;
-    best.pair_subsets = mfma_nn * 4 <= 4 ? 4 : (mfma_nn * 2 <= 4 ? 2 : 1);
-  }
+  mbd_shape best = builtin_shape(plan, S);
   apply_shape(plan, S, best);
   best = S.shape;
   double tbest = time_matvec<R>(plan, S, 5);
@@ -777,8 +792,9 @@ void tune_system(Plan& plan, System& S, int sys_index) {
   residency();
   if (list) {
     const mbd_shape base = best;
+    // (float64 and blocks below 64 always run on the matrix cores, whatever the shape)
     for (int ns : {1, 2, 4}) {
-      if (ns * B < 64) continue;
+      if (!mfma) break;
       mbd_shape sh = base;
       sh.pair_mode = 0;
       sh.pair_subsets = ns;
@@ -1148,7 +1164,7 @@ mbd_status mbd_plan_create(mbd_plan* out, const mbd_system* systems, int32_t n_s
           cache_store(prm.tune_cache, key, S.shape, S.tune_ms);
         }
       } else {
-        apply_shape(plan, S, kBuiltinShape);
+        apply_shape(plan, S, builtin_shape(plan, S));
         S.shape_source = MBD_SHAPE_BUILTIN;
       }
     }
@@ -1275,7 +1291,8 @@ void enqueue_system(Plan& P, int s, double* energy, double* sd, double* forces) 
   System& S = P.sys[s];
   size_t off = 0;
   for (int k = 0; k < s; ++k) off += (size_t)P.sys[k].geo.n;
-  if (forces) fill_double(S.buf.fsum, 0.0, 6 * (size_t)S.geo.n, P.stream);
+  if (forces)
+    fill_double(S.buf.fsum, 0.0, 3 * (size_t)S.geo.n * (1 + S.buf.fs_parts), P.stream);
   double* sds = sd ? sd + s : nullptr;
   if (P.prec == MBD_PREC_FP64) run_energy<double>(P, S, s, energy + s, sds, forces != nullptr);
   else run_energy<float>(P, S, s, energy + s, sds, forces != nullptr);

@@ -140,6 +140,7 @@ struct SysBuffers {
   int* pg_max = nullptr;       // [1] max over groups of pg_count
   int2* pg_hdr = nullptr;      // [ngroups][pg_cap] (source index, 16-bit target mask)
   void* pg_T = nullptr;        // Real [ngroups][pg_cap][kGroup][kTensorWords]
+  int pg_real = 0;             // bytes of a Real of the list (4 or 8)
   void* pg_zero = nullptr;     // Real [kTensorWords] zeros (matrix-core rows past a list)
   // neighbour list (B <= 8): per sorted target the pairs within r_pair
   int nb_cap = 0;              // entries per target (0: no list, pairs summed on the fly)
@@ -150,7 +151,8 @@ struct SysBuffers {
   double* W = nullptr;         // [m][n][3][B] Krylov vectors, unnormalized
   double* Lt = nullptr;        // [n][3][B] C w_k
   void* dv = nullptr;          // Real [n][3][B] generalized dipoles g * w_k
-  void* Ed = nullptr;          // Real [n][3][B] direct-space field
+  void* Ed = nullptr;          // Real [ed_parts][n][3][B] direct-space field, in parts
+  int ed_parts = 1;            // parts the matrix-core list kernel splits a group's list into
   void* grid = nullptr;        // Real [B / BG][K3][K2][K1 + 2][BG]
   double* part = nullptr;      // [kRedBlocks][kPartSlots][B] partial sums
   double* coef = nullptr;      // [B][kMaxSteps] reorthogonalization coefficients
@@ -169,8 +171,9 @@ struct SysBuffers {
   double* abar = nullptr;      // [B][m] dQ/da_k, then the full adjoint of a_k
   double* bbar = nullptr;      // [B][m] dQ/d nrm_k (k >= 1)
   double* adj = nullptr;       // [B][8] per-step adjoint scalars
-  double* fsum = nullptr;      // [2][n][3] sums over probes and steps of l-bar^T dC/dR y
-                               // (sorted): [0] reciprocal part, [1] direct (pair) part
+  double* fsum = nullptr;      // [1 + fs_parts][n][3] sums over probes and steps of
+                               // l-bar^T dC/dR y (sorted): [0] reciprocal, then direct parts
+  int fs_parts = 1;            // parts of the direct force sums (disjoint candidate ranges)
   BlockWork blk;               // block Lanczos workspace (krylov_block > 1)
 };
 
@@ -252,6 +255,9 @@ void launch_line_lists(const Geometry& g, SysBuffers& b, hipStream_t st);
 template <typename R>
 void launch_setup(const Geometry& g, SysBuffers& b, const double* pos, const double* alpha,
                   const double* omega, const double* rvdw, hipStream_t st);
+
+// Parts of the direct-space field that launch_pair leaves in b.Ed.
+int pair_parts(const Geometry& g, const SysBuffers& b, int B);
 
 template <typename R>
 void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st);

@@ -594,15 +594,18 @@ __global__ void k_fill_double(double* __restrict__ p, double v, size_t count) {
 }
 
 // F = -dE/dR = -1/2 (3N / R) dsum/dR, back to caller order; dsum/dR is the sum of
-// the reciprocal half and the direct (pair) half of fsum.
-__global__ void k_forces_finish(int n, int R, const int* __restrict__ perm,
+// the reciprocal part and the direct (pair) parts of fsum.
+__global__ void k_forces_finish(int n, int R, int parts, const int* __restrict__ perm,
                                 const double* __restrict__ fsum, double* __restrict__ out) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const double sc = -0.5 * (3.0 * n / R);
   const int i = perm[s];
-  for (int a = 0; a < 3; ++a)
-    out[3 * i + a] = sc * (fsum[3 * s + a] + fsum[3 * ((size_t)n + s) + a]);
+  for (int a = 0; a < 3; ++a) {
+    double v = fsum[3 * (size_t)s + a];
+    for (int q = 1; q <= parts; ++q) v += fsum[3 * ((size_t)q * n + s) + a];
+    out[3 * i + a] = sc * v;
+  }
 }
 
 inline int rb_for(int B) { return B >= 64 ? 64 : B; }
@@ -750,7 +753,8 @@ void launch_adjoint_accumulate(const Geometry& geo, const SysBuffers& b, int B, 
 
 void launch_forces_finish(const Geometry& geo, const SysBuffers& b, int R, double* forces,
                           hipStream_t st) {
-  k_forces_finish<<<(geo.n + 255) / 256, 256, 0, st>>>(geo.n, R, b.perm, b.fsum, forces);
+  k_forces_finish<<<(geo.n + 255) / 256, 256, 0, st>>>(geo.n, R, b.fs_parts, b.perm, b.fsum,
+                                                           forces);
 }
 
 void launch_pack(const Geometry& geo, const SysBuffers& b, const double* v, int nrhs, int B,

@@ -575,47 +575,81 @@ k_pair_list(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
   }  // groups of this work-group
 }
 
-// E_dir of a group on the matrix cores (float, B a multiple of 64). For the group's 16
-// targets t the field is one dense product over k = 3 c + b (candidate c, component b):
+// E_dir of a group on the matrix cores. For the group's 16 targets t the field is one
+// dense product over k = 3 c + b (candidate c, component b):
 //   E[t][a][rhs] = sum_k T_(c,t)[a][b] d_(j(c))[b][rhs],
 // the list's zero tensors standing for out-of-range (target, candidate) pairs. It is
 // computed as three 16-row tiles (a = x, y, z) times NT column tiles of 16 right-hand
-// sides with v_mfma_f32_16x16x4_f32, four rows of k per instruction: the instruction
-// takes A[i][k] from lane i + 16 k and B[k][j] from lane j + 16 k and leaves D[i][j] in
-// register i % 4 of lane j + 16 (i / 4). A wavefront owns 16 NT right-hand sides and
-// every NK-th block of four candidates (three steps of four k rows); the NK partial
-// products of a group are added in LDS
-// in wavefront order, so the result does not depend on timing. The source atoms of up
-// to kMfmaChunk candidates at a time are staged in LDS; each lane then reads its tensor
-// row and dipole component straight from global memory, one block of three steps ahead
-// of the matrix instructions that use them. With NK = 1 the k order is the vector
-// kernel's, and so far the two have given the same bits.
+// sides with v_mfma_f32_16x16x4_f32 or v_mfma_f64_16x16x4_f64, four rows of k per
+// instruction: the instruction takes A[i][k] from lane i + 16 k and B[k][j] from lane
+// j + 16 k and leaves D[i][j], in float, in register i % 4 of lane j + 16 (i / 4), and in
+// double in register i / 4 of lane j + 16 (i % 4). A wavefront owns 16 NT right-hand sides
+// and every NK-th block of four candidates (three steps of four k rows); the NK partial
+// products of a group are added in LDS in wavefront order, so the result does not depend
+// on timing. The source atoms of up to kMfmaChunk candidates at a time are staged in LDS;
+// each lane then reads its tensor row and dipole component straight from global memory,
+// one block of three steps ahead of the matrix instructions that use them. In float with
+// NK = 1 and one part the k order is the vector kernel's, and so far the two have given
+// the same bits.
+// Small systems: a launch of one work-group per group leaves most of the GPU idle (41 of
+// 256 CUs at 648 atoms) while each wavefront walks several hundred candidates, so the
+// candidates of a group are also split over gridDim.y work-groups, each writing its own
+// part of the field; the gather adds the parts in order (pair_parts).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaChunk = 1024;  // candidates per LDS chunk (a multiple of 4)
 
-template <int NT>
-struct MfmaOperands {
-  float a[3];
-  float b[NT];
+template <typename R> struct Mma;
+template <> struct Mma<float> {
+  typedef f32x4 acc;
+  static __device__ __forceinline__ acc fma(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  // matrix row of register r in a lane of row group g = lane / 16
+  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
+};
+template <> struct Mma<double> {
+  typedef f64x4 acc;
+  static __device__ __forceinline__ acc fma(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int g, int r) { return g + 4 * r; }
 };
 
-template <int NK, int NT, int NN>
+// N consecutive reals moved as one vector (at most 16 bytes).
+template <typename R, int N>
+struct alignas(sizeof(R) * N) Pack {
+  R v[N];
+};
+
+template <typename R, int NT>
+struct MfmaOperands {
+  R a[3];
+  R b[NT];
+};
+
+template <typename R, int NK, int NT, int NN>
 __global__ void __launch_bounds__(256)
-k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const float* __restrict__ Tg,
-            const float* __restrict__ Tz, const int* __restrict__ gcount, int cap,
-            const float* __restrict__ dv, float* __restrict__ Ed, int B) {
-  // partial tiles of one component for the NK-way reduction: [wavefront][tile][lane]
+k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restrict__ Tg,
+            const R* __restrict__ Tz, const int* __restrict__ gcount, int cap,
+            const R* __restrict__ dv, R* __restrict__ Ed, int B) {
+  typedef typename Mma<R>::acc Acc;
+  constexpr int VN = NT * (int)sizeof(R) > 16 ? 16 / (int)sizeof(R) : NT;  // reals per vector
+  // partial tiles of one component for the NK-way reduction: [wavefront][tile][row][lane]
   // for the work-group's NN x NK wavefronts (NN column wavefronts)
-  __shared__ f32x4 red[NK > 1 ? NN * NK * NT * 64 : 1];
+  __shared__ R red[NK > 1 ? NN * NK * NT * 256 : 1];
   __shared__ int jl[kMfmaChunk];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wk = wave % NK, wn = wave / NK;
   const int col = lane & 15, row = lane >> 4;
   // column col of column tile t is right-hand side rhs + t: a lane's NT right-hand
-  // sides are contiguous, so its dipoles and results move as 16-byte vectors
+  // sides are contiguous, so its dipoles and results move as vectors of 16 bytes
   const int rhs = wn * 16 * NT + NT * col;
   const size_t Bs = (size_t)B;
+  // this work-group's part of every candidate list, in units of four candidates
+  const int part = blockIdx.y, parts = gridDim.y;
+  Ed += (size_t)part * 3 * geo.n * Bs;
   // XCD-aware walk over groups, as in the vector list kernel
   const int ngroups = (geo.n + kGroup - 1) / kGroup;
   const int per = (ngroups + 7) / 8;
@@ -623,43 +657,46 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const float* __res
   for (int gi = blockIdx.x / 8; gi < per; gi += nbx) {
     const int group = (blockIdx.x % 8) * per + gi;
     if (group >= ngroups) return;  // uniform over the work-group
-    const int cnt = min(gcount[group], cap);
+    const int full = min(gcount[group], cap);
+    const int q4 = (full + 3) / 4;
+    const int clo = 4 * (int)((long)q4 * part / parts);
+    const int cnt = min(full, 4 * (int)((long)q4 * (part + 1) / parts));
     const int2* H = hdr + (size_t)group * cap;
-    const float* T = Tg + (size_t)group * cap * kCandStride;
-    f32x4 acc[3][NT];
+    const R* T = Tg + (size_t)group * cap * kCandStride;
+    Acc acc[3][NT];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < cnt; c0 += kMfmaChunk) {
+      for (int t = 0; t < NT; ++t) acc[a][t] = Acc{R(0), R(0), R(0), R(0)};
+    for (int c0 = clo; c0 < cnt; c0 += kMfmaChunk) {
       const int nc = min(kMfmaChunk, cnt - c0);
       __syncthreads();  // the previous chunk's source atoms have been read
       for (int c = threadIdx.x; c < nc; c += blockDim.x) jl[c] = H[c0 + c].x;
       __syncthreads();
-      const float* Tc = T + (size_t)c0 * kCandStride;
+      const R* Tc = T + (size_t)c0 * kCandStride;
       // operands of one step: row b of the symmetric tensor (xx, yy, zz, xy, xz, yz) of
       // candidate c and target col (b = 0: xx xy xz, b = 1: xy yy yz, b = 2: xz yz zz)
       // and component b of the candidate's dipoles. Every load is issued: candidates
       // past the chunk read the zero tensor Tz and the chunk's first dipoles, so no
       // branch hides a load from the compiler's count of loads in flight.
-      auto load = [&](int c, int b, const int (&w)[3], MfmaOperands<NT>& o) {
+      auto load = [&](int c, int b, const int (&w)[3], MfmaOperands<R, NT>& o) {
         const bool ok = c < nc;
-        const float* tt = ok ? Tc + ((size_t)c * kGroup + col) * kTensorWords : Tz;
-        const float4* dj =
-            reinterpret_cast<const float4*>(dv + ((size_t)jl[ok ? c : 0] * 3 + b) * Bs + rhs);
+        const R* tt = ok ? Tc + ((size_t)c * kGroup + col) * kTensorWords : Tz;
+        const Pack<R, VN>* dj = reinterpret_cast<const Pack<R, VN>*>(
+            dv + ((size_t)jl[ok ? c : 0] * 3 + b) * Bs + rhs);
         o.a[0] = tt[w[0]]; o.a[1] = tt[w[1]]; o.a[2] = tt[w[2]];
 #pragma unroll
-        for (int q = 0; q < NT / 4; ++q) {
-          const float4 v = dj[q];
-          o.b[4 * q] = v.x; o.b[4 * q + 1] = v.y; o.b[4 * q + 2] = v.z; o.b[4 * q + 3] = v.w;
+        for (int q = 0; q < NT / VN; ++q) {
+          const Pack<R, VN> v = dj[q];
+#pragma unroll
+          for (int u = 0; u < VN; ++u) o.b[VN * q + u] = v.v[u];
         }
       };
-      auto apply = [&](const MfmaOperands<NT>& o) {
+      auto apply = [&](const MfmaOperands<R, NT>& o) {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-          for (int t = 0; t < NT; ++t)
-            acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[a], o.b[t], acc[a][t], 0, 0, 0);
+          for (int t = 0; t < NT; ++t) acc[a][t] = Mma<R>::fma(o.a[a], o.b[t], acc[a][t]);
       };
       // The work comes in blocks of 4 candidates = 12 rows of k = 3 steps, and the
       // wavefront takes blocks p = wk, wk + NK, ...: lane row r of step u of block p has
@@ -678,7 +715,7 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const float* __res
       }
       const int nb = (nc + 3) / 4;
       const int m = wk < nb ? (nb - wk + NK - 1) / NK : 0;  // this wavefront's blocks
-      MfmaOperands<NT> buf[3];
+      MfmaOperands<R, NT> buf[3];
 #pragma unroll
       for (int u = 0; u < 3; ++u) load(4 * wk + cu[u], bu[u], wu[u], buf[u]);
       for (int i = 0; i < m; ++i) {
@@ -693,47 +730,54 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const float* __res
         }
       }
     }
-    // D[i][j] in register i % 4 of lane j + 16 (i / 4): target 4 row + r, column col;
-    // the lane's four right-hand sides rhs + 4 q .. rhs + 4 q + 3 of component a
-    auto store = [&](int a, int q, const f32x4 (&v)[4]) {
+    // component a of the lane's NT right-hand sides for the target of register r
+    auto store = [&](int a, int r, const R (&v)[NT]) {
+      const int i = group * kGroup + Mma<R>::row(row, r);
+      if (i >= geo.n) return;
+      Pack<R, VN>* o = reinterpret_cast<Pack<R, VN>*>(Ed + ((size_t)i * 3 + a) * Bs + rhs);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = group * kGroup + 4 * row + r;
-        if (i < geo.n)
-          *reinterpret_cast<float4*>(Ed + ((size_t)i * 3 + a) * Bs + rhs + 4 * q) =
-              make_float4(v[0][r], v[1][r], v[2][r], v[3][r]);
+      for (int q = 0; q < NT / VN; ++q) {
+        Pack<R, VN> w;
+#pragma unroll
+        for (int u = 0; u < VN; ++u) w.v[u] = v[VN * q + u];
+        o[q] = w;
       }
     };
     if constexpr (NK == 1) {
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int q = 0; q < NT / 4; ++q) {
-          const f32x4 v[4] = {acc[a][4 * q], acc[a][4 * q + 1], acc[a][4 * q + 2],
-                              acc[a][4 * q + 3]};
-          store(a, q, v);
+        for (int r = 0; r < 4; ++r) {
+          R v[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) v[t] = acc[a][t][r];
+          store(a, r, v);
         }
     } else {
       // one component at a time: every wavefront leaves its partial tiles in LDS, then
-      // wavefront wk adds the NK partials of the quads q = wk, wk + NK, ... in wavefront
+      // wavefront wk adds the NK partials of the rows r = wk, wk + NK, ... in wavefront
       // order and stores them
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         __syncthreads();  // the previous round's partials have been read
 #pragma unroll
-        for (int t = 0; t < NT; ++t) red[((wn * NK + wk) * NT + t) * 64 + lane] = acc[a][t];
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            red[(((wn * NK + wk) * NT + t) * 4 + r) * 64 + lane] = acc[a][t][r];
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < NT / 4; ++q) {
-          if (q % NK != wk) continue;
-          f32x4 v[4];
+        for (int r = 0; r < 4; ++r) {
+          if (r % NK != wk) continue;
+          R v[NT];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            v[u] = red[((wn * NK) * NT + 4 * q + u) * 64 + lane];
+          for (int t = 0; t < NT; ++t) {
+            v[t] = red[((wn * NK * NT + t) * 4 + r) * 64 + lane];
 #pragma unroll
-            for (int w = 1; w < NK; ++w) v[u] += red[((wn * NK + w) * NT + 4 * q + u) * 64 + lane];
+            for (int w = 1; w < NK; ++w)
+              v[t] += red[(((wn * NK + w) * NT + t) * 4 + r) * 64 + lane];
           }
-          store(a, q, v);
+          store(a, r, v);
         }
       }
     }
@@ -781,7 +825,11 @@ k_pair_force(const Geometry geo, const int2* __restrict__ hdr, const R* __restri
   const int group = (blockIdx.x % 8) * per + blockIdx.x / 8;
   const int ngroups = (geo.n + kGroup - 1) / kGroup;
   if (group >= ngroups) return;  // uniform over the work-group
-  const int cnt = min(gcount[group], cap);
+  // this work-group's part of the candidates, with its own force sums
+  const int full = min(gcount[group], cap);
+  const int clo = (int)((long)full * blockIdx.y / gridDim.y);
+  const int cnt = (int)((long)full * (blockIdx.y + 1) / gridDim.y);
+  fsum += (size_t)blockIdx.y * 3 * geo.n;
   const int2* H = hdr + (size_t)group * cap;
   const uint4* F4 = reinterpret_cast<const uint4*>(Fg + (size_t)group * cap * kCandStride);
   for (int pass = 0; pass < NPASS; ++pass) {
@@ -796,7 +844,7 @@ k_pair_force(const Geometry geo, const int2* __restrict__ hdr, const R* __restri
         G[k][a] = R(0);
       }
     }
-    for (int c0 = 0; c0 < cnt; c0 += CH) {
+    for (int c0 = clo; c0 < cnt; c0 += CH) {
       const int nc = min(CH, cnt - c0);
       __syncthreads();
       for (int w = tid; w < nc * W16; w += NT) Fl4[w] = F4[(size_t)c0 * W16 + w];
@@ -891,6 +939,7 @@ k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float*
   __shared__ int ml[kMfmaChunk];
   __shared__ double red[NK][kGroup][3];
   float* tl = reinterpret_cast<float*>(tl4);
+  fsum += (size_t)blockIdx.y * 3 * geo.n;
   const int lane = threadIdx.x & 63;
   const int wk = threadIdx.x >> 6;
   const int col = lane & 15, row = lane >> 4;
@@ -901,7 +950,11 @@ k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float*
   for (int gi = blockIdx.x / 8; gi < per; gi += nbx) {
     const int group = (blockIdx.x % 8) * per + gi;
     if (group >= ngroups) return;  // uniform over the work-group
-    const int cnt = min(gcount[group], cap);
+    // this work-group's part of the candidates (in blocks of 16), with its own force sums
+    const int full = min(gcount[group], cap);
+    const int q16 = (full + 15) / 16;
+    const int clo = 16 * (int)((long)q16 * blockIdx.y / gridDim.y);
+    const int cnt = min(full, 16 * (int)((long)q16 * (blockIdx.y + 1) / gridDim.y));
     const int2* H = hdr + (size_t)group * cap;
     const float* F = Fg + (size_t)group * cap * kCandStride;
     __syncthreads();  // the previous group's LDS contents have been read
@@ -915,7 +968,7 @@ k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float*
     double G[4][3];
 #pragma unroll
     for (int r = 0; r < 4; ++r) G[r][0] = G[r][1] = G[r][2] = 0.0;
-    for (int c0 = 0; c0 < cnt; c0 += kMfmaChunk) {
+    for (int c0 = clo; c0 < cnt; c0 += kMfmaChunk) {
       const int nc = min(kMfmaChunk, cnt - c0);
       __syncthreads();  // the previous chunk's lists have been read
       for (int c = threadIdx.x; c < nc; c += 64 * NK) {
@@ -1142,6 +1195,15 @@ long long count_pairs(const Geometry& g, const SysBuffers& b, hipStream_t st) {
 template long long count_pairs<float>(const Geometry&, const SysBuffers&, hipStream_t);
 template long long count_pairs<double>(const Geometry&, const SysBuffers&, hipStream_t);
 
+// Parts the field of a list launch comes in (partial sums over disjoint candidate ranges,
+// added by the gather): 1 for the vector list kernel and the neighbour list, otherwise
+// what the plan sized the buffer for.
+int pair_parts(const Geometry& g, const SysBuffers& b, int B) {
+  if (B <= 8 || g.replica_cut > 0.0) return 1;
+  const bool vec = b.pg_real == 4 && B >= 64 && g.pair_mode == 0;
+  return vec ? 1 : b.ed_parts;
+}
+
 // Target subsets per wavefront for the list kernels: at least 64 / B (every lane
 // busy); g.pair_ns when set and valid (a power of two, at least 64 / B, at most 4);
 // otherwise doubled (up to 4) while the launch would have fewer than 4096 wavefronts
@@ -1192,22 +1254,40 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
   const int nblk = pair_blocks(g, ngroups);
   const int2* H = b.pg_hdr;
   const R* T = (const R*)b.pg_T;
-  if constexpr (sizeof(R) == 4) {
-    // matrix cores: 128 right-hand sides per wavefront (64 when B = 64 or 192, or with
-    // pair_mode 2), B / wide column wavefronts x NK candidate shares per group (NK from
-    // pair_ns, at most 4 wavefronts per work-group)
-    if ((g.pair_mode == 1 || g.pair_mode == 2) && B % 64 == 0 && B <= 256) {
+  const int nparts = pair_parts(g, b, B);
+  const dim3 grd(nparts > 1 ? (ngroups + 7) / 8 * 8 : nblk, nparts);
+#define MBD_PM(NK, NT, NN)                                                                   \
+  k_pair_mfma<R, NK, NT, NN><<<grd, 64 * nn * nk, 0, st>>>(g, H, T, (const R*)b.pg_zero,    \
+                                                          b.pg_count, b.pg_cap, dv, Ed, B)
+  if constexpr (sizeof(R) == 8) {
+    // float64: always the matrix cores, up to 64 right-hand sides per wavefront, four
+    // wavefronts per group (3000 atoms, B = 16, r_c = 7 A: 424 us a launch with one vector
+    // lane per right-hand side and one work-group per group, 24 us here in 5 parts)
+    const int nn = B <= 64 ? 1 : B / 64, nk = 4 / nn;
+    switch (B) {
+      case 16: MBD_PM(4, 1, 1); break;
+      case 32: MBD_PM(4, 2, 1); break;
+      case 64: MBD_PM(4, 4, 1); break;
+      case 128: MBD_PM(2, 4, 2); break;
+      default: MBD_PM(1, 4, 4); break;
+    }
+    return;
+  } else {
+    // one wavefront holds the whole block, four share a group's candidates (648 atoms,
+    // B = 32: 298 us a launch of the vector kernel, 11 us here in 16 parts)
+    if (B < 64) {
+      const int nn = 1, nk = 4;
+      if (B == 16) MBD_PM(4, 1, 1); else MBD_PM(4, 2, 1);
+      return;
+    }
+    // 128 right-hand sides per wavefront (64 when B = 64 or 192, or with pair_mode 2),
+    // B / wide column wavefronts x NK candidate shares per group (NK from pair_ns, at most
+    // 4 wavefronts per work-group)
+    if (g.pair_mode == 1 || g.pair_mode == 2) {
       const int wide = (g.pair_mode == 1 && B % 128 == 0) ? 128 : 64;
       const int nn = B / wide;
       int nk = g.pair_ns > 0 ? g.pair_ns : 1;
       while (nk > 1 && nn * nk > 4) nk /= 2;
-      const dim3 blk(64 * nn * nk);
-      const float* Tf = (const float*)T;
-      const float* df = (const float*)dv;
-      float* Ef = (float*)Ed;
-#define MBD_PM(NK, NT, NN) \
-      k_pair_mfma<NK, NT, NN><<<nblk, blk, 0, st>>>(g, H, Tf, (const float*)b.pg_zero, b.pg_count, \
-                                            b.pg_cap, df, Ef, B)
       // (nk > 1 only with nn <= 2, and nn = 2 only with nk <= 2)
       if (nk == 1) {
         if (wide == 128) MBD_PM(1, 8, 1); else MBD_PM(1, 4, 1);
@@ -1216,28 +1296,25 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
       } else {
         if (nk == 4) MBD_PM(4, 4, 1); else if (nn == 1) MBD_PM(2, 4, 1); else MBD_PM(2, 4, 2);
       }
-#undef MBD_PM
       return;
     }
-  }
-  const int ns = pair_subsets(g, ngroups, B);
+#undef MBD_PM
+    const int ns = pair_subsets(g, ngroups, B);
 #define MBD_PL(NS, WP) \
   k_pair_list<R, NS, WP><<<nblk, 64 * WP, 0, st>>>(g, H, T, b.pg_count, b.pg_cap, dv, Ed, B)
-  switch (B * 16 + ns) {
-    case 16 * 16 + 4: MBD_PL(4, 1); break;
-    case 32 * 16 + 2: MBD_PL(2, 1); break;
-    case 32 * 16 + 4: MBD_PL(4, 2); break;
-    case 64 * 16 + 1: MBD_PL(1, 1); break;
-    case 64 * 16 + 2: MBD_PL(2, 2); break;
-    case 64 * 16 + 4: MBD_PL(4, 4); break;
-    case 128 * 16 + 1: MBD_PL(1, 2); break;
-    case 128 * 16 + 2: MBD_PL(2, 4); break;
-    case 128 * 16 + 4: MBD_PL(4, 8); break;
-    case 256 * 16 + 1: MBD_PL(1, 4); break;
-    case 256 * 16 + 2: MBD_PL(2, 8); break;
-    default: MBD_PL(4, 16); break;
-  }
+    switch (B * 16 + ns) {
+      case 64 * 16 + 1: MBD_PL(1, 1); break;
+      case 64 * 16 + 2: MBD_PL(2, 2); break;
+      case 64 * 16 + 4: MBD_PL(4, 4); break;
+      case 128 * 16 + 1: MBD_PL(1, 2); break;
+      case 128 * 16 + 2: MBD_PL(2, 4); break;
+      case 128 * 16 + 4: MBD_PL(4, 8); break;
+      case 256 * 16 + 1: MBD_PL(1, 4); break;
+      case 256 * 16 + 2: MBD_PL(2, 8); break;
+      default: MBD_PL(4, 16); break;
+    }
 #undef MBD_PL
+  }
 }
 
 template <typename R>
@@ -1268,10 +1345,10 @@ void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_
   const R* p = (const R*)b.dv;
   const R* q = (const R*)b.dq;
   if constexpr (sizeof(R) == 4) {
-    // matrix cores, with the matrix-core direct sum: four wavefronts per group
-    if ((g.pair_mode == 1 || g.pair_mode == 2) && B % 16 == 0 && B <= 128) {
-      // one work-group per group, whatever residency cap the direct sum runs with
-      k_pair_force_mfma<4><<<(ngroups + 7) / 8 * 8, 256, 0, st>>>(
+    // matrix cores, with the matrix-core direct sum: four wavefronts per group and part
+    if ((g.pair_mode == 1 || g.pair_mode == 2 || B < 64) && B % 16 == 0 && B <= 128) {
+      // every group resident, whatever residency cap the direct sum runs with
+      k_pair_force_mfma<4><<<dim3(nblk, b.fs_parts), 256, 0, st>>>(
           g, H, (const float*)F, b.pg_count, b.pg_cap, (const float*)p, (const float*)q,
           b.fsum + 3 * (size_t)g.n, B);
       return;
@@ -1284,7 +1361,7 @@ void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_
   int tw = 1;
   while (tw < 4 && tw * nsub < 16 && tw * rs < 16 && (long)ngroups * tw * rs < 4096) tw *= 2;
 #define MBD_PF(NS, TWV, RSV, TPV)                                                        \
-  k_pair_force<R, NS, TWV, RSV, TPV><<<nblk, 64 * TWV * RSV, 0, st>>>(                   \
+  k_pair_force<R, NS, TWV, RSV, TPV><<<dim3(nblk, b.fs_parts), 64 * TWV * RSV, 0, st>>>( \
       g, H, F, b.pg_count, b.pg_cap, p, q, b.fsum + 3 * (size_t)g.n, B)
   switch (B * 16 + tw) {
     case 4 * 16 + 1: MBD_PF(16, 1, 1, 1); break;

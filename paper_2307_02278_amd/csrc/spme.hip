@@ -173,7 +173,7 @@ template <typename R, int P, int BG>
 __global__ void __launch_bounds__(512)
 k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __restrict__ th,
                   const R* __restrict__ dth, const R* __restrict__ grid, size_t chunk_elems,
-                  const R* __restrict__ Ed, const double* __restrict__ w,
+                  const R* __restrict__ Ed, int ed_parts, const double* __restrict__ w,
                   const double* __restrict__ g, const double* __restrict__ om2, int B,
                   uint32_t comps, double self_coef, double* __restrict__ lt,
                   double* __restrict__ part, int chunk0) {
@@ -263,7 +263,11 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
         const size_t idx = ((size_t)s * 3 + a) * B + bg;
         const double wv = w[idx];
         double E = (a == 0) ? (double)e0 : (a == 1) ? (double)e1 : (double)e2;
-        if (comps & MBD_C_DIR) E += (double)Ed[idx];
+        if (comps & MBD_C_DIR) {
+          E += (double)Ed[idx];
+          for (int q = 1; q < ed_parts; ++q)
+            E += (double)Ed[(size_t)q * 3 * geo.n * B + idx];
+        }
         if (comps & MBD_C_SELF) E += self_coef * gs * wv;
         double l = gs * E;
         if (comps & MBD_C_DIAG) l += o2 * wv;
@@ -432,7 +436,7 @@ void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, 
 #define MBD_GATHER(PP, BB)                                                                  \
   k_gather_epilogue<R, PP, BB><<<grd, 64 * gather_waves(geo), 0, st>>>(                   \
       geo, b.base, (const R*)b.th, (const R*)b.dth, (const R*)b.grid, chunk,               \
-      (const R*)b.Ed, w, b.g, b.om2, B, comps, self_coef, b.Lt, b.part, chunk0)
+      (const R*)b.Ed, pair_parts(geo, b, B), w, b.g, b.om2, B, comps, self_coef, b.Lt, b.part, chunk0)
 #define MBD_GATHER_P(BB)                    \
   switch (geo.p) {                          \
     case 4: MBD_GATHER(4, BB); break;       \

@@ -6,6 +6,7 @@ ordered sums), 1e-5 for the direct part alone in mixed precision."""
 import numpy as np
 import pytest
 import torch
+from scipy.spatial import cKDTree
 
 import synth
 from oracle import method as om
@@ -25,10 +26,27 @@ def _random(n, L_ang, seed):
                         rng.uniform(5, 15, n), rng.uniform(0.3, 0.7, n), rng.uniform(3, 4, n))
 
 
+def _cutoff(s, rc_ang):
+    """A cutoff (bohr) near rc_ang with no pair within 1e-6 of it, relative (a float32
+    distance is good to about 3e-7): a pair at the
+    cutoff itself belongs to the float32 sum or not by its rounded distance, while the bare
+    cutoff of these plans (no damping tail) leaves it a finite tensor."""
+    L = s.cell[0, 0]
+    tree = cKDTree(s.pos % L, boxsize=L)
+    p = tree.query_pairs(min(rc_ang * A * 1.001, 0.499 * L), output_type="ndarray")
+    d = s.pos[p[:, 0]] - s.pos[p[:, 1]]
+    d -= L * np.round(d / L)
+    r = np.sort(np.concatenate([np.linalg.norm(d, axis=1), np.array([0.999, 1.001]) * rc_ang * A]))
+    r = r[r >= 0.999 * rc_ang * A]
+    k = int(np.argmax(np.diff(r)))
+    assert r[k + 1] - r[k] > 2e-6 * r[k]
+    return 0.5 * (r[k] + r[k + 1])
+
+
 def _plan(s, prec, block, rc_ang, grid):
     import paper_2307_02278_amd as P
     ds = P.DeviceSystem(s.pos, s.cell, s.alpha, s.omega, s.rvdw)
-    return P.Plan([ds], P.Params(real_cutoff=rc_ang * A, grid=grid, n_probes=block, n_steps=2,
+    return P.Plan([ds], P.Params(real_cutoff=_cutoff(s, rc_ang), grid=grid, n_probes=block, n_steps=2,
                                  block=block, precision=prec, damp_tol=-1.0))
 
 
@@ -76,3 +94,14 @@ def test_no_pair_in_range():
     plan = _plan(s, 0, 1, 5.0, (16, 16, 16))
     v = torch.ones(1, 1, 3, dtype=torch.float64).cuda()
     assert float(plan.matvec(v, components=2).abs().max()) == 0.0
+
+
+# one group (its list in 16 parts, some of them empty), a ragged second group, 16 groups and
+# enough groups for one part; every width of the float64 and the narrow mixed wavefronts
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,block", [(5, 16), (17, 32), (250, 16), (250, 64), (250, 128),
+                                     (131, 256), (8200, 16), (16400, 32)])
+def test_tensor_list_parts_match_the_oracle(n, block, prec):
+    s = _random(n, (n / 0.05) ** (1 / 3), seed=n + 1)
+    plan = _plan(s, prec, block, 6.0, (24, 24, 24))
+    assert _direct_error(plan, s, block) < TOL[prec]
