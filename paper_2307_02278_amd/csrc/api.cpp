@@ -540,7 +540,7 @@ void run_energy(Plan& plan, System& S, int sys_index, double* energy, double* sd
       void* slot = (forces && S.buf.phi) ? (void*)((R*)S.buf.phi + (size_t)k * gsz) : nullptr;
       matvec_block<R>(plan, S, S.buf.W + (size_t)k * vs, MBD_C_ALL, slot);
       staged(plan, MBD_STAGE_LANCZOS, [&] {
-        launch_finish_a(S.buf, B, nb, k, m, l0, plan.status, st);
+        launch_finish_a(S.buf, B, nb, k, m, l0, gather_blocks(S.geo, S.BG), plan.status, st);
         if (k + 1 < m) {
           const int ro = plan.prm.reorth;
           launch_update(S.geo, S.buf, B, nb, k, m, l0, fl, ro == MBD_REORTH_NONE, st);

@@ -300,10 +300,12 @@ void launch_update(const Geometry& g, const SysBuffers& b, int B, int nb, int k,
                    int probe0, bool use_float, bool write_d, hipStream_t st);
 void launch_reorth(const Geometry& g, const SysBuffers& b, int B, int nb, int k, int m,
                    int probe0, int j0, bool use_float, hipStream_t st);
-void launch_finish_a(const SysBuffers& b, int B, int nb, int k, int m, int probe0,
+void launch_finish_a(const SysBuffers& b, int B, int nb, int k, int m, int probe0, int ng,
                      uint32_t* status, hipStream_t st);
 void launch_finish_norm(const SysBuffers& b, int B, int nb, int k, int m, int probe0,
                         uint32_t* status, hipStream_t st);
+// Work-groups (and partial sums of a_k) of a gather over chunks of BG right-hand sides.
+int gather_blocks(const Geometry& g, int BG);
 void launch_tridiag(const SysBuffers& b, int nb, int m, int probe0, uint32_t* status,
                     hipStream_t st);
 void launch_energy(const Geometry& g, const SysBuffers& b, int R, double* energy_out,

@@ -130,13 +130,14 @@ k_dot(int n, int B, const double* __restrict__ x, const double* __restrict__ y,
   if (threadIdx.x < RB && b < B) part[((size_t)blockIdx.x * kPartSlots + slot) * B + b] = red[threadIdx.x];
 }
 
-// Sum the per-block partials of one slot for each RHS, in a fixed order.
+// Sum the nblk per-block partials of one slot for each RHS, in a fixed order.
 __global__ void __launch_bounds__(256)
-k_sum_slot(int B, int slot, const double* __restrict__ part, double* __restrict__ out) {
+k_sum_slot(int B, int slot, int nblk, const double* __restrict__ part,
+           double* __restrict__ out) {
   __shared__ double red[256];
   const int b = blockIdx.x;
   double s = 0.0;
-  for (int k = threadIdx.x; k < kRedBlocks; k += 256) s += part[((size_t)k * kPartSlots + slot) * B + b];
+  for (int k = threadIdx.x; k < nblk; k += 256) s += part[((size_t)k * kPartSlots + slot) * B + b];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int h = 128; h > 0; h >>= 1) {
@@ -667,7 +668,7 @@ void launch_reorth(const Geometry& geo, const SysBuffers& b, int B, int nb, int 
     for (int j = c0; j < c1; ++j) {
       MBD_RB_SWITCH(rb, (k_dot<RB><<<grd, 256, 0, st>>>(geo.n, B, w, b.W + (size_t)j * vs,
                                                         b.part, 2)));
-      k_sum_slot<<<B, 256, 0, st>>>(B, 2, b.part, b.coef + (size_t)(j - c0) * B);
+      k_sum_slot<<<B, 256, 0, st>>>(B, 2, kRedBlocks, b.part, b.coef + (size_t)(j - c0) * B);
     }
     MBD_RB_SWITCH(rb, (k_orth_apply<RB><<<grd, 256, 0, st>>>(
                            geo.n, B, nb, m, probe0, b.W, vs, c0, c1, b.coef, b.b, b.meff, k,
@@ -675,16 +676,16 @@ void launch_reorth(const Geometry& geo, const SysBuffers& b, int B, int nb, int 
   }
 }
 
-void launch_finish_a(const SysBuffers& b, int B, int nb, int k, int m, int probe0,
+void launch_finish_a(const SysBuffers& b, int B, int nb, int k, int m, int probe0, int ng,
                      uint32_t* status, hipStream_t st) {
-  k_sum_slot<<<B, 256, 0, st>>>(B, 0, b.part, b.coef);
+  k_sum_slot<<<B, 256, 0, st>>>(B, 0, ng, b.part, b.coef);
   k_finish_a<<<(nb + 63) / 64, 64, 0, st>>>(B, nb, k, m, probe0, b.coef, b.b, b.a, b.meff,
                                             status);
 }
 
 void launch_finish_norm(const SysBuffers& b, int B, int nb, int k, int m, int probe0,
                         uint32_t* status, hipStream_t st) {
-  k_sum_slot<<<B, 256, 0, st>>>(B, 1, b.part, b.coef);
+  k_sum_slot<<<B, 256, 0, st>>>(B, 1, kRedBlocks, b.part, b.coef);
   k_finish_norm<<<(nb + 63) / 64, 64, 0, st>>>(B, nb, k, m, probe0, b.coef, b.b, b.a, b.meff,
                                                status);
 }
@@ -731,7 +732,7 @@ void launch_adjoint_step(const Geometry& geo, const SysBuffers& b, int B, int nb
     MBD_RB_SWITCH(rb, (k_adj_dots<RB><<<grd, 256, 0, st>>>(geo.n, B, yn, wn, wk, wkm1,
                                                            k > 0 ? 1 : 0, b.part)));
     for (int q = 0; q < 5; ++q)
-      k_sum_slot<<<B, 256, 0, st>>>(B, q, b.part, b.coef + (size_t)q * B);
+      k_sum_slot<<<B, 256, 0, st>>>(B, q, kRedBlocks, b.part, b.coef + (size_t)q * B);
   } else {
     fill_double(b.coef, 0.0, (size_t)5 * B, st);
   }

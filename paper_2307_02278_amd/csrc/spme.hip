@@ -16,26 +16,48 @@
 //   l~ = Omega w + Diag(g) E*      (eq. lk3, in double precision)
 // with per-block partial sums of w . l~ for a_k (eq. recurs2). Again one wavefront
 // per atom and one lane per right-hand side.
+#include <algorithm>
+
 #include "common.h"
 
 namespace mbd {
 
 namespace {
 
-// Lanes of a wavefront: BG right-hand sides x NSUB sub-lanes that share the stencil.
+// Lanes of a gather wavefront: BG right-hand sides x NS sub-lanes that share one atom's
+// stencil rows (the P^2 (y, z) rows of P points) x AW atoms. Narrow chunks keep NS at 16 or
+// less, because 36 rows over 64 sub-lanes leave 28 of them idle, and take several atoms per
+// wavefront instead.
 template <int BG>
 struct Lanes {
-  static constexpr int NSUB = 64 / BG;
+  static constexpr int NS = BG >= 8 ? 64 / BG : (BG == 4 ? 8 : 16);
+  static constexpr int LA = BG * NS;   // lanes per atom
+  static constexpr int AW = 64 / LA;   // atoms per wavefront
+};
+
+// The tile points of a spread lane: NSUB = 64 / BG sub-lanes split the 4x4x4 points of a
+// tile into NX x NY x NZ bricks, so that a lane's weights along each axis are a run of the
+// staged ones.
+template <int BG>
+struct Brick {
+  static constexpr int T = kSpreadTile;
+  static constexpr int NP = T * T * T * BG / 64;  // points per lane
+  static constexpr int NX = NP < T ? NP : T;
+  static constexpr int NY = NP / NX < T ? NP / NX : T;
+  static constexpr int NZ = NP / (NX * NY);
+  static constexpr int BX = T / NX, BY = T / NY;  // bricks per tile along x and y
 };
 
 // Spread with register tiles: one wavefront owns a 4x4x4 tile of grid points for BG
-// right-hand sides and keeps the 64 point values of its lane in registers
-// (64 / NSUB per lane when fewer than 64 right-hand sides share the wavefront).
+// right-hand sides and keeps the point values of its lane in registers (64, or the BG of
+// its brick when fewer than 64 right-hand sides share the wavefront).
 // It walks the tile's atom list in a fixed order, so the result is deterministic.
-// For one atom the weights along each axis of the tile are uniform scalars:
+// For one atom the weights along each axis of the tile are
 //   w_a(q) = M_p(u_a - k_a) for the tile point k_a = tile origin + q,
 // nonzero only when 0 <= t = (base_a - k_a) mod K_a < p, i.e. t = o_a - q with
-// o_a = (base_a - origin_a) mod K_a.
+// o_a = (base_a - origin_a) mod K_a; a batch of atoms at a time has them staged in LDS.
+// Narrow chunks are bound by the latency of the dipole loads, so they take four atoms'
+// dipoles at a time, and up to 8 right-hand sides stage them beside the weights.
 template <typename R, int P, int BG>
 __global__ void __launch_bounds__(256)
 k_spread(const Geometry geo, const int* __restrict__ tile_start,
@@ -43,11 +65,18 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
          const R* __restrict__ th, const R* __restrict__ dth, const R* __restrict__ dv, int B,
          R* __restrict__ grid, size_t chunk_elems, int chunk0) {
   constexpr int T = kSpreadTile;
-  constexpr int NSUB = Lanes<BG>::NSUB;
-  constexpr int NP = T * T * T / NSUB;  // points per lane
+  typedef Brick<BG> Bk;
+  constexpr int NX = Bk::NX, NY = Bk::NY, NZ = Bk::NZ;
   constexpr int NWT = 6 * T;            // staged weights per atom: w, dw along x, y, z
-  __shared__ R wts_all[4][64][NWT];
-  __shared__ int sat_all[4][64];        // atom index of each staged slot
+  // atoms per batch: about 20 touch a tile at 0.1 atoms per A^3 and 1.5 points per A; the
+  // stage of a work-group stays at 24 KB, so that LDS does not limit the resident waves
+  constexpr int NBAT = BG == 64 ? 64 : (sizeof(R) == 8 ? 16 : 32);
+  constexpr int NPART = 64 / NBAT;      // staging lanes per atom
+  constexpr bool DLDS = BG <= 8;        // dipoles staged too
+  constexpr int PF = BG == 64 ? 1 : 4;  // dipoles in flight (atoms) otherwise
+  __shared__ R wts_all[4][NBAT][NWT];
+  __shared__ R dip_all[4][DLDS ? NBAT : 1][DLDS ? 3 * BG : 1];
+  __shared__ int sat_all[4][NBAT];      // atom index of each staged slot
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int lane = threadIdx.x & 63;
   R(*wts)[NWT] = wts_all[wave];
@@ -63,39 +92,50 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
   const int b = lane % BG;
   const int sub = lane / BG;
   const int bg = chunk * BG + b;
+  // origin of the lane's brick in the tile
+  const int px0 = (sub % Bk::BX) * NX, py0 = (sub / Bk::BX % Bk::BY) * NY,
+            pz0 = sub / (Bk::BX * Bk::BY) * NZ;
   const int tx = tile % geo.tiles[0];
   const int ty = (tile / geo.tiles[0]) % geo.tiles[1];
   const int tz = tile / (geo.tiles[0] * geo.tiles[1]);
   const int x0 = tx * T, y0 = ty * T, z0 = tz * T;
   const int K1 = geo.K[0], K2 = geo.K[1], K3 = geo.K[2];
-  R acc[NP];
+  R acc[NX * NY * NZ];
 #pragma unroll
-  for (int i = 0; i < NP; ++i) acc[i] = R(0);
+  for (int i = 0; i < NX * NY * NZ; ++i) acc[i] = R(0);
   const int lo = tile_start[tile], hi = tile_start[tile + 1];
-  for (int a0 = lo; a0 < hi; a0 += 64) {
-    const int na = min(64, hi - a0);
-    // Stage: lane i computes the tile-clipped weights of the batch's atom i.
-    // For one atom the weights along each axis of the tile are
-    //   w_a(q) = M_p(u_a - k_a) at the tile point k_a = origin_a + q,
-    // nonzero only when t = o_a - q lies in [0, p), o_a = (base_a - origin_a) mod K_a.
-    if (lane < na) {
-      const int s = tile_atoms[a0 + lane];
-      int o[3] = {base[3 * s] - x0, base[3 * s + 1] - y0, base[3 * s + 2] - z0};
-      if (o[0] < 0) o[0] += K1;
-      if (o[1] < 0) o[1] += K2;
-      if (o[2] < 0) o[2] += K3;
-      const R* thp = th + (size_t)s * 3 * P;
-      const R* dthp = dth + (size_t)s * 3 * P;
+  for (int a0 = lo; a0 < hi; a0 += NBAT) {
+    const int na = min(NBAT, hi - a0);
+    // Stage: lane i computes the tile-clipped weights of the batch's atom i % NBAT, the
+    // NPART lanes of an atom every NPART-th of its six weight rows.
+    {
+      const int i = lane % NBAT, part = lane / NBAT;
+      if (i < na) {
+        const int s = tile_atoms[a0 + i];
+        int o[3] = {base[3 * s] - x0, base[3 * s + 1] - y0, base[3 * s + 2] - z0};
+        if (o[0] < 0) o[0] += K1;
+        if (o[1] < 0) o[1] += K2;
+        if (o[2] < 0) o[2] += K3;
+        const R* thp = th + (size_t)s * 3 * P;
+        const R* dthp = dth + (size_t)s * 3 * P;
 #pragma unroll
-      for (int ax = 0; ax < 3; ++ax)
+        for (int ax = 0; ax < 3; ++ax)
 #pragma unroll
-        for (int q = 0; q < T; ++q) {
-          const int t = o[ax] - q;
-          const bool v = t >= 0 && t < P;
-          wts[lane][(2 * ax) * T + q] = v ? thp[ax * P + t] : R(0);
-          wts[lane][(2 * ax + 1) * T + q] = v ? dthp[ax * P + t] : R(0);
+          for (int d = 0; d < 2; ++d) {
+            if ((2 * ax + d) % NPART != part) continue;
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+              const int t = o[ax] - q;
+              const bool v = t >= 0 && t < P;
+              wts[i][(2 * ax + d) * T + q] = v ? (d ? dthp : thp)[ax * P + t] : R(0);
+            }
+          }
+        if (part == 0) sat[i] = s;
+        if constexpr (DLDS) {
+          for (int e = part; e < 3 * BG; e += NPART)
+            dip_all[wave][i][e] = dv[((size_t)s * 3 + e / BG) * B + chunk * BG + e % BG];
         }
-      sat[lane] = s;
+      }
     }
     // the batch's LDS writes are visible to the whole wavefront before it reads them
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -104,53 +144,60 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
     const R m00 = (R)geo.Mu[0][0], m01 = (R)geo.Mu[0][1], m02 = (R)geo.Mu[0][2];
     const R m10 = (R)geo.Mu[1][0], m11 = (R)geo.Mu[1][1], m12 = (R)geo.Mu[1][2];
     const R m20 = (R)geo.Mu[2][0], m21 = (R)geo.Mu[2][1], m22 = (R)geo.Mu[2][2];
-    int s = __builtin_amdgcn_readfirstlane(sat[0]);
-    R n0 = dv[((size_t)s * 3 + 0) * B + bg];
-    R n1 = dv[((size_t)s * 3 + 1) * B + bg];
-    R n2 = dv[((size_t)s * 3 + 2) * B + bg];
-    for (int a = 0; a < na; ++a) {
-      // dipole in u: (Mu d)_b
-      const R d0 = m00 * n0 + m01 * n1 + m02 * n2;
-      const R d1 = m10 * n0 + m11 * n1 + m12 * n2;
-      const R d2 = m20 * n0 + m21 * n1 + m22 * n2;
-      if (a + 1 < na) {  // next atom's dipoles while this one is spread
-        s = __builtin_amdgcn_readfirstlane(sat[a + 1]);
-        n0 = dv[((size_t)s * 3 + 0) * B + bg];
-        n1 = dv[((size_t)s * 3 + 1) * B + bg];
-        n2 = dv[((size_t)s * 3 + 2) * B + bg];
-      }
-      const R* wa = wts[a];
-      R wx[T], dwx[T], wy[T], dwy[T], wz[T], dwz[T];
+    // dipoles of PF atoms from slot a on (past the batch: its last atom again, unused)
+    auto fetch = [&](int a, R (&n)[PF][3]) {
 #pragma unroll
-      for (int q = 0; q < T; ++q) {
-        wx[q] = wa[q]; dwx[q] = wa[T + q];
-        wy[q] = wa[2 * T + q]; dwy[q] = wa[3 * T + q];
-        wz[q] = wa[4 * T + q]; dwz[q] = wa[5 * T + q];
+      for (int u = 0; u < PF; ++u) {
+        const int i = min(a + u, na - 1);
+        if constexpr (DLDS) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) n[u][c] = dip_all[wave][i][c * BG + b];
+        } else {
+          const int s = __builtin_amdgcn_readfirstlane(sat[i]);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) n[u][c] = dv[((size_t)s * 3 + c) * B + bg];
+        }
       }
-      if (NSUB == 1) {
-        // every point of the tile: the staged weights are zero outside the stencil, and
+    };
+    R nx[PF][3];
+    fetch(0, nx);
+    for (int a = 0; a < na; a += PF) {
+      R cur[PF][3];
+#pragma unroll
+      for (int u = 0; u < PF; ++u)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) cur[u][c] = nx[u][c];
+      if (a + PF < na) fetch(a + PF, nx);  // next dipoles while these are spread
+#pragma unroll
+      for (int u = 0; u < PF; ++u) {
+        if (PF > 1 && a + u >= na) break;  // uniform over the wavefront
+        // dipole in u: (Mu d)_b
+        const R d0 = m00 * cur[u][0] + m01 * cur[u][1] + m02 * cur[u][2];
+        const R d1 = m10 * cur[u][0] + m11 * cur[u][1] + m12 * cur[u][2];
+        const R d2 = m20 * cur[u][0] + m21 * cur[u][1] + m22 * cur[u][2];
+        const R* wa = wts[a + u];
+        R wx[NX], dwx[NX], wy[NY], dwy[NY], wz[NZ], dwz[NZ];
+#pragma unroll
+        for (int q = 0; q < NX; ++q) { wx[q] = wa[px0 + q]; dwx[q] = wa[T + px0 + q]; }
+#pragma unroll
+        for (int q = 0; q < NY; ++q) { wy[q] = wa[2 * T + py0 + q]; dwy[q] = wa[3 * T + py0 + q]; }
+#pragma unroll
+        for (int q = 0; q < NZ; ++q) { wz[q] = wa[4 * T + pz0 + q]; dwz[q] = wa[5 * T + pz0 + q]; }
+        // every point of the brick: the staged weights are zero outside the stencil, and
         // a branch-free loop issues fewer instructions than uniform per-point tests
 #pragma unroll
-        for (int pz = 0; pz < T; ++pz) {
+        for (int pz = 0; pz < NZ; ++pz) {
 #pragma unroll
-          for (int py = 0; py < T; ++py) {
+          for (int py = 0; py < NY; ++py) {
             const R A = d0 * wy[py] * wz[pz];
             const R Bc = d1 * dwy[py] * wz[pz] + d2 * wy[py] * dwz[pz];
 #pragma unroll
-            for (int px = 0; px < T; ++px) {
-              R& q = acc[(pz * T + py) * T + px];
+            for (int px = 0; px < NX; ++px) {
+              R& q = acc[(pz * NY + py) * NX + px];
               q = fma(dwx[px], A, q);
               q = fma(wx[px], Bc, q);
             }
           }
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-          const int p = sub + i * NSUB;
-          const int px = p % T, py = (p / T) % T, pz = p / (T * T);
-          acc[i] += (dwx[px] * wy[py] * wz[pz]) * d0 + (wx[px] * dwy[py] * wz[pz]) * d1 +
-                    (wx[px] * wy[py] * dwz[pz]) * d2;
         }
       }
     }
@@ -162,11 +209,20 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
   R* g = grid + (size_t)chunk * chunk_elems;
   const int XS = K1 + 2;
 #pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int p = sub + i * NSUB;
-    const int x = x0 + p % T, y = y0 + (p / T) % T, z = z0 + p / (T * T);
+  for (int i = 0; i < NX * NY * NZ; ++i) {
+    const int x = x0 + px0 + i % NX, y = y0 + py0 + (i / NX) % NY, z = z0 + pz0 + i / (NX * NY);
     if (x < K1 && y < K2 && z < K3) g[(((size_t)z * K2 + y) * XS + x) * BG + b] = acc[i];
   }
+}
+
+// Row r = P t3 + t2 of an atom's stencil rows: its first grid value (without the x index).
+template <typename R, int P, int BG>
+__device__ __forceinline__ const R* stencil_row(const R* gr, int by, int bz, int t2, int t3,
+                                                int K2, int K3, int XS) {
+  int k2 = by - t2, k3 = bz - t3;
+  if (k2 < 0) k2 += K2;
+  if (k3 < 0) k3 += K3;
+  return gr + ((size_t)k3 * K2 + k2) * XS * BG;
 }
 
 template <typename R, int P, int BG>
@@ -177,13 +233,13 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
                   const double* __restrict__ g, const double* __restrict__ om2, int B,
                   uint32_t comps, double self_coef, double* __restrict__ lt,
                   double* __restrict__ part, int chunk0) {
-  constexpr int NSUB = Lanes<BG>::NSUB;
-  __shared__ double red[512];
+  constexpr int NS = Lanes<BG>::NS, LA = Lanes<BG>::LA, AW = Lanes<BG>::AW;
+  __shared__ double red[8 * BG];
   const int nw = blockDim.x >> 6;  // wavefronts per work-group (4 or 8)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int lane = threadIdx.x & 63;
   const int b = lane % BG;
-  const int sub = lane / BG;
+  const int sub = lane % LA / BG;
   const int chunk = blockIdx.y + chunk0;
   const int bg = chunk * BG + b;
   const R* gr = grid + (size_t)chunk * chunk_elems;
@@ -192,26 +248,25 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
   double dot = 0.0;
   // Blocks are dealt round-robin to the 8 XCDs. Each XCD takes one contiguous range
   // of sorted atoms and sweeps it with all of its wavefronts side by side (wave lw
-  // takes atoms lo + lw, lo + lw + nwx, ...), so the atoms in flight on an XCD at
-  // any time are consecutive, i.e. spatially compact, and their stencils share L2.
+  // takes atoms lo + AW lw, lo + AW (lw + nwx), ...), so the atoms in flight on an XCD
+  // at any time are consecutive, i.e. spatially compact, and their stencils share L2.
   const int nb8 = gridDim.x / 8;
   const int xcd = blockIdx.x % 8;
   const int nwx = nb8 * nw;
   const int lw = (blockIdx.x / 8) * nw + wave;
   const int x_lo = (int)(((long)geo.n * xcd) / 8);
   const int x_hi = (int)(((long)geo.n * (xcd + 1)) / 8);
-  for (int s = x_lo + lw; s < x_hi; s += nwx) {
+  for (int s0 = x_lo + lw * AW; s0 < x_hi; s0 += nwx * AW) {
+    // (past the range: its last atom again, computed and dropped)
+    const int s = AW == 1 ? s0 : min(s0 + lane / LA, x_hi - 1);
+    const bool valid = AW == 1 || s0 + lane / LA < x_hi;
     R e0 = R(0), e1 = R(0), e2 = R(0);
     if (comps & MBD_C_REC) {
       const R* thp = th + s * 3 * P;
       const R* dthp = dth + s * 3 * P;
-      R mx[P], dmx[P], my[P], dmy[P], mz[P], dmz[P];
+      R mx[P], dmx[P];
 #pragma unroll
-      for (int t = 0; t < P; ++t) {
-        mx[t] = thp[t]; dmx[t] = dthp[t];
-        my[t] = thp[P + t]; dmy[t] = dthp[P + t];
-        mz[t] = thp[2 * P + t]; dmz[t] = dthp[2 * P + t];
-      }
+      for (int t = 0; t < P; ++t) { mx[t] = thp[t]; dmx[t] = dthp[t]; }
       const int bx = base[3 * s], by = base[3 * s + 1], bz = base[3 * s + 2];
       int kxs[P];
 #pragma unroll
@@ -220,46 +275,66 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
         if (k1 < 0) k1 += K1;
         kxs[t1] = k1 * BG + b;
       }
+      auto row = [&](const R* line, R my, R dmy, R mz, R dmz) {
+        R sx = R(0), sy = R(0);
 #pragma unroll
-      for (int t3 = 0; t3 < P; ++t3) {
-        int k3 = bz - t3;
-        if (k3 < 0) k3 += K3;
+        for (int t1 = 0; t1 < P; ++t1) {
+          const R phi = line[kxs[t1]];
+          sx += dmx[t1] * phi;
+          sy += mx[t1] * phi;
+        }
+        e0 += sx * my * mz;
+        e1 += sy * dmy * mz;
+        e2 += sy * my * dmz;
+      };
+      if constexpr (NS == 1) {
+        R my[P], dmy[P], mz[P], dmz[P];
 #pragma unroll
-        for (int t2 = 0; t2 < P; ++t2) {
-          if ((t3 * P + t2) % NSUB != sub) continue;
-          int k2 = by - t2;
-          if (k2 < 0) k2 += K2;
-          const R* line = gr + ((size_t)k3 * K2 + k2) * XS * BG;
-          R sx = R(0), sy = R(0);
+        for (int t = 0; t < P; ++t) {
+          my[t] = thp[P + t]; dmy[t] = dthp[P + t];
+          mz[t] = thp[2 * P + t]; dmz[t] = dthp[2 * P + t];
+        }
 #pragma unroll
-          for (int t1 = 0; t1 < P; ++t1) {
-            const R phi = line[kxs[t1]];
-            sx += dmx[t1] * phi;
-            sy += mx[t1] * phi;
-          }
-          e0 += sx * my[t2] * mz[t3];
-          e1 += sy * dmy[t2] * mz[t3];
-          e2 += sy * my[t2] * dmz[t3];
+        for (int t3 = 0; t3 < P; ++t3)
+#pragma unroll
+          for (int t2 = 0; t2 < P; ++t2)
+            row(stencil_row<R, P, BG>(gr, by, bz, t2, t3, K2, K3, XS), my[t2], dmy[t2], mz[t3],
+                dmz[t3]);
+      } else {
+        // the rows r = sub, sub + NS, ... with the row index in a register: one pass over
+        // ceil(P^2 / NS) rows for the whole wavefront (unrolled over all P^2 rows with a
+        // test per row, every row is issued for the sake of the few lanes that own it)
+        constexpr int NR = (P * P + NS - 1) / NS;
+#pragma unroll (NR <= 5 ? NR : 3)
+        for (int i = 0; i < NR; ++i) {
+          const int r = min(sub + i * NS, P * P - 1);
+          const bool own = sub + i * NS < P * P;
+          const int t3 = r / P, t2 = r % P;
+          const R mz = own ? thp[2 * P + t3] : R(0), dmz = own ? dthp[2 * P + t3] : R(0);
+          row(stencil_row<R, P, BG>(gr, by, bz, t2, t3, K2, K3, XS), thp[P + t2], dthp[P + t2],
+              mz, dmz);
         }
       }
       // combine the sub-lanes that split the stencil rows
 #pragma unroll
-      for (int off = BG; off < 64; off <<= 1) {
+      for (int off = BG; off < LA; off <<= 1) {
         e0 += __shfl_xor(e0, off);
         e1 += __shfl_xor(e1, off);
         e2 += __shfl_xor(e2, off);
       }
-      // gradient in u -> Cartesian: E_c = sum_b Mu[b][c] (dE/du_b)
+      // gradient in u -> gradient in R: Mu^T
       const R g0 = e0, g1 = e1, g2 = e2;
       e0 = (R)geo.Mu[0][0] * g0 + (R)geo.Mu[1][0] * g1 + (R)geo.Mu[2][0] * g2;
       e1 = (R)geo.Mu[0][1] * g0 + (R)geo.Mu[1][1] * g1 + (R)geo.Mu[2][1] * g2;
       e2 = (R)geo.Mu[0][2] * g0 + (R)geo.Mu[1][2] * g1 + (R)geo.Mu[2][2] * g2;
     }
-    if (sub == 0) {
+    // one component per sub-lane where there are at least three
+    if (valid && sub < 3) {
       const double gs = g[s];
       const double o2 = om2[s];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
+        if (NS >= 4 ? a != sub : sub != 0) continue;
         const size_t idx = ((size_t)s * 3 + a) * B + bg;
         const double wv = w[idx];
         double E = (a == 0) ? (double)e0 : (a == 1) ? (double)e1 : (double)e2;
@@ -276,13 +351,14 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
       }
     }
   }
-  // per-RHS sum over the work-group's wavefronts (sub-lanes hold zero)
-  red[threadIdx.x] = dot;
+  // per-RHS sum over the lanes of a right-hand side, then the work-group's wavefronts
+#pragma unroll
+  for (int off = BG; off < 64; off <<= 1) dot += __shfl_xor(dot, off);
+  if (lane < BG) red[wave * BG + lane] = dot;
   __syncthreads();
   if (threadIdx.x < BG) {
     double t = 0.0;
-    for (int wv = 0; wv < nw; ++wv)
-      for (int sb = 0; sb < NSUB; ++sb) t += red[wv * 64 + sb * BG + threadIdx.x];
+    for (int wv = 0; wv < nw; ++wv) t += red[wv * BG + threadIdx.x];
     part[((size_t)blockIdx.x * kPartSlots + 0) * B + chunk * BG + threadIdx.x] = t;
   }
 }
@@ -300,12 +376,12 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
              const R* __restrict__ dth, const R* __restrict__ ddth, const R* __restrict__ grid,
              size_t chunk_elems, const R* __restrict__ hv, int B, int chunk0,
              double* __restrict__ fsum, const double* __restrict__ hscale) {
-  constexpr int NSUB = Lanes<BG>::NSUB;
+  constexpr int NS = Lanes<BG>::NS, LA = Lanes<BG>::LA, AW = Lanes<BG>::AW;
   const int nw = blockDim.x >> 6;  // wavefronts per work-group (4 or 8)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int lane = threadIdx.x & 63;
   const int b = lane % BG;
-  const int sub = lane / BG;
+  const int sub = lane % LA / BG;
   const int chunk = blockIdx.y + chunk0;
   const int bg = chunk * BG + b;
   const R* gr = grid + (size_t)chunk * chunk_elems;
@@ -317,15 +393,16 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
   const int lw = (blockIdx.x / 8) * nw + wave;
   const int x_lo = (int)(((long)geo.n * xcd) / 8);
   const int x_hi = (int)(((long)geo.n * (xcd + 1)) / 8);
-  for (int s = x_lo + lw; s < x_hi; s += nwx) {
+  for (int s0 = x_lo + lw * AW; s0 < x_hi; s0 += nwx * AW) {
+    const int s = AW == 1 ? s0 : min(s0 + lane / LA, x_hi - 1);
+    const bool valid = AW == 1 || s0 + lane / LA < x_hi;
     const R* tp = th + (size_t)s * 3 * P;
     const R* dp = dth + (size_t)s * 3 * P;
     const R* ddp = ddth + (size_t)s * 3 * P;
-    R mx[P], dmx[P], ddmx[P], my[P], dmy[P], ddmy[P];
+    R mx[P], dmx[P], ddmx[P];
 #pragma unroll
     for (int t = 0; t < P; ++t) {
       mx[t] = tp[t]; dmx[t] = dp[t]; ddmx[t] = ddp[t];
-      my[t] = tp[P + t]; dmy[t] = dp[P + t]; ddmy[t] = ddp[P + t];
     }
     const int bx = base[3 * s], by = base[3 * s + 1], bz = base[3 * s + 2];
     int kxs[P];
@@ -336,33 +413,49 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
       kxs[t1] = k1 * BG + b;
     }
     R hxx = R(0), hyy = R(0), hzz = R(0), hxy = R(0), hxz = R(0), hyz = R(0);
-    // one z plane of the stencil at a time (not unrolled: unrolled, the compiler keeps
-    // all p^3 grid values of an atom in flight and the kernel runs at 2 waves per SIMD)
+    auto row = [&](const R* line, R my, R dmy, R ddmy, R mz3, R dmz3, R ddmz3) {
+      R s0 = R(0), s1 = R(0), s2 = R(0);
+#pragma unroll
+      for (int t1 = 0; t1 < P; ++t1) {
+        const R phi = line[kxs[t1]];
+        s0 += mx[t1] * phi;
+        s1 += dmx[t1] * phi;
+        s2 += ddmx[t1] * phi;
+      }
+      hxx += s2 * my * mz3;
+      hyy += s0 * ddmy * mz3;
+      hzz += s0 * my * ddmz3;
+      hxy += s1 * dmy * mz3;
+      hxz += s1 * my * dmz3;
+      hyz += s0 * dmy * dmz3;
+    };
+    if constexpr (NS == 1) {
+      R my[P], dmy[P], ddmy[P];
+#pragma unroll
+      for (int t = 0; t < P; ++t) {
+        my[t] = tp[P + t]; dmy[t] = dp[P + t]; ddmy[t] = ddp[P + t];
+      }
+      // one z plane of the stencil at a time (not unrolled: unrolled, the compiler keeps
+      // all p^3 grid values of an atom in flight and the kernel runs at 2 waves per SIMD)
 #pragma unroll 1
-    for (int t3 = 0; t3 < P; ++t3) {
-      const R mz3 = tp[2 * P + t3], dmz3 = dp[2 * P + t3], ddmz3 = ddp[2 * P + t3];
-      int k3 = bz - t3;
-      if (k3 < 0) k3 += K3;
+      for (int t3 = 0; t3 < P; ++t3) {
+        const R mz3 = tp[2 * P + t3], dmz3 = dp[2 * P + t3], ddmz3 = ddp[2 * P + t3];
 #pragma unroll
-      for (int t2 = 0; t2 < P; ++t2) {
-        if ((t3 * P + t2) % NSUB != sub) continue;
-        int k2 = by - t2;
-        if (k2 < 0) k2 += K2;
-        const R* line = gr + ((size_t)k3 * K2 + k2) * XS * BG;
-        R s0 = R(0), s1 = R(0), s2 = R(0);
-#pragma unroll
-        for (int t1 = 0; t1 < P; ++t1) {
-          const R phi = line[kxs[t1]];
-          s0 += mx[t1] * phi;
-          s1 += dmx[t1] * phi;
-          s2 += ddmx[t1] * phi;
-        }
-        hxx += s2 * my[t2] * mz3;
-        hyy += s0 * ddmy[t2] * mz3;
-        hzz += s0 * my[t2] * ddmz3;
-        hxy += s1 * dmy[t2] * mz3;
-        hxz += s1 * my[t2] * dmz3;
-        hyz += s0 * dmy[t2] * dmz3;
+        for (int t2 = 0; t2 < P; ++t2)
+          row(stencil_row<R, P, BG>(gr, by, bz, t2, t3, K2, K3, XS), my[t2], dmy[t2], ddmy[t2],
+              mz3, dmz3, ddmz3);
+      }
+    } else {
+      // rows by register index, as in the gather
+      constexpr int NR = (P * P + NS - 1) / NS;
+#pragma unroll 3
+      for (int i = 0; i < NR; ++i) {
+        const int r = min(sub + i * NS, P * P - 1);
+        const bool own = sub + i * NS < P * P;
+        const int t3 = r / P, t2 = r % P;
+        row(stencil_row<R, P, BG>(gr, by, bz, t2, t3, K2, K3, XS), tp[P + t2], dp[P + t2],
+            ddp[P + t2], own ? tp[2 * P + t3] : R(0), own ? dp[2 * P + t3] : R(0),
+            own ? ddp[2 * P + t3] : R(0));
       }
     }
     const size_t o = (size_t)s * 3 * B + bg;
@@ -379,12 +472,13 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
     double f0 = (double)((R)geo.Mu[0][0] * u0 + (R)geo.Mu[1][0] * u1 + (R)geo.Mu[2][0] * u2);
     double f1 = (double)((R)geo.Mu[0][1] * u0 + (R)geo.Mu[1][1] * u1 + (R)geo.Mu[2][1] * u2);
     double f2 = (double)((R)geo.Mu[0][2] * u0 + (R)geo.Mu[1][2] * u1 + (R)geo.Mu[2][2] * u2);
-    for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+    for (int off = 1; off < LA; off <<= 1) {
       f0 += __shfl_xor(f0, off);
       f1 += __shfl_xor(f1, off);
       f2 += __shfl_xor(f2, off);
     }
-    if (lane == 0) {
+    if (valid && lane % LA == 0) {
       fsum[3 * (size_t)s] += f0;
       fsum[3 * (size_t)s + 1] += f1;
       fsum[3 * (size_t)s + 2] += f2;
@@ -392,11 +486,20 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
   }
 }
 
-// Wavefronts per work-group of the gather-type kernels (one atom per wavefront at a
-// time; kRedBlocks work-groups per chunk).
+// Wavefronts per work-group of the gather-type kernels (one atom per wavefront at a time,
+// more for chunks of fewer than 8 right-hand sides).
 int gather_waves(const Geometry& geo) { return geo.gather_waves == 8 ? 8 : 4; }
 
 }  // namespace
+
+// Work-groups of a gather launch (a multiple of 8 for the XCD ranges): as many as hold every
+// atom at once, up to kRedBlocks; more would only add empty partial sums for the reduction
+// of a_k (96 atoms: 8 instead of 1024).
+int gather_blocks(const Geometry& geo, int BG) {
+  const int aw = BG >= 8 ? 1 : (BG == 1 ? 4 : 2);  // Lanes<BG>::AW
+  const int per = 8 * gather_waves(geo) * aw;
+  return std::min(kRedBlocks, (geo.n + per - 1) / per * 8);
+}
 
 template <typename R>
 void launch_spread(const Geometry& geo, const SysBuffers& b, int B, int BG, int chunk0,
@@ -431,7 +534,7 @@ template <typename R>
 void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, int B, int BG,
                      int chunk0, int nchunks, uint32_t comps, hipStream_t st) {
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
-  dim3 grd(kRedBlocks, nchunks);
+  dim3 grd(gather_blocks(geo, BG), nchunks);
   const double self_coef = -4.0 * geo.tau * geo.tau * geo.tau / (3.0 * sqrt(M_PI));
 #define MBD_GATHER(PP, BB)                                                                  \
   k_gather_epilogue<R, PP, BB><<<grd, 64 * gather_waves(geo), 0, st>>>(                   \
@@ -460,7 +563,7 @@ template <typename R>
 void launch_spme_force(const Geometry& geo, const SysBuffers& b, const void* h, int B, int BG,
                        int chunk0, hipStream_t st, const double* hscale) {
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
-  dim3 grd(kRedBlocks, 1);
+  dim3 grd(gather_blocks(geo, BG), 1);
 #define MBD_SF(PP, BB)                                                                      \
   k_spme_force<R, PP, BB><<<grd, 64 * gather_waves(geo), 0, st>>>(                       \
       geo, b.base, (const R*)b.th, (const R*)b.dth,                                         \
