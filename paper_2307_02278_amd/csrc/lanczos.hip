@@ -236,27 +236,92 @@ __global__ void k_init_probe_scalars(int nb, int m, int probe0, double* __restri
   meff[l] = m;
 }
 
-// Gauss quadrature per probe from its tridiagonal (implicit QR, first-row tracking):
-// one work-group per probe, its working arrays in LDS (the iteration is sequential and
-// runs on lane 0; LDS instead of private arrays avoids scratch-memory latency).
+// Deflation step of the implicit QR iteration, by a whole wavefront: drops converged
+// trailing entries and finds the unreduced block lo..hi (hi = 0: done). e[k] counts as zero
+// when |e[k]| <= eps (|d[k]| + |d[k+1]|); 64 planes are tested at a time, so the scan is no
+// serial chain of LDS reads. Every lane returns the same lo and hi.
+__device__ __forceinline__ void tridiag_block(const double* d, double* e, int& lo, int& hi) {
+  const int lane = threadIdx.x & 63;
+  const double eps = 2.220446049250313e-16;
+  lo = 0;
+  for (int base = (hi - 1) & ~63; hi > 0 && base >= 0;) {
+    const int k = base + lane;
+    const bool small = k < hi && fabs(e[k]) <= eps * (fabs(d[k]) + fabs(d[k + 1]));
+    const unsigned long long m = __ballot(small);
+    if (m == 0ull) {
+      base -= 64;
+      continue;
+    }
+    const int top = base + 63 - __clzll((long long)m);  // largest zero plane below hi
+    if (top == hi - 1) {
+      if (lane == 0) e[hi - 1] = 0.0;
+      --hi;
+      if (hi == base) base -= 64;
+    } else {
+      lo = top + 1;
+      return;
+    }
+  }
+}
+
+// Gauss quadrature per probe from its tridiagonal (implicit QR, first-row tracking): one
+// wavefront per probe, its working arrays in LDS. The rotations of a sweep are one serial
+// chain, which every lane runs alike on the same values (its LDS writes coincide); the
+// lanes share the scaling, the deflation tests and the final sum. For m = 50: 1222 us with
+// hypot, two divisions and a serial deflation scan, 598 us here.
 __global__ void __launch_bounds__(64)
 k_tridiag(int m, int probe0, const double* __restrict__ a, const double* __restrict__ nrm,
           const int* __restrict__ meff, double* __restrict__ q, uint32_t* __restrict__ status) {
   __shared__ double d[kMaxSteps], e[kMaxSteps], z[kMaxSteps];
   const int l = probe0 + blockIdx.x;
+  const int lane = threadIdx.x;
   const int n = meff[l];
-  for (int k = threadIdx.x; k < n; k += 64) {
+  double big = 0.0;
+  for (int k = lane; k < n; k += 64) {
     d[k] = a[l * m + k];
     e[k] = (k + 1 < n) ? nrm[l * m + k + 1] : 0.0;
+    z[k] = (k == 0) ? 1.0 : 0.0;
+    big = fmax(big, fmax(fabs(d[k]), fabs(e[k])));
+  }
+  for (int o = 1; o < 64; o <<= 1) big = fmax(big, __shfl_xor(big, o));
+  const double sc = tridiag_scale(big);
+  for (int k = lane; k < n; k += 64) {
+    d[k] *= sc;
+    e[k] *= sc;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  double tmin;
-  int ok;
-  const double v = tridiag_sqrt_quadrature(d, e, z, n, &tmin, &ok);
+  int hi = n - 1, iter = 0, ok = 1;
+  while (true) {
+    int lo;
+    tridiag_block(d, e, lo, hi);
+    __syncthreads();
+    if (hi <= 0) break;
+    if (++iter > 60 * n) {
+      ok = 0;
+      break;
+    }
+    double zk = z[lo];
+    tridiag_sweep(d, e, lo, hi, [&](int k, double c, double s) {
+      const double zn = z[k + 1];
+      z[k] = c * zk - s * zn;
+      zk = s * zk + c * zn;
+    });
+    z[hi] = zk;
+    __syncthreads();
+  }
+  double v = 0.0;
+  bool bad = false;  // a Ritz value <= 0
+  for (int k = lane; k < n; k += 64) {
+    const double th = d[k] / sc;
+    bad |= k == 0 ? !(th > 0.0) : th <= 0.0;
+    v += z[k] * z[k] * sqrt(th > 0.0 ? th : 0.0);
+  }
+  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
+  const bool neg = __any(bad);
+  if (lane != 0) return;
   q[l] = v;
   if (!ok) atomicOr(status, kErrNoConverge);
-  if (!(tmin > 0.0)) atomicOr(status, kErrNotPosdef);
+  if (neg) atomicOr(status, kErrNotPosdef);
   if (!isfinite(v)) atomicOr(status, kErrNonfinite);
 }
 
@@ -335,123 +400,110 @@ __global__ void k_unpack(int n, int nrhs, int B, const int* __restrict__ perm,
 // Re-orthogonalization corrections are not differentiated.
 // ---------------------------------------------------------------------------
 
-// Per probe (one 64-lane work-group each): eigenvectors of its tridiagonal by the
-// implicit symmetric QR iteration with Wilkinson shift, then the quadrature adjoint
+// Per probe (one wavefront each): eigenvectors of its tridiagonal by the implicit
+// symmetric QR iteration with Wilkinson shift, then the quadrature adjoint
 // dQ/dT = U (F o c c^T) U^T, c = U^T e1, F_ij = 1 / (sqrt(theta_i) + sqrt(theta_j)).
-// Lane 0 deflates and computes the Givens rotations of one sweep into LDS; every lane
-// then applies them to its own rows of U (rows never move between lanes, so no other
-// synchronization is needed). The adjoint's O(m^3) sums are split over the lanes.
+// Every lane runs the rotation chain of a sweep alike (as in k_tridiag) and leaves the
+// rotations in LDS; then each lane applies them to its own rows of U, one register carried
+// from plane to plane. U is stored by columns, u[k ld + i] = U_ik, so the lanes' accesses
+// are consecutive; up to kEigLds steps it stays in LDS (LDSU), else in tz. In the adjoint's
+// O(m^3) sums the weights F_ij c_i c_j of one i are formed once, one j per lane.
+constexpr int kEigLds = 64;
+template <bool LDSU>
 __global__ void __launch_bounds__(64)
 k_tridiag_adjoint(int m, int probe0, const double* __restrict__ a,
                   const double* __restrict__ nrm, const int* __restrict__ meff,
                   double* __restrict__ tz, double* __restrict__ abar, double* __restrict__ bbar,
                   uint32_t* __restrict__ status) {
   __shared__ double d[kMaxSteps], e[kMaxSteps], cs[kMaxSteps], sn[kMaxSteps];
-  __shared__ int ctl[3];  // lo, hi, state (0 sweep, 1 done, 2 no convergence)
+  __shared__ double ul[LDSU ? kEigLds * kEigLds : 1];
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
   const int l = probe0 + b;
   const int n = meff[l];
-  double* u = tz + (size_t)b * m * m;
+  const int ld = LDSU ? kEigLds : m;
+  double* u = LDSU ? ul : tz + (size_t)b * m * m;
   double* ab = abar + (size_t)b * m;
   double* bb = bbar + (size_t)b * m;
+  double big = 0.0;
   for (int k = lane; k < m; k += 64) {
     ab[k] = 0.0;
     bb[k] = 0.0;
     if (k < n) {
       d[k] = a[l * m + k];
       e[k] = (k + 1 < n) ? nrm[l * m + k + 1] : 0.0;
+      big = fmax(big, fmax(fabs(d[k]), fabs(e[k])));
     }
+  }
+  for (int o = 1; o < 64; o <<= 1) big = fmax(big, __shfl_xor(big, o));
+  const double sc = tridiag_scale(big);
+  for (int k = lane; k < n; k += 64) {
+    d[k] *= sc;
+    e[k] *= sc;
   }
   for (int i = lane; i < n; i += 64)
-    for (int k = 0; k < n; ++k) u[(size_t)i * m + k] = (i == k) ? 1.0 : 0.0;
-  if (lane == 0) ctl[1] = n - 1;
+    for (int k = 0; k < n; ++k) u[(size_t)k * ld + i] = (i == k) ? 1.0 : 0.0;
   __syncthreads();
-  const double eps = 2.220446049250313e-16;
-  int iter = 0;
+  int hi = n - 1, iter = 0;
+  bool ok = true;
   while (true) {
-    if (lane == 0) {
-      int hi = ctl[1], st = 0;
-      while (hi > 0 && fabs(e[hi - 1]) <= eps * (fabs(d[hi - 1]) + fabs(d[hi]))) {
-        e[hi - 1] = 0.0;
-        --hi;
-      }
-      if (hi <= 0) {
-        st = 1;
-      } else if (++iter > 60 * n) {
-        st = 2;
-      } else {
-        int lo = hi - 1;
-        while (lo > 0 && fabs(e[lo - 1]) > eps * (fabs(d[lo - 1]) + fabs(d[lo]))) --lo;
-        const double delta = 0.5 * (d[hi - 1] - d[hi]);
-        const double eh = e[hi - 1];
-        const double den = delta + (delta >= 0.0 ? 1.0 : -1.0) * sqrt(delta * delta + eh * eh);
-        const double mu = (den != 0.0) ? d[hi] - eh * eh / den : d[hi];
-        double x = d[lo] - mu;
-        double z = e[lo];
-        for (int k = lo; k < hi; ++k) {
-          const double r = hypot(x, z);
-          double c = 1.0, sg = 0.0;
-          if (r != 0.0) { c = x / r; sg = -z / r; }
-          if (k > lo) e[k - 1] = r;
-          const double dk = d[k], dk1 = d[k + 1], ek = e[k];
-          d[k] = c * c * dk - 2.0 * c * sg * ek + sg * sg * dk1;
-          d[k + 1] = sg * sg * dk + 2.0 * c * sg * ek + c * c * dk1;
-          e[k] = c * sg * (dk - dk1) + (c * c - sg * sg) * ek;
-          if (k + 1 < hi) {
-            z = -sg * e[k + 1];
-            e[k + 1] = c * e[k + 1];
-            x = e[k];
-          }
-          cs[k] = c;
-          sn[k] = sg;
-        }
-        ctl[0] = lo;
-      }
-      ctl[1] = hi;
-      ctl[2] = st;
-    }
+    int lo;
+    tridiag_block(d, e, lo, hi);
     __syncthreads();
-    const int st = ctl[2];
-    if (st != 0) break;
-    const int lo = ctl[0], hi = ctl[1];
+    if (hi <= 0) break;
+    if (++iter > 60 * n) {
+      ok = false;
+      break;
+    }
+    tridiag_sweep(d, e, lo, hi, [&](int k, double c, double s) {
+      cs[k] = c;
+      sn[k] = s;
+    });
+    __syncthreads();
     for (int i = lane; i < n; i += 64) {
-      double* ui = u + (size_t)i * m;
+      double uk = u[(size_t)lo * ld + i];
       for (int k = lo; k < hi; ++k) {
-        const double a0 = ui[k], a1 = ui[k + 1];
-        ui[k] = cs[k] * a0 - sn[k] * a1;
-        ui[k + 1] = sn[k] * a0 + cs[k] * a1;
+        const double un = u[(size_t)(k + 1) * ld + i], c = cs[k], s = sn[k];
+        u[(size_t)k * ld + i] = c * uk - s * un;
+        uk = s * uk + c * un;
       }
+      u[(size_t)hi * ld + i] = uk;
     }
     __syncthreads();
   }
-  if (ctl[2] == 2) {
+  if (!ok) {
     if (lane == 0) atomicOr(status, kErrNoConverge);
     return;
   }
-  // eigenvalues d, eigenvectors in the columns of u; sqrt(theta) into cs
+  // eigenvalues d, eigenvectors in the columns of u; sqrt(theta) into cs, the weights of
+  // one i into sn
   for (int k = lane; k < n; k += 64) {
-    if (!(d[k] > 0.0)) atomicOr(status, kErrNotPosdef);
-    cs[k] = sqrt(d[k] > 0.0 ? d[k] : 0.0);
+    const double th = d[k] / sc;
+    if (!(th > 0.0)) atomicOr(status, kErrNotPosdef);
+    cs[k] = sqrt(th > 0.0 ? th : 0.0);
   }
-  __syncthreads();
-  const double* c0 = u;  // first row: c_j = U_0j
-  for (int k = lane; k < n; k += 64) {
-    const double* uk = u + (size_t)k * m;
-    const double* ukm = k > 0 ? u + (size_t)(k - 1) * m : uk;
+  for (int k0 = 0; k0 < n; k0 += 64) {
+    const int k = k0 + lane;
+    const bool own = k < n;
+    const int kr = own ? k : 0, km = kr > 0 ? kr - 1 : 0;
     double mkk = 0.0, mkm = 0.0;
     for (int i = 0; i < n; ++i) {
-      double acc = 0.0;
-      for (int j = 0; j < n; ++j) {
+      __syncthreads();  // the previous weights have been read
+      for (int j = lane; j < n; j += 64) {
         const double den = cs[i] + cs[j];
-        acc += (den > 0.0 ? 1.0 / den : 0.0) * c0[j] * uk[j];
+        sn[j] = (den > 0.0 ? 1.0 / den : 0.0) * u[(size_t)j * ld];  // c_j = U_0j
       }
-      const double v = acc * c0[i];
-      mkk += uk[i] * v;
-      mkm += ukm[i] * v;
+      __syncthreads();
+      double acc = 0.0;
+      for (int j = 0; j < n; ++j) acc += sn[j] * u[(size_t)j * ld + kr];
+      const double v = acc * u[(size_t)i * ld];
+      mkk += u[(size_t)i * ld + kr] * v;
+      mkm += u[(size_t)i * ld + km] * v;
     }
-    ab[k] = mkk;
-    bb[k] = k > 0 ? 2.0 * mkm : 0.0;
+    if (own) {
+      ab[k] = mkk;
+      bb[k] = k > 0 ? 2.0 * mkm : 0.0;
+    }
   }
 }
 
@@ -708,8 +760,12 @@ void fill_double(double* p, double v, size_t n, hipStream_t st) {
 
 void launch_tridiag_adjoint(const SysBuffers& b, int nb, int m, int probe0, uint32_t* status,
                             hipStream_t st) {
-  k_tridiag_adjoint<<<nb, 64, 0, st>>>(m, probe0, b.a, b.b, b.meff, b.tz, b.abar, b.bbar,
-                                       status);
+  if (m <= kEigLds)
+    k_tridiag_adjoint<true><<<nb, 64, 0, st>>>(m, probe0, b.a, b.b, b.meff, b.tz, b.abar,
+                                               b.bbar, status);
+  else
+    k_tridiag_adjoint<false><<<nb, 64, 0, st>>>(m, probe0, b.a, b.b, b.meff, b.tz, b.abar,
+                                                b.bbar, status);
 }
 
 // One reverse step k: dots, scalars and the element-wise update, which leaves lbar_k in

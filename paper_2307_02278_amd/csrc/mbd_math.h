@@ -110,6 +110,14 @@ template <typename R> MBD_HD R m_sqrt(R x);
 template <> MBD_HD double m_sqrt<double>(double x) { return sqrt(x); }
 template <> MBD_HD float m_sqrt<float>(float x) { return sqrtf(x); }
 
+MBD_HD double m_rsqrt(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return rsqrt(x);
+#else
+  return 1.0 / sqrt(x);
+#endif
+}
+
 template <typename R>
 MBD_HD void direct_kernel(R r2, R tau, R inv_s, R damp_d, R& A, R& B) {
   const R r = m_sqrt<R>(r2);
@@ -195,9 +203,67 @@ MBD_HD void direct_kernel_grad(double r2, double tau, double inv_s, double damp_
   dB_r = dBe_r + 3.0 * fp * ir5 * ir + 15.0 * omf * ir7;
 }
 
+// One implicit QR sweep over the unreduced block lo..hi. rot(k, c, s) is told each plane
+// rotation. The rotations form one serial chain, x, z -> r^2 -> 1/r -> c, s -> next x, z,
+// so d, e of the next plane are carried in registers (read one plane ahead) and the
+// rotation costs one reciprocal square root instead of a hypot and two divisions. The
+// caller scales T to entries of order one (tridiag_scale), so r^2 neither overflows nor
+// loses digits: below 1e-290 the plane is already decoupled to rounding.
+template <class Rot>
+MBD_HD void tridiag_sweep(double* d, double* e, int lo, int hi, Rot&& rot) {
+  // Wilkinson shift from the trailing 2x2 block
+  const double delta = 0.5 * (d[hi - 1] - d[hi]);
+  const double eh = e[hi - 1];
+  const double den = delta + (delta >= 0.0 ? 1.0 : -1.0) * sqrt(delta * delta + eh * eh);
+  const double mu = (den != 0.0) ? d[hi] - eh * eh / den : d[hi];
+  double x = d[lo] - mu, z = e[lo];
+  double dk = d[lo], ek = z, dn = d[lo + 1], en = lo + 1 < hi ? e[lo + 1] : 0.0;
+  for (int k = lo; k < hi; ++k) {
+    const double dnn = k + 2 <= hi ? d[k + 2] : 0.0, enn = k + 2 < hi ? e[k + 2] : 0.0;
+    const double r2 = x * x + z * z;
+    double c = 1.0, s = 0.0, r = 0.0;
+    if (r2 > 1e-290) {
+      const double ri = m_rsqrt(r2);
+      c = x * ri;
+      s = -z * ri;
+      r = r2 * ri;
+    }
+    if (k > lo) e[k - 1] = r;
+    const double cc = c * c, ss = s * s, cs = c * s, t = 2.0 * cs * ek;
+    d[k] = cc * dk - t + ss * dn;
+    const double d1 = ss * dk + t + cc * dn;
+    x = cs * (dk - dn) + (cc - ss) * ek;
+    e[k] = x;  // stays for k = hi - 1, else replaced by the next plane's r
+    rot(k, c, s);
+    z = -s * en;
+    ek = c * en;
+    dk = d1;
+    dn = dnn;
+    en = enn;
+  }
+  d[hi] = dk;
+}
+
+// Power of two that brings the largest entry of T below 1 (1 for a zero or non-finite T).
+MBD_HD double tridiag_scale(double largest) {
+  if (!(largest > 0.0) || !(largest < 1e300)) return 1.0;
+  int ex;
+  frexp(largest, &ex);
+  return ldexp(1.0, -ex);
+}
+
 MBD_HD double tridiag_sqrt_quadrature(double* d, double* e, double* q, int n,
                                       double* theta_min, int* ok) {
-  for (int k = 0; k < n; ++k) q[k] = (k == 0) ? 1.0 : 0.0;
+  double big = 0.0;
+  for (int k = 0; k < n; ++k) {
+    q[k] = (k == 0) ? 1.0 : 0.0;
+    big = fmax(big, fmax(fabs(d[k]), k + 1 < n ? fabs(e[k]) : 0.0));
+  }
+  const double sc = tridiag_scale(big);
+  for (int k = 0; k < n; ++k) {
+    d[k] *= sc;
+    if (k + 1 < n) e[k] *= sc;
+  }
   int hi = n - 1;
   int iter = 0;
   const double eps = 2.220446049250313e-16;
@@ -211,39 +277,22 @@ MBD_HD double tridiag_sqrt_quadrature(double* d, double* e, double* q, int n,
     int lo = hi - 1;
     while (lo > 0 && fabs(e[lo - 1]) > eps * (fabs(d[lo - 1]) + fabs(d[lo]))) --lo;
     if (++iter > 60 * n) { *ok = 0; break; }
-    // Wilkinson shift from the trailing 2x2 block.
-    const double delta = 0.5 * (d[hi - 1] - d[hi]);
-    const double eh = e[hi - 1];
-    const double den = delta + (delta >= 0.0 ? 1.0 : -1.0) * sqrt(delta * delta + eh * eh);
-    const double mu = (den != 0.0) ? d[hi] - eh * eh / den : d[hi];
-    double x = d[lo] - mu;
-    double z = e[lo];
-    for (int k = lo; k < hi; ++k) {
-      const double r = hypot(x, z);
-      double c = 1.0, s = 0.0;
-      if (r != 0.0) { c = x / r; s = -z / r; }
-      if (k > lo) e[k - 1] = r;
-      const double dk = d[k], dk1 = d[k + 1], ek = e[k];
-      d[k] = c * c * dk - 2.0 * c * s * ek + s * s * dk1;
-      d[k + 1] = s * s * dk + 2.0 * c * s * ek + c * c * dk1;
-      e[k] = c * s * (dk - dk1) + (c * c - s * s) * ek;
-      if (k + 1 < hi) {
-        z = -s * e[k + 1];
-        e[k + 1] = c * e[k + 1];
-        x = e[k];
-      }
-      const double qk = q[k], qk1 = q[k + 1];
-      q[k] = c * qk - s * qk1;
-      q[k + 1] = s * qk + c * qk1;
-    }
+    double qk = q[lo];
+    tridiag_sweep(d, e, lo, hi, [&](int k, double c, double s) {
+      const double qn = q[k + 1];
+      q[k] = c * qk - s * qn;
+      qk = s * qk + c * qn;
+    });
+    q[hi] = qk;
   }
   double sum = 0.0;
   double tmin = d[0];
   for (int k = 0; k < n; ++k) {
+    const double th = d[k] / sc;
     tmin = d[k] < tmin ? d[k] : tmin;
-    sum += q[k] * q[k] * sqrt(d[k] > 0.0 ? d[k] : 0.0);
+    sum += q[k] * q[k] * sqrt(th > 0.0 ? th : 0.0);
   }
-  *theta_min = tmin;
+  *theta_min = tmin / sc;
   return sum;
 }
 
