@@ -536,21 +536,26 @@ void run_energy(Plan& plan, System& S, int sys_index, double* energy, double* sd
       launch_probes(S.geo, S.buf, B, nb, l0, plan.prm.seed, sys_index, fl, st);
     });
     const size_t gsz = (size_t)S.geo.K[2] * S.geo.K[1] * (S.geo.K[0] + 2) * B;
+    const int ng = gather_blocks(S.geo, S.BG);
+    const bool fused = update_finishes(S.geo, B, ng);
     for (int k = 0; k < m; ++k) {
       void* slot = (forces && S.buf.phi) ? (void*)((R*)S.buf.phi + (size_t)k * gsz) : nullptr;
       matvec_block<R>(plan, S, S.buf.W + (size_t)k * vs, MBD_C_ALL, slot);
       staged(plan, MBD_STAGE_LANCZOS, [&] {
-        launch_finish_a(S.buf, B, nb, k, m, l0, gather_blocks(S.geo, S.BG), plan.status, st);
+        // the scalars of the step in their own launch where the update does not form them
+        // from the partial sums itself; nrm_{k+1} is left to the next step
+        if (k + 1 == m || !fused)
+          launch_finish_step(S.geo, S.buf, B, nb, k, m, l0, ng, plan.status, st);
         if (k + 1 < m) {
           const int ro = plan.prm.reorth;
-          launch_update(S.geo, S.buf, B, nb, k, m, l0, fl, ro == MBD_REORTH_NONE, st);
+          launch_update(S.geo, S.buf, B, nb, k, m, l0, fl, ro == MBD_REORTH_NONE, fused ? ng : 0,
+                        plan.status, st);
           if (ro == MBD_REORTH_LOCAL) {
             launch_reorth(S.geo, S.buf, B, nb, k, m, l0, std::max(0, k - 1), fl, st);
           } else if (ro == MBD_REORTH_FULL) {
             launch_reorth(S.geo, S.buf, B, nb, k, m, l0, 0, fl, st);
             launch_reorth(S.geo, S.buf, B, nb, k, m, l0, 0, fl, st);
           }
-          launch_finish_norm(S.buf, B, nb, k, m, l0, plan.status, st);
         }
       });
     }

@@ -16,7 +16,8 @@ constexpr int kMaxOrder = 8;
 constexpr int kRedBlocks = 1024;   // blocks (and partial sums) of the row reductions
 constexpr int kSpreadTile = 4;     // grid points per spread-tile edge (one wavefront per tile)
 constexpr int kMaxSteps = 512;
-constexpr int kPartSlots = 8;      // partial-sum slots per reduction block
+constexpr int kPartSlots = 8;      // partial-sum slots per reduction block: 0 a_k, 1 and 2
+                                   // ||w_k||^2 of even and odd k, 3 re-orthogonalization
 // Direct-space tensor list: targets per group, stored components per (source,
 // target) pair (xx, yy, zz, xy, xz, yz) and values per listed source.
 constexpr int kGroup = 16;
@@ -297,13 +298,16 @@ void launch_probes(const Geometry& g, const SysBuffers& b, int B, int nb, int pr
                    uint64_t seed, int system, bool use_float, hipStream_t st);
 void launch_init_scalars(const SysBuffers& b, int nb, int m, int probe0, hipStream_t st);
 void launch_update(const Geometry& g, const SysBuffers& b, int B, int nb, int k, int m,
-                   int probe0, bool use_float, bool write_d, hipStream_t st);
+                   int probe0, bool use_float, bool write_d, int ng, uint32_t* status,
+                   hipStream_t st);
 void launch_reorth(const Geometry& g, const SysBuffers& b, int B, int nb, int k, int m,
                    int probe0, int j0, bool use_float, hipStream_t st);
-void launch_finish_a(const SysBuffers& b, int B, int nb, int k, int m, int probe0, int ng,
-                     uint32_t* status, hipStream_t st);
-void launch_finish_norm(const SysBuffers& b, int B, int nb, int k, int m, int probe0,
-                        uint32_t* status, hipStream_t st);
+// Scalars of step k from the partial sums left by the gather (ng work-groups) and by the
+// update or re-orthogonalization before it: nrm_k (k > 0; breakdown ends the probe), a_k.
+void launch_finish_step(const Geometry& g, const SysBuffers& b, int B, int nb, int k, int m,
+                        int probe0, int ng, uint32_t* status, hipStream_t st);
+// True where launch_update forms the scalars of its step itself (few partial sums).
+bool update_finishes(const Geometry& g, int B, int ng);
 // Work-groups (and partial sums of a_k) of a gather over chunks of BG right-hand sides.
 int gather_blocks(const Geometry& g, int BG);
 void launch_tridiag(const SysBuffers& b, int nb, int m, int probe0, uint32_t* status,

@@ -9,6 +9,8 @@
 // with b_{k+1} = nrm_{k+1}; the generalized dipoles of the next step are
 // d = g * w_{k+1} (stored in the SPME precision). Every reduction over atoms is
 // done in a fixed order (per-block partial sums, then one block per RHS).
+#include <algorithm>
+
 #include "common.h"
 #include "mbd_math.h"
 
@@ -60,29 +62,99 @@ k_probes(int n, int B, int nb, int probe0, uint64_t zs, const int* __restrict__ 
   }
 }
 
+// Partial-sum slot of ||w_k||^2: two alternate, so that an update can still read the sums
+// of w_k while other work-groups write those of w_{k+1}.
+__host__ __device__ inline int norm_slot(int k) { return 1 + (k & 1); }
+
+// Scalars of step k of probe l from the sums dot = w_k . l~_k and sq = ||w_k||^2. A probe
+// ends when ||w_k|| <= 1e-12 of the scale of the step before: meff, the steps done, becomes
+// k. (Another work-group of the same launch may already have stored that; a probe that
+// ended in an earlier step has meff < k.)
+struct StepScalars {
+  double nk, ak;
+  bool was, live;  // alive before the norm of this step was looked at, and after
+};
+__device__ __forceinline__ StepScalars step_scalars(int l, int k, int m, double dot, double sq,
+                                                    const double* nrm, const double* a, int me) {
+  StepScalars t;
+  t.was = me >= k && (k > 0 || me > 0);
+  t.nk = k > 0 ? sqrt(sq) : nrm[l * m];
+  t.live = t.was;
+  if (k > 0) {
+    const double scale = fmax(fabs(a[l * m + k - 1]), nrm[l * m + k - 1]);
+    if (!(t.nk > 1e-12 * scale)) t.live = false;
+  }
+  t.ak = dot / (t.nk * t.nk);
+  return t;
+}
+__device__ __forceinline__ void store_scalars(const StepScalars& t, int l, int k, int m,
+                                              double* nrm, double* a, int* meff,
+                                              uint32_t* status) {
+  if (!t.was) return;
+  if (k > 0) nrm[l * m + k] = t.nk;
+  if (!isfinite(t.nk) || (t.live && !isfinite(t.ak))) atomicOr(status, kErrNonfinite);
+  if (t.live) a[l * m + k] = t.ak;
+  else meff[l] = k;
+}
+
+// w_{k+1} from l~_k, w_k, w_{k-1}. With ng > 0 the scalars of step k are formed here, by
+// every work-group alike from the ng + nu partial sums (work-group 0 stores them): for
+// small systems that costs less than the separate launch it saves. With ng = 0 they were
+// stored before.
 template <int RB>
 __global__ void __launch_bounds__(256)
 k_update(int n, int B, int nb, int k, int m, int probe0, const double* __restrict__ lt,
-         const double* __restrict__ wk, const double* __restrict__ wkm1,
-         const double* __restrict__ a, const double* __restrict__ nrm,
-         const int* __restrict__ meff, const double* __restrict__ g, double* __restrict__ wn,
+         const double* __restrict__ wk, const double* __restrict__ wkm1, double* a, double* nrm,
+         int* meff, const double* __restrict__ g, double* __restrict__ wn,
          double* __restrict__ dtmp, float* __restrict__ df, int use_float, int write_d,
-         double* __restrict__ part) {
+         double* part, int ng, int nu, uint32_t* __restrict__ status) {
   constexpr int ROWS = 256 / RB;
-  __shared__ double red[256];
+  __shared__ double red[256], red2[256];
   const int lane = threadIdx.x % RB;
   const int b = blockIdx.y * RB + lane;
   const int row0 = blockIdx.x * ROWS + threadIdx.x / RB;
+  double dot = 0.0, sq = 0.0;
+  if (ng > 0) {
+    if (b < B) {
+      for (int i = threadIdx.x / RB; i < ng; i += ROWS) dot += part[(size_t)i * kPartSlots * B + b];
+      if (k > 0)
+        for (int i = threadIdx.x / RB; i < nu; i += ROWS)
+          sq += part[((size_t)i * kPartSlots + norm_slot(k)) * B + b];
+    }
+    red[threadIdx.x] = dot;
+    red2[threadIdx.x] = sq;
+    __syncthreads();
+    for (int h = ROWS / 2; h > 0; h >>= 1) {
+      if (threadIdx.x / RB < h) {
+        red[threadIdx.x] += red[threadIdx.x + h * RB];
+        red2[threadIdx.x] += red2[threadIdx.x + h * RB];
+      }
+      __syncthreads();
+    }
+    dot = red[lane];
+    sq = red2[lane];
+    __syncthreads();
+  }
   double ss = 0.0;
   if (b < B) {
     bool live = false;
     double c_l = 0.0, c_k = 0.0, c_km1 = 0.0;
     if (b < nb) {
       const int l = probe0 + b;
-      live = meff[l] > k;  // w_{k+1} is needed only while the probe has not broken down
-      const double nk = nrm[l * m + k];
+      double nk, ak;
+      if (ng > 0) {
+        const StepScalars t = step_scalars(l, k, m, dot, sq, nrm, a, meff[l]);
+        nk = t.nk;
+        ak = t.ak;
+        live = t.live;
+        if (blockIdx.x == 0 && threadIdx.x < RB) store_scalars(t, l, k, m, nrm, a, meff, status);
+      } else {
+        nk = nrm[l * m + k];
+        ak = a[l * m + k];
+        live = meff[l] > k;  // w_{k+1} is needed only while the probe has not broken down
+      }
       c_l = 1.0 / nk;
-      c_k = a[l * m + k] / nk;
+      c_k = ak / nk;
       c_km1 = (k > 0) ? nk / nrm[l * m + k - 1] : 0.0;
     }
     for (int row = row0; row < 3 * n; row += gridDim.x * ROWS) {
@@ -103,7 +175,8 @@ k_update(int n, int B, int nb, int k, int m, int probe0, const double* __restric
   red[threadIdx.x] = ss;
   __syncthreads();
   block_reduce_rows(red, RB, ROWS);
-  if (threadIdx.x < RB && b < B) part[((size_t)blockIdx.x * kPartSlots + 1) * B + b] = red[threadIdx.x];
+  if (threadIdx.x < RB && b < B)
+    part[((size_t)blockIdx.x * kPartSlots + norm_slot(k + 1)) * B + b] = red[threadIdx.x];
 }
 
 // Dot products of w with earlier Krylov vectors for re-orthogonalization:
@@ -155,7 +228,7 @@ k_orth_apply(int n, int B, int nb, int m, int probe0, const double* __restrict__
              size_t vstride, int j0, int j1, const double* __restrict__ dots,
              const double* __restrict__ nrm, const int* __restrict__ meff, int k,
              const double* __restrict__ g, double* __restrict__ w, double* __restrict__ dtmp,
-             float* __restrict__ df, int use_float, double* __restrict__ part) {
+             float* __restrict__ df, int use_float, double* __restrict__ part, int slot) {
   constexpr int ROWS = 256 / RB;
   __shared__ double red[256];
   const int lane = threadIdx.x % RB;
@@ -190,37 +263,37 @@ k_orth_apply(int n, int B, int nb, int m, int probe0, const double* __restrict__
   red[threadIdx.x] = ss;
   __syncthreads();
   block_reduce_rows(red, RB, ROWS);
-  if (threadIdx.x < RB && b < B) part[((size_t)blockIdx.x * kPartSlots + 1) * B + b] = red[threadIdx.x];
+  if (threadIdx.x < RB && b < B)
+    part[((size_t)blockIdx.x * kPartSlots + slot) * B + b] = red[threadIdx.x];
 }
 
-// a_k from the epilogue partials (slot 0).
-__global__ void k_finish_a(int B, int nb, int k, int m, int probe0, const double* __restrict__ sums,
-                           const double* __restrict__ nrm, double* __restrict__ a,
-                           const int* __restrict__ meff, uint32_t* __restrict__ status) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
+// Scalars of step k, one work-group per right-hand side: the sums over the ng partials of
+// a_k and the nu partials of ||w_k||^2 in a fixed order, then step_scalars.
+__global__ void __launch_bounds__(256)
+k_finish_step(int B, int nb, int k, int m, int probe0, int ng, int nu,
+              const double* __restrict__ part, double* __restrict__ nrm,
+              double* __restrict__ a, int* __restrict__ meff, uint32_t* __restrict__ status) {
+  __shared__ double red[256], red2[256];
+  const int b = blockIdx.x;
+  double s = 0.0, s2 = 0.0;
+  for (int i = threadIdx.x; i < ng; i += 256) s += part[(size_t)i * kPartSlots * B + b];
+  if (k > 0)
+    for (int i = threadIdx.x; i < nu; i += 256)
+      s2 += part[((size_t)i * kPartSlots + norm_slot(k)) * B + b];
+  red[threadIdx.x] = s;
+  red2[threadIdx.x] = s2;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (threadIdx.x < h) {
+      red[threadIdx.x] += red[threadIdx.x + h];
+      red2[threadIdx.x] += red2[threadIdx.x + h];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x != 0 || b >= nb) return;
   const int l = probe0 + b;
-  if (meff[l] <= k) return;
-  const double nk = nrm[l * m + k];
-  const double v = sums[b] / (nk * nk);
-  a[l * m + k] = v;
-  if (!isfinite(v)) atomicOr(status, kErrNonfinite);
-}
-
-// nrm_{k+1} from the update partials (slot 1); breakdown truncates the tridiagonal.
-__global__ void k_finish_norm(int B, int nb, int k, int m, int probe0,
-                              const double* __restrict__ sums, double* __restrict__ nrm,
-                              const double* __restrict__ a, int* __restrict__ meff,
-                              uint32_t* __restrict__ status) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb) return;
-  const int l = probe0 + b;
-  if (meff[l] <= k) return;
-  const double v = sqrt(sums[b]);
-  nrm[l * m + k + 1] = v;
-  const double scale = fmax(fabs(a[l * m + k]), nrm[l * m + k]);
-  if (!isfinite(v)) atomicOr(status, kErrNonfinite);
-  if (!(v > 1e-12 * scale)) meff[l] = k + 1;
+  store_scalars(step_scalars(l, k, m, red[0], red2[0], nrm, a, meff[l]), l, k, m, nrm, a, meff,
+                status);
 }
 
 __global__ void k_init_probe_scalars(int nb, int m, int probe0, double* __restrict__ nrm,
@@ -663,6 +736,13 @@ __global__ void k_forces_finish(int n, int R, int parts, const int* __restrict__
 
 inline int rb_for(int B) { return B >= 64 ? 64 : B; }
 
+// Work-groups (and partial sums) of the row kernels along the rows: four rows per thread,
+// up to kRedBlocks (96 atoms, B = 1: one instead of 1024).
+inline int row_blocks(int n, int B) {
+  const int rows = 4 * (256 / rb_for(B));
+  return std::max(1, std::min(kRedBlocks, (3 * n + rows - 1) / rows));
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -683,7 +763,7 @@ void launch_probes(const Geometry& geo, const SysBuffers& b, int B, int nb, int 
                    uint64_t seed, int system, bool use_float, hipStream_t st) {
   const uint64_t zs = splitmix_at(seed, (uint64_t)system);
   const int rb = rb_for(B);
-  dim3 grd(kRedBlocks, (B + rb - 1) / rb);
+  dim3 grd(row_blocks(geo.n, B), (B + rb - 1) / rb);
   MBD_RB_SWITCH(rb, (k_probes<RB><<<grd, 256, 0, st>>>(geo.n, B, nb, probe0, zs, b.perm, b.g,
                                                        b.W, (double*)b.dv, (float*)b.dv,
                                                        use_float ? 1 : 0)));
@@ -694,17 +774,26 @@ void launch_init_scalars(const SysBuffers& b, int nb, int m, int probe0, hipStre
 }
 
 void launch_update(const Geometry& geo, const SysBuffers& b, int B, int nb, int k, int m,
-                   int probe0, bool use_float, bool write_d, hipStream_t st) {
+                   int probe0, bool use_float, bool write_d, int ng, uint32_t* status,
+                   hipStream_t st) {
   const size_t vs = (size_t)geo.n * 3 * B;
   const int rb = rb_for(B);
-  dim3 grd(kRedBlocks, (B + rb - 1) / rb);
+  dim3 grd(row_blocks(geo.n, B), (B + rb - 1) / rb);
   const double* wk = b.W + (size_t)k * vs;
   const double* wkm1 = k > 0 ? b.W + (size_t)(k - 1) * vs : b.W;
   double* wn = b.W + (size_t)(k + 1) * vs;
   MBD_RB_SWITCH(rb, (k_update<RB><<<grd, 256, 0, st>>>(
                          geo.n, B, nb, k, m, probe0, b.Lt, wk, wkm1, b.a, b.b, b.meff, b.g, wn,
                          (double*)b.dv, (float*)b.dv, use_float ? 1 : 0, write_d ? 1 : 0,
-                         b.part)));
+                         b.part, ng, (int)grd.x, status)));
+}
+
+// Every work-group of k_update then reads the ng + nu partials of its right-hand sides: up
+// to 8 MB of L2 reads over the launch that takes less time than the launch it saves (648
+// atoms, B = 32: 3.6 MB; 24k atoms, B = 128: 2 GB).
+bool update_finishes(const Geometry& geo, int B, int ng) {
+  const size_t nu = (size_t)row_blocks(geo.n, B);
+  return (ng + nu) * sizeof(double) * B * nu <= ((size_t)8 << 20);
 }
 
 // Re-orthogonalize w_{k+1} against w_j for j in [j0, k] (classical Gram-Schmidt,
@@ -713,33 +802,26 @@ void launch_reorth(const Geometry& geo, const SysBuffers& b, int B, int nb, int 
                    int probe0, int j0, bool use_float, hipStream_t st) {
   const size_t vs = (size_t)geo.n * 3 * B;
   const int rb = rb_for(B);
-  dim3 grd(kRedBlocks, (B + rb - 1) / rb);
+  dim3 grd(row_blocks(geo.n, B), (B + rb - 1) / rb);
   double* w = b.W + (size_t)(k + 1) * vs;
   for (int c0 = j0; c0 <= k; c0 += 64) {
     const int c1 = (k + 1 < c0 + 64) ? k + 1 : c0 + 64;
     for (int j = c0; j < c1; ++j) {
       MBD_RB_SWITCH(rb, (k_dot<RB><<<grd, 256, 0, st>>>(geo.n, B, w, b.W + (size_t)j * vs,
-                                                        b.part, 2)));
-      k_sum_slot<<<B, 256, 0, st>>>(B, 2, kRedBlocks, b.part, b.coef + (size_t)(j - c0) * B);
+                                                        b.part, 3)));
+      k_sum_slot<<<B, 256, 0, st>>>(B, 3, (int)grd.x, b.part, b.coef + (size_t)(j - c0) * B);
     }
     MBD_RB_SWITCH(rb, (k_orth_apply<RB><<<grd, 256, 0, st>>>(
                            geo.n, B, nb, m, probe0, b.W, vs, c0, c1, b.coef, b.b, b.meff, k,
-                           b.g, w, (double*)b.dv, (float*)b.dv, use_float ? 1 : 0, b.part)));
+                           b.g, w, (double*)b.dv, (float*)b.dv, use_float ? 1 : 0, b.part,
+                           norm_slot(k + 1))));
   }
 }
 
-void launch_finish_a(const SysBuffers& b, int B, int nb, int k, int m, int probe0, int ng,
-                     uint32_t* status, hipStream_t st) {
-  k_sum_slot<<<B, 256, 0, st>>>(B, 0, ng, b.part, b.coef);
-  k_finish_a<<<(nb + 63) / 64, 64, 0, st>>>(B, nb, k, m, probe0, b.coef, b.b, b.a, b.meff,
-                                            status);
-}
-
-void launch_finish_norm(const SysBuffers& b, int B, int nb, int k, int m, int probe0,
-                        uint32_t* status, hipStream_t st) {
-  k_sum_slot<<<B, 256, 0, st>>>(B, 1, kRedBlocks, b.part, b.coef);
-  k_finish_norm<<<(nb + 63) / 64, 64, 0, st>>>(B, nb, k, m, probe0, b.coef, b.b, b.a, b.meff,
-                                               status);
+void launch_finish_step(const Geometry& geo, const SysBuffers& b, int B, int nb, int k, int m,
+                        int probe0, int ng, uint32_t* status, hipStream_t st) {
+  k_finish_step<<<nb, 256, 0, st>>>(B, nb, k, m, probe0, ng, row_blocks(geo.n, B), b.part, b.b,
+                                    b.a, b.meff, status);
 }
 
 void launch_tridiag(const SysBuffers& b, int nb, int m, int probe0, uint32_t* status,
@@ -774,7 +856,7 @@ void launch_adjoint_step(const Geometry& geo, const SysBuffers& b, int B, int nb
                          int probe0, bool use_float, hipStream_t st) {
   const size_t vs = (size_t)geo.n * 3 * B;
   const int rb = rb_for(B);
-  dim3 grd(kRedBlocks, (B + rb - 1) / rb);
+  dim3 grd(row_blocks(geo.n, B), (B + rb - 1) / rb);
   double* Y0 = b.ybar;
   double* yn = Y0 + (size_t)((k + 1) % 3) * vs;
   double* yc = Y0 + (size_t)(k % 3) * vs;
@@ -788,7 +870,7 @@ void launch_adjoint_step(const Geometry& geo, const SysBuffers& b, int B, int nb
     MBD_RB_SWITCH(rb, (k_adj_dots<RB><<<grd, 256, 0, st>>>(geo.n, B, yn, wn, wk, wkm1,
                                                            k > 0 ? 1 : 0, b.part)));
     for (int q = 0; q < 5; ++q)
-      k_sum_slot<<<B, 256, 0, st>>>(B, q, kRedBlocks, b.part, b.coef + (size_t)q * B);
+      k_sum_slot<<<B, 256, 0, st>>>(B, q, (int)grd.x, b.part, b.coef + (size_t)q * B);
   } else {
     fill_double(b.coef, 0.0, (size_t)5 * B, st);
   }
