@@ -1513,7 +1513,7 @@ size_t scs_piece(size_t count) { return (count + kScsAlign - 1) / kScsAlign * kS
 size_t scs_doubles(int n, int nq, int nblk) {
   const size_t ncol = 3 * (size_t)nq, vec = (size_t)n * 3 * ncol;
   return scs_piece(4 * (size_t)n) + 2 * scs_piece((size_t)n * nq) + 5 * scs_piece(vec) +
-         scs_piece((size_t)nblk * 2 * ncol) + scs_piece(2 * ncol) + scs_piece(8 * ncol) +
+         scs_piece((size_t)nblk * 2 * ncol) + scs_piece(8 * ncol) +
          scs_piece(1) + 2 * scs_piece((size_t)nq);
 }
 
@@ -1534,7 +1534,6 @@ void carve_scs(double* base, ScsWork& w, double*& u_d, double*& w_d) {
   w.p = take(vec);
   w.q = take(vec);
   w.part = take((size_t)w.nblk * 2 * ncol);
-  w.sums = take(2 * ncol);
   w.sc = take(8 * ncol);
   w.nact = reinterpret_cast<int*>(take(1));
   u_d = take((size_t)w.nq);
@@ -1556,7 +1555,12 @@ mbd_status scs_prepare(Plan& P, int32_t sys, const mbd_scs_params* prm_in, mbd_s
   w.n = P.sys[sys].geo.n;
   w.nq = prm.n_freq + 1;  // the static point u = 0, then the quadrature nodes
   w.ncol = 3 * w.nq;
+  // row blocks of the dot products: at least 32 rows each up to 256 blocks, where the fixed
+  // scratch holds that many partial sums (the count decides the summation order, so it must
+  // not depend on which entry point runs), else at least 128 rows each
   w.nblk = std::max(1, std::min(512, (3 * w.n + 127) / 128));
+  const int fine = std::max(w.nblk, std::min(256, (3 * w.n + 31) / 32));
+  if (scs_doubles(w.n, w.nq, fine) <= kScsScratchDoubles) w.nblk = fine;
   return MBD_OK;
 }
 

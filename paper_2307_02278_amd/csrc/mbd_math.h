@@ -428,21 +428,30 @@ MBD_HD void tridiag_sqrt_adjoint(const double* theta, const double* u, int n, in
 //   z^2 = r2 / sig2,  c = (2 / sqrt pi) z exp(-z^2).
 // Beyond r = 7 sigma_ij, erf z = 1 and c (3 + 2 z^2) < 1e-18, so the bare tensor is used
 // (identical in float64).
-MBD_HD void scs_kernel(double r2, double sig2, double S, double d, double& A, double& B) {
+// scs_damped gives the frequency-independent part, A0 = (1 - f) / r^3 and
+// B0 = 3 (1 - f) / r^5, and returns the exponent d (r / S - 1); scs_overlap turns it into
+// A and B of one frequency.
+MBD_HD double scs_damped(double r2, double S, double d, double& A0, double& B0) {
   const double r = sqrt(r2);
-  const double omf = 1.0 / (1.0 + exp(d * (r / S - 1.0)));
-  const double z2 = r2 / sig2;
+  const double z = d * (r / S - 1.0);
   const double ir2 = 1.0 / r2;
-  const double ir3 = ir2 / r;
-  A = omf * ir3;
-  B = 3.0 * omf * ir3 * ir2;
+  A0 = ir2 / (r * (1.0 + exp(z)));
+  B0 = 3.0 * A0 * ir2;
+  return z;
+}
+MBD_HD void scs_overlap(double r2, double sig2, double& A, double& B) {
+  const double z2 = r2 / sig2;
   if (z2 < 49.0) {
     const double z = sqrt(z2);
     const double c = 1.1283791670955126 * z * exp(-z2);
     const double er = erf(z);
-    A = omf * (er - c) * ir3;
-    B = omf * (3.0 * er - c * (3.0 + 2.0 * z2)) * ir3 * ir2;
+    A *= er - c;
+    B *= er - c * (1.0 + (2.0 / 3.0) * z2);
   }
+}
+MBD_HD void scs_kernel(double r2, double sig2, double S, double d, double& A, double& B) {
+  scs_damped(r2, S, d, A, B);
+  scs_overlap(r2, sig2, A, B);
 }
 
 // Gauss-Legendre rule on [-1, 1]: the nodes are the roots of the Legendre polynomial
