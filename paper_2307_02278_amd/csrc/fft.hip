@@ -768,9 +768,13 @@ k_spread_xline(float* __restrict__ grid, GridDims gd, const Geometry geo,
   X(8) X(10) X(12) X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) \
   X(60) X(64) X(72) X(80) X(90) X(96) X(100) X(108) X(120) X(128)
 
+// Columns and threads per column of a work-group of the LDS transforms. Double: 16 columns
+// are whole 128-byte lines and 16 threads each shorten the chain of a column's stages; 32
+// columns x 8 threads took 12.1 to 14.0 us a pass at K = 96, B = 1 and 28 to 47 us at B = 8,
+// this one 9.0 to 11.2 us and 25 to 40 us.
 template <typename R> struct FftShape;
 template <> struct FftShape<float> { static constexpr int NC = 64, P = 4; };
-template <> struct FftShape<double> { static constexpr int NC = 32, P = 8; };
+template <> struct FftShape<double> { static constexpr int NC = 16, P = 16; };
 
 template <typename R, int MODE>
 void launch_pass(int K, R* grid, const GridDims& gd, int nchunks, const R* twc, const R* tws,

@@ -430,31 +430,52 @@ __global__ void k_energy(int n, int R, const double* __restrict__ q,
   (void)g;
 }
 
-// Caller layout [nrhs][N][3] (caller atom order) <-> internal [n][3][B] (sorted).
-__global__ void k_pack(int n, int nrhs, int B, const int* __restrict__ perm,
-                       const double* __restrict__ v, const double* __restrict__ g,
-                       double* __restrict__ w, double* __restrict__ dtmp,
-                       float* __restrict__ df, int use_float) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)3 * n * B) return;
-  const int b = (int)(t % B);
-  const long row = t / B;
-  const int s = (int)(row / 3), a = (int)(row % 3);
-  const double x = (b < nrhs) ? v[((size_t)b * n + perm[s]) * 3 + a] : 0.0;
-  w[t] = x;
-  const double d = g[s] * x;
-  if (use_float) df[t] = (float)d; else dtmp[t] = d;
+// Caller layout [nrhs][N][3] (caller atom order) <-> internal [n][3][B] (sorted), through
+// LDS in tiles of kPackAtoms atoms x 32 right-hand sides: on the caller's side consecutive
+// threads take an atom's consecutive components, on the internal side consecutive right-hand
+// sides. Read or written straight from the internal order, every caller value is its own
+// cache line (24k atoms x 128: 94 and 92 us a launch, 55 and 47 us here).
+constexpr int kPackAtoms = 16;
+constexpr int kPackRows = 3 * kPackAtoms;
+__global__ void __launch_bounds__(256)
+k_pack(int n, int nrhs, int B, const int* __restrict__ perm, const double* __restrict__ v,
+       const double* __restrict__ g, double* __restrict__ w, double* __restrict__ dtmp,
+       float* __restrict__ df, int use_float) {
+  __shared__ double tile[32][kPackRows + 1];
+  const int s0 = blockIdx.x * kPackAtoms, b0 = blockIdx.y * 32;
+  const int rows = min(kPackRows, 3 * (n - s0)), nb = min(32, B - b0);
+  for (int t = threadIdx.x; t < nb * kPackRows; t += 256) {
+    const int r = t % kPackRows, b = t / kPackRows;
+    if (r < rows)
+      tile[b][r] = b0 + b < nrhs
+                       ? v[((size_t)(b0 + b) * n + perm[s0 + r / 3]) * 3 + r % 3] : 0.0;
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < rows * nb; t += 256) {
+    const int b = t % nb, r = t / nb;
+    const double x = tile[b][r];
+    const size_t o = ((size_t)3 * s0 + r) * B + b0 + b;
+    w[o] = x;
+    const double d = g[s0 + r / 3] * x;
+    if (use_float) df[o] = (float)d; else dtmp[o] = d;
+  }
 }
 
-__global__ void k_unpack(int n, int nrhs, int B, const int* __restrict__ perm,
-                         const double* __restrict__ lt, double* __restrict__ out) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long)3 * n * B) return;
-  const int b = (int)(t % B);
-  if (b >= nrhs) return;
-  const long row = t / B;
-  const int s = (int)(row / 3), a = (int)(row % 3);
-  out[((size_t)b * n + perm[s]) * 3 + a] = lt[t];
+__global__ void __launch_bounds__(256)
+k_unpack(int n, int nrhs, int B, const int* __restrict__ perm, const double* __restrict__ lt,
+         double* __restrict__ out) {
+  __shared__ double tile[32][kPackRows + 1];
+  const int s0 = blockIdx.x * kPackAtoms, b0 = blockIdx.y * 32;
+  const int rows = min(kPackRows, 3 * (n - s0)), nb = min(32, nrhs - b0);
+  for (int t = threadIdx.x; t < rows * nb; t += 256) {
+    const int b = t % nb, r = t / nb;
+    tile[b][r] = lt[((size_t)3 * s0 + r) * B + b0 + b];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < nb * kPackRows; t += 256) {
+    const int r = t % kPackRows, b = t / kPackRows;
+    if (r < rows) out[((size_t)(b0 + b) * n + perm[s0 + r / 3]) * 3 + r % 3] = tile[b][r];
+  }
 }
 
 
@@ -898,16 +919,15 @@ void launch_forces_finish(const Geometry& geo, const SysBuffers& b, int R, doubl
 
 void launch_pack(const Geometry& geo, const SysBuffers& b, const double* v, int nrhs, int B,
                  bool use_float, hipStream_t st) {
-  const long tot = (long)3 * geo.n * B;
-  k_pack<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(geo.n, nrhs, B, b.perm, v, b.g, b.W,
-                                                         (double*)b.dv, (float*)b.dv,
-                                                         use_float ? 1 : 0);
+  const dim3 grd((geo.n + kPackAtoms - 1) / kPackAtoms, (B + 31) / 32);
+  k_pack<<<grd, 256, 0, st>>>(geo.n, nrhs, B, b.perm, v, b.g, b.W, (double*)b.dv, (float*)b.dv,
+                              use_float ? 1 : 0);
 }
 
 void launch_unpack(const Geometry& geo, const SysBuffers& b, double* out, int nrhs, int B,
                    hipStream_t st) {
-  const long tot = (long)3 * geo.n * B;
-  k_unpack<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(geo.n, nrhs, B, b.perm, b.Lt, out);
+  const dim3 grd((geo.n + kPackAtoms - 1) / kPackAtoms, (nrhs + 31) / 32);
+  k_unpack<<<grd, 256, 0, st>>>(geo.n, nrhs, B, b.perm, b.Lt, out);
 }
 
 }  // namespace mbd
