@@ -119,7 +119,8 @@ typedef struct {
 } mbd_shape;
 
 enum {
-  MBD_TUNE_OFF = 0,       /* built-in shape: pair_wg_per_cu 0, default chunk, overlap 1, and
+  MBD_TUNE_OFF = 0,       /* built-in shape: pair_wg_per_cu 0, default chunk, overlap 1 (0 for
+                             small systems, where the fork costs more than it hides), and
                              the matrix-core list kernel (pair_mode 1, widest split) where
                              it applies                                                   */
   MBD_TUNE_MEASURE = 1,   /* time candidate shapes on each system at plan creation and

@@ -608,12 +608,16 @@ double* scratch_of(int device) {
 // gather (sub-lanes share a stencil below 64 right-hand sides per chunk), and the
 // matrix-core pair kernel the order of the direct-space sums.
 
-// The built-in shape: every group resident, the default chunk, the side stream, and the
-// matrix-core list kernel with its widest candidate split where it applies (24k atoms, 128
-// right-hand sides, alone: 425 us a launch against 598 us of the vector kernel).
+// The built-in shape: every group resident, the default chunk, and the matrix-core list
+// kernel with its widest candidate split where it applies (24k atoms, 128 right-hand sides,
+// alone: 425 us a launch against 598 us of the vector kernel). The side stream costs each
+// matvec a fork and a join, 10 to 20 us, so it is used where the direct sum it hides takes
+// longer (matvec in us without and with it: 96 atoms, B = 1: 49 and 88; 648 atoms, B = 32,
+// energy: 1626 and 1714; 1501 atoms, B = 64: 135 and 128; 24k atoms, B = 1, energy: 18.8
+// and 18.6 ms).
 mbd_shape builtin_shape(const Plan& plan, const System& S) {
-  mbd_shape sh = {0, 0, 0, 1, 0, 0, 0};
   const int B = plan.B;
+  mbd_shape sh = {0, 0, 0, (long)S.geo.n * std::max(B, 4) >= 50000 ? 1 : 0, 0, 0, 0};
   if (plan.prec == MBD_PREC_MIXED && B % 64 == 0 && B <= 256 && S.buf.pg_T &&
       S.geo.replica_cut <= 0.0) {
     sh.pair_mode = 1;
