@@ -90,9 +90,8 @@ typedef struct {
                              0 => one work-group per 16-atom target group (all resident)  */
   int32_t pair_subsets;   /* vector list kernel: target subsets per wavefront, 1, 2 or 4
                              (at least 64 / block); 0 => the size rule (4096 wavefronts
-                             or more). Matrix-core kernel: wavefronts that share one
-                             group's candidates, 1, 2 or 4 (at most 4 wavefronts per
-                             work-group with block / 64 column wavefronts); 0 => 1      */
+                             or more). The matrix-core kernels, whose work-groups are
+                             always four wavefronts, ignore it                           */
   int32_t grid_chunk;     /* right-hand sides per SPME grid chunk: a power of two <= 64
                              that divides block; 0 => 64 (mixed) or 16 (float64)         */
   int32_t overlap;        /* pair kernel on a side stream, concurrent with the grid stages
@@ -108,12 +107,13 @@ typedef struct {
                              real grid; the fused form never writes it                  */
   int32_t pair_mode;      /* direct-space list kernel: 0 => vector FMA lanes, one lane per
                              right-hand side, skipping out-of-range pairs; 1 => matrix
-                             cores (v_mfma_f32_16x16x4_f32) over the dense per-group
-                             product (mixed precision, block a multiple of 64 up to 256;
-                             otherwise 0 is used), a wavefront holding 128 right-hand
-                             sides where block is a multiple of 128, else 64; 2 => the
-                             same with 64 right-hand sides per wavefront (half the
-                             accumulator registers). With forces, 1 and 2 also compute
+                             cores over the dense per-group product, floats in three
+                             bfloat16 planes (mixed precision, block a multiple of 64 up
+                             to 256; otherwise 0 is used), a wavefront holding 128
+                             right-hand sides where block is a multiple of 128, else 64;
+                             2 => the same with 64 right-hand sides per wavefront (half
+                             the accumulator registers). float64 and blocks below 64 run
+                             on the float matrix cores whatever the mode. With forces, 1 and 2 also compute
                              the direct force term on the matrix cores when
                              block <= 128                                                 */
 } mbd_shape;
@@ -121,8 +121,7 @@ typedef struct {
 enum {
   MBD_TUNE_OFF = 0,       /* built-in shape: pair_wg_per_cu 0, default chunk, overlap 1 (0 for
                              small systems, where the fork costs more than it hides), and
-                             the matrix-core list kernel (pair_mode 1, widest split) where
-                             it applies                                                   */
+                             the matrix-core list kernel (pair_mode 1) where it applies   */
   MBD_TUNE_MEASURE = 1,   /* time candidate shapes on each system at plan creation and
                              keep the fastest (reused from tune_cache when it holds one)  */
   MBD_TUNE_GIVEN = 2      /* use params.shape as given, for every system                 */

@@ -342,7 +342,7 @@ void create_pair_list(Plan& plan, System& S) {
   int mx = 0;
   check(hipStreamSynchronize(plan.stream), "pair list count");
   check(hipMemcpy(&mx, b.pg_max, sizeof(int), hipMemcpyDeviceToHost), "pair list count");
-  b.pg_cap = ((mx + mx / 4 + 32) + 15) / 16 * 16;
+  b.pg_cap = ((mx + mx / 4 + 32) + kListBlock - 1) / kListBlock * kListBlock;
   b.pg_hdr = dalloc<int2>(plan, (size_t)ngroups * b.pg_cap, S.bytes);
   b.pg_T = dalloc<R>(plan, (size_t)ngroups * b.pg_cap * kCandStride, S.bytes);
   b.pg_zero = dalloc<R>(plan, kTensorWords, S.bytes);
@@ -609,8 +609,8 @@ double* scratch_of(int device) {
 // matrix-core pair kernel the order of the direct-space sums.
 
 // The built-in shape: every group resident, the default chunk, and the matrix-core list
-// kernel with its widest candidate split where it applies (24k atoms, 128 right-hand sides,
-// alone: 425 us a launch against 598 us of the vector kernel). The side stream costs each
+// kernel where it applies (24k atoms, 128 right-hand sides, alone: 278 us a launch against
+// 598 us of the vector kernel). The side stream costs each
 // matvec a fork and a join, 10 to 20 us, so it is used where the direct sum it hides takes
 // longer (matvec in us without and with it: 96 atoms, B = 1: 49 and 88; 648 atoms, B = 32,
 // energy: 1626 and 1714; 1501 atoms, B = 64: 135 and 128; 24k atoms, B = 1, energy: 18.8
@@ -621,7 +621,6 @@ mbd_shape builtin_shape(const Plan& plan, const System& S) {
   if (plan.prec == MBD_PREC_MIXED && B % 64 == 0 && B <= 256 && S.buf.pg_T &&
       S.geo.replica_cut <= 0.0) {
     sh.pair_mode = 1;
-    sh.pair_subsets = B <= 128 ? 4 : 2;  // at most 4 wavefronts with B / 128 column wavefronts
   }
   return sh;
 }
@@ -753,13 +752,10 @@ double time_matvec(Plan& plan, System& S, int reps) {
 }
 
 // Coordinate search over the shape knobs on the system's real data: the pair kernel's
-// residency together with the side stream, then its lanes per target or the matrix-core
-// kernel with its candidate split, then the gather's work-group size, then the grid
-// chunk width, then the residency once more under the chosen chunk. Where the
-// matrix-core kernel applies it is the starting point, with its widest candidate split:
-// alone it is the faster pair kernel by about a fifth, while beside the side stream's
-// grid chain the two kernels often time within the 2 % margin, and a start from the
-// vector kernel would then keep the slower one. The fused x-line
+// residency together with the side stream, then the vector kernel's lanes per target or the
+// matrix-core kernel's wavefront width, then the gather's work-group size, then the grid
+// chunk width, then the residency once more under the chosen chunk. It starts from the
+// built-in shape. The fused x-line
 // spread is left out: it runs about four times slower than the tile spread plus the x
 // pass on a 96^3 grid with 24,000 atoms (each atom's loads and weights are repeated on
 // all 36 lines it touches).
@@ -768,10 +764,7 @@ void tune_system(Plan& plan, System& S, int sys_index) {
   const int B = plan.B;
   launch_probes(S.geo, S.buf, B, B, 0, plan.prm.seed, sys_index, sizeof(R) == 4, plan.stream);
   const bool list = S.buf.pg_T != nullptr && S.geo.replica_cut <= 0.0;
-  // the matrix-core launcher's rule: B / (128 or 64) column wavefronts times NK candidate
-  // shares, at most 4 wavefronts per work-group
   const bool mfma = list && plan.prec == MBD_PREC_MIXED && B % 64 == 0 && B <= 256;
-  const int mfma_nn = B / (B % 128 == 0 ? 128 : 64);
   mbd_shape best = builtin_shape(plan, S);
   apply_shape(plan, S, best);
   best = S.shape;
@@ -809,25 +802,12 @@ void tune_system(Plan& plan, System& S, int sys_index) {
       sh.pair_subsets = ns;
       if (base.pair_mode != 0 || base.pair_subsets != ns) trial(sh);
     }
-    // the matrix-core kernel with 4, 2 or 1 wavefronts per group's candidates, and, where
-    // B is a multiple of 128, with 64-column wavefronts (fewer accumulator registers per
-    // wavefront, which leaves room for the transforms beside it)
-    if (mfma) {
-      for (int nk : {4, 2, 1}) {
-        if (mfma_nn * nk > 4) continue;
-        mbd_shape sh = base;
-        sh.pair_mode = 1;
-        sh.pair_subsets = nk;
-        if (base.pair_mode != 1 || base.pair_subsets != nk) trial(sh);
-      }
-      if (B % 128 == 0)
-        for (int nk : {2, 1}) {
-          if ((B / 64) * nk > 4) continue;
-          mbd_shape sh = base;
-          sh.pair_mode = 2;
-          sh.pair_subsets = nk;
-          trial(sh);
-        }
+    // the matrix-core kernel with 64 right-hand sides per wavefront (fewer registers, which
+    // leaves room for the transforms beside it)
+    if (mfma && B % 128 == 0) {
+      mbd_shape sh = base;
+      sh.pair_mode = 2;
+      trial(sh);
     }
   }
   {

@@ -23,6 +23,7 @@ constexpr int kPartSlots = 8;      // partial-sum slots per reduction block: 0 a
 constexpr int kGroup = 16;
 constexpr int kTensorWords = 6;
 constexpr int kCandStride = kGroup * kTensorWords;
+constexpr int kListBlock = 32;     // candidates per block of the matrix-core kernels
 
 // Device-side error bits (status word).
 enum : uint32_t { kErrNotPosdef = 1u, kErrNonfinite = 2u, kErrNoConverge = 4u };

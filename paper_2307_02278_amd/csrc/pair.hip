@@ -450,6 +450,12 @@ k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
       __syncthreads();  // the round's staging is free again
     }
   }
+  // zero tensors up to a whole block of the matrix-core kernels (cap is a multiple of it)
+  if (cap > 0 && count < cap) {
+    const int pad = (count + kListBlock - 1) / kListBlock * kListBlock;
+    R* o = Tg + (size_t)group * cap * kCandStride;
+    for (int w = count * kCandStride + tid; w < pad * kCandStride; w += 256) o[w] = R(0);
+  }
   if (tid == 0) {
     gcount[group] = count;
     atomicMax(maxcount, count);
@@ -563,9 +569,8 @@ k_pair_list(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
 // products of a group are added in LDS in wavefront order, so the result does not depend
 // on timing. The source atoms of up to kMfmaChunk candidates at a time are staged in LDS;
 // each lane then reads its tensor row and dipole component straight from global memory,
-// one block of three steps ahead of the matrix instructions that use them. In float with
-// NK = 1 and one part the k order is the vector kernel's, and so far the two have given
-// the same bits.
+// one block of three steps ahead of the matrix instructions that use them.
+// Float blocks of 64 and more run k_pair_split instead.
 // Small systems: a launch of one work-group per group leaves most of the GPU idle (41 of
 // 256 CUs at 648 atoms) while each wavefront walks several hundred candidates, so the
 // candidates of a group are also split over gridDim.y work-groups, each writing its own
@@ -757,6 +762,190 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
       }
     }
   }  // groups of this work-group
+}
+
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// x = h + m + l in bfloat16, each the rounded remainder of the ones before: 8 bits each with
+// signs, so the 24 bits of a float, over the whole range of its exponents.
+struct Split8 {
+  bf16x8 h, m, l;
+};
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+  Split8 o;
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    const f32x2 v = {x[i], x[i + 1]};
+    const bf16x2 h = __builtin_convertvector(v, bf16x2);
+    const f32x2 r = v - __builtin_convertvector(h, f32x2);
+    const bf16x2 m = __builtin_convertvector(r, bf16x2);
+    const f32x2 q = r - __builtin_convertvector(m, f32x2);
+    const bf16x2 l = __builtin_convertvector(q, bf16x2);
+    o.h[i] = h[0]; o.h[i + 1] = h[1];
+    o.m[i] = m[0]; o.m[i + 1] = m[1];
+    o.l[i] = l[0]; o.l[i + 1] = l[1];
+  }
+  return o;
+}
+
+// The float direct sum for 64 right-hand sides and more, on the bfloat16 matrix cores, whose
+// rate is 16 times the float ones'. Tensors and dipoles are split into three bfloat16 planes
+// (h, m, l) in registers, and of the nine products of planes the six down to 2^-16 are
+// summed, the dropped three (2^-24 and below) being under the rounding of a float product.
+// For one component b of 32 candidates, v_mfma_f32_16x16x32_bf16 multiplies the tensor
+// components (a, b) of the group's 16 targets with 16 right-hand sides: it takes
+// A[i][k] from lane i + 16 (k / 8), element k % 8, B[k][j] likewise from lane
+// j + 16 (k / 8), and leaves D as the float instruction of k_pair_mfma does. The products of
+// a block of 32 candidates start from zero, smallest first, and are added to the running sum
+// in float once, so the instruction's alignment of its addends works on a block's sum and
+// not on the total: against a double sum the field's error is 1.25e-7 of its norm, 2.8e-7
+// with float products (24k atoms, 724 candidates a group).
+// A wavefront owns 16 NT right-hand sides and every fourth block of 32 candidates; it reads
+// the block's tensors once (24 bytes a pair, the list padded with zero tensors to whole
+// blocks), then the dipoles of ST column tiles at a time, one step ahead of their use. The
+// four partial sums are added in LDS in wavefront order; gridDim.y parts of the candidates
+// as in k_pair_mfma, gridDim.z slices of the right-hand sides. 24k atoms, B = 128: 417 us a
+// launch with float products, 278 us here, 12k atoms, B = 64: 122 and 78 us. What remains
+// is loads: 1.7 GB of dipoles and 0.42 GB of tensors a launch, half of it from beyond L2.
+template <int NT, int ST>
+__global__ void __launch_bounds__(256, 2)
+k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __restrict__ Tg,
+             const int* __restrict__ gcount, int cap, const float* __restrict__ dv,
+             float* __restrict__ Ed, int B) {
+  constexpr int NQ = NT / ST;  // column steps of ST tiles
+  __shared__ float red[4 * NT * 256];
+  __shared__ int jl[kMfmaChunk];
+  const int lane = threadIdx.x & 63;
+  const int wk = threadIdx.x >> 6;
+  const int col = lane & 15, row = lane >> 4;
+  const size_t Bs = (size_t)B;
+  const int rhs0 = blockIdx.z * 16 * NT;
+  const int part = blockIdx.y, parts = gridDim.y;
+  Ed += (size_t)part * 3 * geo.n * Bs + rhs0;
+  const int ngroups = (geo.n + kGroup - 1) / kGroup;
+  const int per = (ngroups + 7) / 8;
+  const int nbx = gridDim.x / 8;
+  for (int gi = blockIdx.x / 8; gi < per; gi += nbx) {
+    const int group = (blockIdx.x % 8) * per + gi;
+    if (group >= ngroups) return;  // uniform over the work-group
+    const int full = min(gcount[group], cap);
+    const int q32 = (full + 31) / 32;
+    const int clo = 32 * (int)((long)q32 * part / parts);
+    const int cnt = min(full, 32 * (int)((long)q32 * (part + 1) / parts));
+    const int2* H = hdr + (size_t)group * cap;
+    const float* T = Tg + (size_t)group * cap * kCandStride;
+    f32x4 acc[3][NT];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[a][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = clo; c0 < cnt; c0 += kMfmaChunk) {
+      const int nc = min(kMfmaChunk, cnt - c0);
+      const int nb = (nc + 31) / 32;
+      __syncthreads();  // the previous chunk's source atoms have been read
+      for (int c = threadIdx.x; c < 32 * nb; c += 256) jl[c] = H[c0 + (c < nc ? c : 0)].x;
+      __syncthreads();
+      for (int p = wk; p < nb; p += 4) {
+        const int cb = 32 * p + 8 * row;  // first of this lane's 8 candidates
+        const float* dp[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          dp[e] = dv + (size_t)jl[cb + e] * 3 * Bs + rhs0 + ST * col;
+        float d[2][8][ST];
+        auto load = [&](int b, int q, float (&o)[8][ST]) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const Pack<float, ST> v =
+                *reinterpret_cast<const Pack<float, ST>*>(dp[e] + b * Bs + 16 * ST * q);
+#pragma unroll
+            for (int u = 0; u < ST; ++u) o[e][u] = v.v[u];
+          }
+        };
+        load(0, 0, d[0]);
+        Split8 tt[6];
+        {
+          const float2* tp =
+              reinterpret_cast<const float2*>(T + ((size_t)(c0 + cb) * kGroup + col) * kTensorWords);
+          float tr[6][8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int w = 0; w < 3; ++w) {
+              const float2 v = tp[e * (kCandStride / 2) + w];
+              tr[2 * w][e] = v.x;
+              tr[2 * w + 1][e] = v.y;
+            }
+#pragma unroll
+          for (int w = 0; w < 6; ++w) tt[w] = split8(tr[w]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          // stored components (a, b): xx xy xz, xy yy yz, xz yz zz
+          constexpr int kRow[3][3] = {{0, 3, 4}, {3, 1, 5}, {4, 5, 2}};
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            const int st = b * NQ + q;
+            if (st + 1 < 3 * NQ) load((st + 1) / NQ, (st + 1) % NQ, d[(st + 1) & 1]);
+#pragma unroll
+            for (int u = 0; u < ST; ++u) {
+              float x[8];
+#pragma unroll
+              for (int e = 0; e < 8; ++e) x[e] = d[st & 1][e][u];
+              const Split8 s = split8(x);
+              f32x4 w[3];
+#pragma unroll
+              for (int a = 0; a < 3; ++a) w[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+#define MBD_STEP(TP, DP)                                                                  \
+  _Pragma("unroll") for (int a = 0; a < 3; ++a) w[a] =                                    \
+      __builtin_amdgcn_mfma_f32_16x16x32_bf16(tt[kRow[b][a]].TP, s.DP, w[a], 0, 0, 0)
+              MBD_STEP(l, h);
+              MBD_STEP(h, l);
+              MBD_STEP(m, m);
+              MBD_STEP(m, h);
+              MBD_STEP(h, m);
+              MBD_STEP(h, h);
+#undef MBD_STEP
+#pragma unroll
+              for (int a = 0; a < 3; ++a) acc[a][q * ST + u] += w[a];
+              // tile by tile: interleaved, the tiles' splits no longer fit the registers
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      __syncthreads();  // the previous round's partials have been read
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[((wk * NT + t) * 4 + r) * 64 + lane] = acc[a][t][r];
+      __syncthreads();
+      // wavefront wk: matrix row 4 row + wk of every tile
+      const int i = group * kGroup + 4 * row + wk;
+      if (i < geo.n) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          Pack<float, ST> w;
+#pragma unroll
+          for (int u = 0; u < ST; ++u) {
+            const int t = q * ST + u;
+            float v = red[(t * 4 + wk) * 64 + lane];
+#pragma unroll
+            for (int k = 1; k < 4; ++k) v += red[((k * NT + t) * 4 + wk) * 64 + lane];
+            w.v[u] = v;
+          }
+          *reinterpret_cast<Pack<float, ST>*>(Ed + ((size_t)i * 3 + a) * Bs + 16 * ST * q +
+                                              ST * col) = w;
+        }
+      }
+    }
+  }
 }
 
 
@@ -1255,22 +1444,14 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
       if (B == 16) MBD_PM(4, 1, 1); else MBD_PM(4, 2, 1);
       return;
     }
-    // 128 right-hand sides per wavefront (64 when B = 64 or 192, or with pair_mode 2),
-    // B / wide column wavefronts x NK candidate shares per group (NK from pair_ns, at most
-    // 4 wavefronts per work-group)
+    // 128 right-hand sides per wavefront, 64 when B = 64 or with pair_mode 2
     if (g.pair_mode == 1 || g.pair_mode == 2) {
-      const int wide = (g.pair_mode == 1 && B % 128 == 0) ? 128 : 64;
-      const int nn = B / wide;
-      int nk = g.pair_ns > 0 ? g.pair_ns : 1;
-      while (nk > 1 && nn * nk > 4) nk /= 2;
-      // (nk > 1 only with nn <= 2, and nn = 2 only with nk <= 2)
-      if (nk == 1) {
-        if (wide == 128) MBD_PM(1, 8, 1); else MBD_PM(1, 4, 1);
-      } else if (wide == 128) {
-        if (nk == 4) MBD_PM(4, 8, 1); else if (nn == 1) MBD_PM(2, 8, 1); else MBD_PM(2, 8, 2);
-      } else {
-        if (nk == 4) MBD_PM(4, 4, 1); else if (nn == 1) MBD_PM(2, 4, 1); else MBD_PM(2, 4, 2);
-      }
+      if (g.pair_mode == 1 && B % 128 == 0)
+        k_pair_split<8, 2><<<dim3(grd.x, nparts, B / 128), 256, 0, st>>>(
+            g, H, (const float*)T, b.pg_count, b.pg_cap, (const float*)dv, (float*)Ed, B);
+      else
+        k_pair_split<4, 4><<<dim3(grd.x, nparts, B / 64), 256, 0, st>>>(
+            g, H, (const float*)T, b.pg_count, b.pg_cap, (const float*)dv, (float*)Ed, B);
       return;
     }
 #undef MBD_PM
