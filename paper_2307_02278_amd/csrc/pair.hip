@@ -1074,40 +1074,42 @@ k_pair_force(const Geometry geo, const int2* __restrict__ hdr, const R* __restri
 }
 
 
-// The same direct force term on the matrix cores (float, B a multiple of 16, at most
-// 128). Summed over the right-hand sides, a pair's term needs only two 3x3 matrices,
-//   M1 = sum_rhs p_t q_j^T,  M2 = sum_rhs q_t p_j^T:
-//   X = tr M1 + tr M2,  (M1 + M1^T + M2 + M2^T) r = sum_rhs [p_t (q_j.r) + q_j (p_t.r)
-//   + q_t (p_j.r) + p_j (q_t.r)] =: m,  Y = r.m / 2,
-//   grad_r u = r (A'/r X - B'/r Y) - B m.
-// For a group's 16 targets and a block of 16 candidates, M1 and M2 are dense products
-// over the right-hand sides: 9 + 9 tiles of 16 x 16 (component pairs (a, b), rows =
-// targets, columns = candidates) with v_mfma_f32_16x16x4_f32 over k = right-hand side.
-// The order of k is free: in the u-th of four consecutive steps lane row kk takes right-
-// hand side 16 s + 4 kk + u, so that each lane reads its four values as one 16-byte
-// vector. The group's p_t and q_t sit in LDS for the whole group; the candidates' p_j and
-// q_j come from global memory one group of four steps ahead. After a block's last step
-// each lane holds M1 and M2 of the pairs (targets 4 kk .. 4 kk + 3, candidate lane % 16)
-// and adds their terms (in-range pairs only) to its float64 partial forces; the 16
-// candidate lanes, then the NK wavefronts of the group are summed in a fixed order and
-// the group's forces added to fsum (each group owns its targets: no atomics).
-template <int NK>
-__global__ void __launch_bounds__(64 * NK)
-k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float* __restrict__ Fg,
-                  const int* __restrict__ gcount, int cap, const float* __restrict__ pv,
-                  const float* __restrict__ qv, double* __restrict__ fsum, int B) {
-  constexpr int kMaxB = 128;
-  constexpr int RP = kMaxB + 4;  // padded row of one (vector, component, target) in LDS
-  __shared__ float4 tl4[2 * 3 * kGroup * RP / 4];  // [p|q][a][t][rhs]
-  __shared__ int jl[kMfmaChunk];
-  __shared__ int ml[kMfmaChunk];
-  __shared__ double red[NK][kGroup][3];
-  float* tl = reinterpret_cast<float*>(tl4);
-  fsum += (size_t)blockIdx.y * 3 * geo.n;
+// The same direct force term on the bfloat16 matrix cores (float, B a multiple of 16, at
+// most 128). Summed over the right-hand sides, a pair's term needs only one 3x3 matrix,
+//   M = sum_rhs p_t q_j^T + q_t p_j^T:
+//   X = tr M,  (M + M^T) r = sum_rhs [p_t (q_j.r) + q_j (p_t.r) + q_t (p_j.r) + p_j (q_t.r)]
+//   =: m,  Y = r.m / 2,  grad_r u = r (A'/r X - B'/r Y) - B m.
+// For a group's 16 targets and a block of 16 candidates, M is 9 tiles of 16 x 16 (component
+// pairs (a, b), rows = targets, columns = candidates), dense products over the 2 B values
+// k = (p_t | q_t) against (q_j | p_j), 32 a step. The floats are split into three bfloat16
+// planes and the six products above 2^-24 summed, as in k_pair_split: the targets' once per
+// group, into LDS, the candidates' in registers, their loads one step ahead. After a block's
+// last step each lane holds M of the pairs (targets 4 row .. 4 row + 3, candidate lane % 16)
+// and adds their terms (in-range pairs only) to its float64 partial forces; the 16 candidate
+// lanes, then the four wavefronts of the group are summed in a fixed order and the group's
+// forces added to this part's fsum (each group owns its targets: no atomics). 12k atoms,
+// B = 64, beside the grid stages: 447 us a launch with float products, 369 us here.
+constexpr int kForceChunk = 512;  // candidates per LDS chunk (a multiple of 16)
+inline size_t force_lds(int B) { return (size_t)3 * 3 * kGroup * (2 * B + 8) * 2; }
+
+__global__ void __launch_bounds__(256, 2)
+k_pair_force_split(const Geometry geo, const int2* __restrict__ hdr,
+                   const float* __restrict__ Fg, const int* __restrict__ gcount, int cap,
+                   const float* __restrict__ pv, const float* __restrict__ qv,
+                   double* __restrict__ fsum, int B) {
+  // [plane][a][t][k], rows padded by 16 bytes; the start of the next group waits for it
+  extern __shared__ unsigned char smem_raw[];
+  __bf16* tl = reinterpret_cast<__bf16*>(smem_raw);
+  __shared__ int jl[kForceChunk];
+  __shared__ int ml[kForceChunk];
+  __shared__ double red[4][kGroup][3];
+  const int RP = 2 * B + 8;                 // padded row
+  const int plane = 3 * kGroup * RP;        // elements of one plane
   const int lane = threadIdx.x & 63;
   const int wk = threadIdx.x >> 6;
   const int col = lane & 15, row = lane >> 4;
   const size_t Bs = (size_t)B;
+  fsum += (size_t)blockIdx.y * 3 * geo.n;
   const int ngroups = (geo.n + kGroup - 1) / kGroup;
   const int per = (ngroups + 7) / 8;
   const int nbx = gridDim.x / 8;
@@ -1122,71 +1124,84 @@ k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float*
     const int2* H = hdr + (size_t)group * cap;
     const float* F = Fg + (size_t)group * cap * kCandStride;
     __syncthreads();  // the previous group's LDS contents have been read
-    // the group's p_t and q_t: [x][a][t][rhs], zero for targets past the end
-    for (int e = threadIdx.x; e < 2 * 3 * kGroup * B; e += 64 * NK) {
-      const int r = e % B, t = (e / B) % kGroup, a = (e / (B * kGroup)) % 3, x = e / (B * kGroup * 3);
+    // the group's (p_t | q_t) in planes, zero for targets past the end: 8 values a thread
+    for (int e = threadIdx.x; e < 3 * kGroup * B / 4; e += 256) {
+      const int k8 = e % (B / 4), t = e / (B / 4) % kGroup, a = e / (B / 4 * kGroup);
       const int i = group * kGroup + t;
-      const float* src = x == 0 ? pv : qv;
-      tl[((x * 3 + a) * kGroup + t) * RP + r] = i < geo.n ? src[((size_t)i * 3 + a) * Bs + r] : 0.f;
+      const bool second = 8 * k8 >= B;
+      const float* src = (second ? qv : pv) + ((size_t)i * 3 + a) * Bs + (8 * k8 - (second ? B : 0));
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = i < geo.n ? src[u] : 0.f;
+      const Split8 sp = split8(x);
+      __bf16* o = tl + (a * kGroup + t) * RP + 8 * k8;
+      *reinterpret_cast<bf16x8*>(o) = sp.h;
+      *reinterpret_cast<bf16x8*>(o + plane) = sp.m;
+      *reinterpret_cast<bf16x8*>(o + 2 * plane) = sp.l;
     }
     double G[4][3];
 #pragma unroll
     for (int r = 0; r < 4; ++r) G[r][0] = G[r][1] = G[r][2] = 0.0;
-    for (int c0 = clo; c0 < cnt; c0 += kMfmaChunk) {
-      const int nc = min(kMfmaChunk, cnt - c0);
+    for (int c0 = clo; c0 < cnt; c0 += kForceChunk) {
+      const int nc = min(kForceChunk, cnt - c0);
       __syncthreads();  // the previous chunk's lists have been read
-      for (int c = threadIdx.x; c < nc; c += 64 * NK) {
+      for (int c = threadIdx.x; c < nc; c += 256) {
         const int2 h = H[c0 + c];
         jl[c] = h.x;
         ml[c] = h.y;
       }
       __syncthreads();
       const int nb = (nc + 15) / 16;  // blocks of 16 candidates
-      for (int blk = wk; blk < nb; blk += NK) {
+      for (int blk = wk; blk < nb; blk += 4) {
         const int c = blk * 16 + col;  // this lane's candidate column
         const bool ok = c < nc;
         const int j = jl[ok ? c : 0];
-        const float4* pj4 = reinterpret_cast<const float4*>(pv + (size_t)j * 3 * Bs);
-        const float4* qj4 = reinterpret_cast<const float4*>(qv + (size_t)j * 3 * Bs);
-        f32x4 m1[9], m2[9];
+        const float* pj = pv + (size_t)j * 3 * Bs;
+        const float* qj = qv + (size_t)j * 3 * Bs;
+        f32x4 acc[9];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) m1[q] = m2[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // candidate operands of the four steps of group s: components b of p_j and q_j at
-        // right-hand sides 16 s + 4 row .. + 3
-        float4 bp[3], bq[3];
-        auto load_b = [&](int s, float4 (&xp)[3], float4 (&xq)[3]) {
-          const int o = (s < B / 16 ? 4 * s + row : row);  // float4 index within a row
+        for (int q = 0; q < 9; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // candidate values of step s: components b of (q_j | p_j) at k = 32 s + 8 row .. + 7
+        const int steps = B / 16;
+        auto load = [&](int s, float (&o)[3][8]) {
+          const int k = 32 * min(s, steps - 1) + 8 * row;
+          const float* src = k < B ? qj + k : pj + (k - B);
 #pragma unroll
           for (int b = 0; b < 3; ++b) {
-            xp[b] = pj4[b * (Bs / 4) + o];
-            xq[b] = qj4[b * (Bs / 4) + o];
+            const float4 u = *reinterpret_cast<const float4*>(src + b * Bs);
+            const float4 v = *reinterpret_cast<const float4*>(src + b * Bs + 4);
+            o[b][0] = u.x; o[b][1] = u.y; o[b][2] = u.z; o[b][3] = u.w;
+            o[b][4] = v.x; o[b][5] = v.y; o[b][6] = v.z; o[b][7] = v.w;
           }
         };
-        load_b(0, bp, bq);
-        for (int s = 0; s < B / 16; ++s) {
-          float4 np[3], nq[3];
-          load_b(s + 1, np, nq);
-          // target operands from LDS: components a of p_t and q_t, target col
-          float4 ap[3], aq[3];
+        float nx[3][8];
+        load(0, nx);
+        for (int s = 0; s < steps; ++s) {
+          Split8 sb[3];
+#pragma unroll
+          for (int b = 0; b < 3; ++b) sb[b] = split8(nx[b]);
+          load(s + 1, nx);
+          const __bf16* ta = tl + col * RP + 32 * s + 8 * row;
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
-            ap[a] = *reinterpret_cast<const float4*>(&tl[((0 * 3 + a) * kGroup + col) * RP + 16 * s + 4 * row]);
-            aq[a] = *reinterpret_cast<const float4*>(&tl[((1 * 3 + a) * kGroup + col) * RP + 16 * s + 4 * row]);
-          }
+            const bf16x8 th = *reinterpret_cast<const bf16x8*>(ta + a * kGroup * RP);
+            const bf16x8 tm = *reinterpret_cast<const bf16x8*>(ta + a * kGroup * RP + plane);
+            const bf16x8 tw = *reinterpret_cast<const bf16x8*>(ta + a * kGroup * RP + 2 * plane);
+            f32x4 w[3];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
+            for (int b = 0; b < 3; ++b) w[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#define MBD_STEP(TP, DP)                                                             \
+  _Pragma("unroll") for (int b = 0; b < 3; ++b) w[b] =                               \
+      __builtin_amdgcn_mfma_f32_16x16x32_bf16(TP, sb[b].DP, w[b], 0, 0, 0)
+            MBD_STEP(tw, h);
+            MBD_STEP(th, l);
+            MBD_STEP(tm, m);
+            MBD_STEP(tm, h);
+            MBD_STEP(th, m);
+            MBD_STEP(th, h);
+#undef MBD_STEP
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-              for (int b = 0; b < 3; ++b) {
-                m1[3 * a + b] = __builtin_amdgcn_mfma_f32_16x16x4f32(ap[a][u], bq[b][u], m1[3 * a + b], 0, 0, 0);
-                m2[3 * a + b] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[a][u], bp[b][u], m2[3 * a + b], 0, 0, 0);
-              }
-          }
-#pragma unroll
-          for (int b = 0; b < 3; ++b) {
-            bp[b] = np[b];
-            bq[b] = nq[b];
+            for (int b = 0; b < 3; ++b) acc[3 * a + b] += w[b];
           }
         }
         // the block's pairs (target 4 row + r, candidate c): D[i][j] sits in register
@@ -1198,15 +1213,13 @@ k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float*
           if (!((msk >> (4 * row + r)) & 1u)) continue;
           const float rx = f[6 * r], ry = f[6 * r + 1], rz = f[6 * r + 2];
           const float Bk = f[6 * r + 3], c1 = f[6 * r + 4], c2 = f[6 * r + 5];
-          float M[3][3];
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) M[a][b] = m1[3 * a + b][r] + m2[3 * a + b][r];
-          const float X = M[0][0] + M[1][1] + M[2][2];
-          const float mx = (M[0][0] + M[0][0]) * rx + (M[0][1] + M[1][0]) * ry + (M[0][2] + M[2][0]) * rz;
-          const float my = (M[1][0] + M[0][1]) * rx + (M[1][1] + M[1][1]) * ry + (M[1][2] + M[2][1]) * rz;
-          const float mz = (M[2][0] + M[0][2]) * rx + (M[2][1] + M[1][2]) * ry + (M[2][2] + M[2][2]) * rz;
+          const float m00 = acc[0][r], m11 = acc[4][r], m22 = acc[8][r];
+          const float sxy = acc[1][r] + acc[3][r], sxz = acc[2][r] + acc[6][r],
+                      syz = acc[5][r] + acc[7][r];
+          const float X = m00 + m11 + m22;
+          const float mx = (m00 + m00) * rx + sxy * ry + sxz * rz;
+          const float my = sxy * rx + (m11 + m11) * ry + syz * rz;
+          const float mz = sxz * rx + syz * ry + (m22 + m22) * rz;
           const float Y = 0.5f * (rx * mx + ry * my + rz * mz);
           const float sc = c1 * X - c2 * Y;
           G[r][0] -= (double)(sc * rx - Bk * mx);
@@ -1235,7 +1248,7 @@ k_pair_force_mfma(const Geometry geo, const int2* __restrict__ hdr, const float*
       const int t = threadIdx.x / 3, a = threadIdx.x % 3;
       double v = 0.0;
 #pragma unroll
-      for (int w = 0; w < NK; ++w) v += red[w][t][a];
+      for (int w = 0; w < 4; ++w) v += red[w][t][a];
       const int i = group * kGroup + t;
       if (i < geo.n) fsum[3 * (size_t)i + a] += v;
     }
@@ -1504,7 +1517,11 @@ void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_
     // matrix cores, with the matrix-core direct sum: four wavefronts per group and part
     if ((g.pair_mode == 1 || g.pair_mode == 2 || B < 64) && B % 16 == 0 && B <= 128) {
       // every group resident, whatever residency cap the direct sum runs with
-      k_pair_force_mfma<4><<<dim3(nblk, b.fs_parts), 256, 0, st>>>(
+      const size_t lds = force_lds(B);
+      if (lds > 65536)  // B = 128: 76 KB, two work-groups a CU
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pair_force_split),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      k_pair_force_split<<<dim3(nblk, b.fs_parts), 256, lds, st>>>(
           g, H, (const float*)F, b.pg_count, b.pg_cap, (const float*)p, (const float*)q,
           b.fsum + 3 * (size_t)g.n, B);
       return;
