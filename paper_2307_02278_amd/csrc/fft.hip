@@ -11,6 +11,7 @@
 // 5) with one lane per column, and writes the columns back. Forward transforms
 // use e^{-2 pi i jk/K}, inverse ones e^{+2 pi i jk/K}; neither is normalized.
 #include "common.h"
+#include "stencil.h"
 
 namespace mbd {
 
@@ -634,10 +635,8 @@ k_fft_x_real(float* __restrict__ grid, GridDims gd) {
 // right-hand sides per chunk, order P): one wavefront per (y, z) line of one chunk, lane
 // = right-hand side. Each lane keeps its right-hand side's K line points in registers and
 // adds, from every atom whose y-z stencil covers the line (the setup's line lists, in atom
-// order), the atom's P x-points with the arithmetic of k_spread:
-//   A = d_x w_y w_z,  B = d_y w'_y w_z + d_z w_y w'_z,  q = fma(w'_x, A, q), fma(w_x, B, q)
-// (d = Mu d in u, w = M_P, w' = M_P'), in the same per-point order, so the real line
-// equals k_spread's. The lane then packs the line as K/2 complex points, runs the
+// order), the atom's P x-points with the weights and in the per-point order of k_spread, so
+// the real line equals k_spread's. The lane then packs the line as K/2 complex points, runs the
 // transform of k_fft_x_real<K, true> in registers and stores the half spectrum: the real
 // grid is never written and the separate x pass is not needed. A line-list entry packs the
 // atom and its stencil offsets along y and z: (s << 8) | (t_y << 4) | t_z.
@@ -698,32 +697,29 @@ k_spread_xline(float* __restrict__ grid, GridDims gd, const Geometry geo,
       const float* dp = dth + (size_t)sc[j] * 3 * P;
       const float wy = tp[P + ty[j]], dwy = dp[P + ty[j]];
       const float wz = tp[2 * P + tz[j]], dwz = dp[2 * P + tz[j]];
-      // dipole in u: (Mu d)_b
-      const float d0 = m00 * e0[j] + m01 * e1[j] + m02 * e2[j];
-      const float d1 = m10 * e0[j] + m11 * e1[j] + m12 * e2[j];
-      const float d2 = m20 * e0[j] + m21 * e1[j] + m22 * e2[j];
-      const float A = d0 * wy * wz;
-      const float Bc = d1 * dwy * wz + d2 * wy * dwz;
 #pragma unroll
       for (int t = 0; t < P; ++t) {
         int x = bx[j] - t;
         if (x < 0) x += K;
-        const float wa = dp[t], wb = tp[t];
+        const float wb = tp[t], wa = dp[t];
+        const float W0 = point_weight<float>(column_weight<float>(m00, m10, m20, wb, wa, wy, dwy), wz, dwz);
+        const float W1 = point_weight<float>(column_weight<float>(m01, m11, m21, wb, wa, wy, dwy), wz, dwz);
+        const float W2 = point_weight<float>(column_weight<float>(m02, m12, m22, wb, wa, wy, dwy), wz, dwz);
         const int g = x >> 5, o = x & 31;
         // the empty asm statements differ per branch, so the compiler does not merge the
         // four updates into one through a pointer that selects the array, which would
         // put the arrays in scratch memory
         if (g == 0) {
-          r0[o] = fma(wb, Bc, fma(wa, A, r0[o]));
+          r0[o] = fma(W2, e2[j], fma(W1, e1[j], fma(W0, e0[j], r0[o])));
           asm volatile("; line segment 0");
         } else if (g == 1) {
-          r1[o] = fma(wb, Bc, fma(wa, A, r1[o]));
+          r1[o] = fma(W2, e2[j], fma(W1, e1[j], fma(W0, e0[j], r1[o])));
           asm volatile("; line segment 1");
         } else if (K > 64 && g == 2) {
-          r2[o] = fma(wb, Bc, fma(wa, A, r2[o]));
+          r2[o] = fma(W2, e2[j], fma(W1, e1[j], fma(W0, e0[j], r2[o])));
           asm volatile("; line segment 2");
         } else if (K > 96) {
-          r3[o] = fma(wb, Bc, fma(wa, A, r3[o]));
+          r3[o] = fma(W2, e2[j], fma(W1, e1[j], fma(W0, e0[j], r3[o])));
           asm volatile("; line segment 3");
         }
       }

@@ -27,6 +27,7 @@
 #include "cells.h"
 #include "common.h"
 #include "mbd_math.h"
+#include "mfma.h"
 
 namespace mbd {
 
@@ -575,32 +576,7 @@ k_pair_list(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
 // 256 CUs at 648 atoms) while each wavefront walks several hundred candidates, so the
 // candidates of a group are also split over gridDim.y work-groups, each writing its own
 // part of the field; the gather adds the parts in order (pair_parts).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaChunk = 1024;  // candidates per LDS chunk (a multiple of 4)
-
-template <typename R> struct Mma;
-template <> struct Mma<float> {
-  typedef f32x4 acc;
-  static __device__ __forceinline__ acc fma(float a, float b, acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  // matrix row of register r in a lane of row group g = lane / 16
-  static __device__ __forceinline__ int row(int g, int r) { return 4 * g + r; }
-};
-template <> struct Mma<double> {
-  typedef f64x4 acc;
-  static __device__ __forceinline__ acc fma(double a, double b, acc c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int g, int r) { return g + 4 * r; }
-};
-
-// N consecutive reals moved as one vector (at most 16 bytes).
-template <typename R, int N>
-struct alignas(sizeof(R) * N) Pack {
-  R v[N];
-};
 
 template <typename R, int NT>
 struct MfmaOperands {

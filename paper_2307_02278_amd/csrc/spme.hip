@@ -19,6 +19,8 @@
 #include <algorithm>
 
 #include "common.h"
+#include "mfma.h"
+#include "stencil.h"
 
 namespace mbd {
 
@@ -48,19 +50,17 @@ struct Brick {
   static constexpr int BX = T / NX, BY = T / NY;  // bricks per tile along x and y
 };
 
-// Spread with register tiles: one wavefront owns a 4x4x4 tile of grid points for BG
-// right-hand sides and keeps the point values of its lane in registers (64, or the BG of
-// its brick when fewer than 64 right-hand sides share the wavefront).
+// Spread with register tiles, for fewer than 16 right-hand sides: one wavefront owns a
+// 4x4x4 tile of grid points and keeps the point values of its lane's brick in registers.
 // It walks the tile's atom list in a fixed order, so the result is deterministic.
 // For one atom the weights along each axis of the tile are
 //   w_a(q) = M_p(u_a - k_a) for the tile point k_a = tile origin + q,
 // nonzero only when 0 <= t = (base_a - k_a) mod K_a < p, i.e. t = o_a - q with
 // o_a = (base_a - origin_a) mod K_a; a batch of atoms at a time has them staged in LDS.
-// Narrow chunks are bound by the latency of the dipole loads, so they take four atoms'
-// dipoles at a time, and up to 8 right-hand sides stage them beside the weights.
+// Bound by the latency of the dipole loads, it stages them beside the weights.
 template <typename R, int P, int BG>
 __global__ void __launch_bounds__(256)
-k_spread(const Geometry geo, const int* __restrict__ tile_start,
+k_spread_brick(const Geometry geo, const int* __restrict__ tile_start,
          const int* __restrict__ tile_atoms, const int* __restrict__ base,
          const R* __restrict__ th, const R* __restrict__ dth, const R* __restrict__ dv, int B,
          R* __restrict__ grid, size_t chunk_elems, int chunk0) {
@@ -70,17 +70,13 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
   constexpr int NWT = 6 * T;            // staged weights per atom: w, dw along x, y, z
   // atoms per batch: about 20 touch a tile at 0.1 atoms per A^3 and 1.5 points per A; the
   // stage of a work-group stays at 24 KB, so that LDS does not limit the resident waves
-  constexpr int NBAT = BG == 64 ? 64 : (sizeof(R) == 8 ? 16 : 32);
+  constexpr int NBAT = sizeof(R) == 8 ? 16 : 32;
   constexpr int NPART = 64 / NBAT;      // staging lanes per atom
-  constexpr bool DLDS = BG <= 8;        // dipoles staged too
-  constexpr int PF = BG == 64 ? 1 : 4;  // dipoles in flight (atoms) otherwise
   __shared__ R wts_all[4][NBAT][NWT];
-  __shared__ R dip_all[4][DLDS ? NBAT : 1][DLDS ? 3 * BG : 1];
-  __shared__ int sat_all[4][NBAT];      // atom index of each staged slot
+  __shared__ R dip_all[4][NBAT][3 * BG];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int lane = threadIdx.x & 63;
   R(*wts)[NWT] = wts_all[wave];
-  int* sat = sat_all[wave];
   const int ntiles = geo.tiles[0] * geo.tiles[1] * geo.tiles[2];
   // Blocks are dealt round-robin to the 8 XCDs (gridDim.x is a multiple of 8):
   // each XCD takes one contiguous range of tiles, a slab of the grid, so the
@@ -91,7 +87,6 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
   const int chunk = blockIdx.y + chunk0;
   const int b = lane % BG;
   const int sub = lane / BG;
-  const int bg = chunk * BG + b;
   // origin of the lane's brick in the tile
   const int px0 = (sub % Bk::BX) * NX, py0 = (sub / Bk::BX % Bk::BY) * NY,
             pz0 = sub / (Bk::BX * Bk::BY) * NZ;
@@ -130,11 +125,8 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
               wts[i][(2 * ax + d) * T + q] = v ? (d ? dthp : thp)[ax * P + t] : R(0);
             }
           }
-        if (part == 0) sat[i] = s;
-        if constexpr (DLDS) {
-          for (int e = part; e < 3 * BG; e += NPART)
-            dip_all[wave][i][e] = dv[((size_t)s * 3 + e / BG) * B + chunk * BG + e % BG];
-        }
+        for (int e = part; e < 3 * BG; e += NPART)
+          dip_all[wave][i][e] = dv[((size_t)s * 3 + e / BG) * B + chunk * BG + e % BG];
       }
     }
     // the batch's LDS writes are visible to the whole wavefront before it reads them
@@ -144,59 +136,33 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
     const R m00 = (R)geo.Mu[0][0], m01 = (R)geo.Mu[0][1], m02 = (R)geo.Mu[0][2];
     const R m10 = (R)geo.Mu[1][0], m11 = (R)geo.Mu[1][1], m12 = (R)geo.Mu[1][2];
     const R m20 = (R)geo.Mu[2][0], m21 = (R)geo.Mu[2][1], m22 = (R)geo.Mu[2][2];
-    // dipoles of PF atoms from slot a on (past the batch: its last atom again, unused)
-    auto fetch = [&](int a, R (&n)[PF][3]) {
+    for (int a = 0; a < na; ++a) {
+      // dipole in u: (Mu d)_b
+      const R* n = &dip_all[wave][a][b];
+      const R d0 = m00 * n[0] + m01 * n[BG] + m02 * n[2 * BG];
+      const R d1 = m10 * n[0] + m11 * n[BG] + m12 * n[2 * BG];
+      const R d2 = m20 * n[0] + m21 * n[BG] + m22 * n[2 * BG];
+      const R* wa = wts[a];
+      R wx[NX], dwx[NX], wy[NY], dwy[NY], wz[NZ], dwz[NZ];
 #pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        const int i = min(a + u, na - 1);
-        if constexpr (DLDS) {
+      for (int q = 0; q < NX; ++q) { wx[q] = wa[px0 + q]; dwx[q] = wa[T + px0 + q]; }
 #pragma unroll
-          for (int c = 0; c < 3; ++c) n[u][c] = dip_all[wave][i][c * BG + b];
-        } else {
-          const int s = __builtin_amdgcn_readfirstlane(sat[i]);
+      for (int q = 0; q < NY; ++q) { wy[q] = wa[2 * T + py0 + q]; dwy[q] = wa[3 * T + py0 + q]; }
 #pragma unroll
-          for (int c = 0; c < 3; ++c) n[u][c] = dv[((size_t)s * 3 + c) * B + bg];
-        }
-      }
-    };
-    R nx[PF][3];
-    fetch(0, nx);
-    for (int a = 0; a < na; a += PF) {
-      R cur[PF][3];
+      for (int q = 0; q < NZ; ++q) { wz[q] = wa[4 * T + pz0 + q]; dwz[q] = wa[5 * T + pz0 + q]; }
+      // every point of the brick: the staged weights are zero outside the stencil, and
+      // a branch-free loop issues fewer instructions than uniform per-point tests
 #pragma unroll
-      for (int u = 0; u < PF; ++u)
+      for (int pz = 0; pz < NZ; ++pz) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) cur[u][c] = nx[u][c];
-      if (a + PF < na) fetch(a + PF, nx);  // next dipoles while these are spread
+        for (int py = 0; py < NY; ++py) {
+          const R A = d0 * wy[py] * wz[pz];
+          const R Bc = d1 * dwy[py] * wz[pz] + d2 * wy[py] * dwz[pz];
 #pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        if (PF > 1 && a + u >= na) break;  // uniform over the wavefront
-        // dipole in u: (Mu d)_b
-        const R d0 = m00 * cur[u][0] + m01 * cur[u][1] + m02 * cur[u][2];
-        const R d1 = m10 * cur[u][0] + m11 * cur[u][1] + m12 * cur[u][2];
-        const R d2 = m20 * cur[u][0] + m21 * cur[u][1] + m22 * cur[u][2];
-        const R* wa = wts[a + u];
-        R wx[NX], dwx[NX], wy[NY], dwy[NY], wz[NZ], dwz[NZ];
-#pragma unroll
-        for (int q = 0; q < NX; ++q) { wx[q] = wa[px0 + q]; dwx[q] = wa[T + px0 + q]; }
-#pragma unroll
-        for (int q = 0; q < NY; ++q) { wy[q] = wa[2 * T + py0 + q]; dwy[q] = wa[3 * T + py0 + q]; }
-#pragma unroll
-        for (int q = 0; q < NZ; ++q) { wz[q] = wa[4 * T + pz0 + q]; dwz[q] = wa[5 * T + pz0 + q]; }
-        // every point of the brick: the staged weights are zero outside the stencil, and
-        // a branch-free loop issues fewer instructions than uniform per-point tests
-#pragma unroll
-        for (int pz = 0; pz < NZ; ++pz) {
-#pragma unroll
-          for (int py = 0; py < NY; ++py) {
-            const R A = d0 * wy[py] * wz[pz];
-            const R Bc = d1 * dwy[py] * wz[pz] + d2 * wy[py] * dwz[pz];
-#pragma unroll
-            for (int px = 0; px < NX; ++px) {
-              R& q = acc[(pz * NY + py) * NX + px];
-              q = fma(dwx[px], A, q);
-              q = fma(wx[px], Bc, q);
-            }
+          for (int px = 0; px < NX; ++px) {
+            R& q = acc[(pz * NY + py) * NX + px];
+            q = fma(dwx[px], A, q);
+            q = fma(wx[px], Bc, q);
           }
         }
       }
@@ -213,6 +179,154 @@ k_spread(const Geometry geo, const int* __restrict__ tile_start,
     const int x = x0 + px0 + i % NX, y = y0 + py0 + (i / NX) % NY, z = z0 + pz0 + i / (NX * NY);
     if (x < K1 && y < K2 && z < K3) g[(((size_t)z * K2 + y) * XS + x) * BG + b] = acc[i];
   }
+}
+
+// Spread on the matrix cores, for chunks of BG = 16 NT right-hand sides: over the atoms of
+// its list a 4x4x4 tile is a dense product,
+//   D[point][rhs] = sum_k W[point][k] d[k][rhs],  k = 3 atom + component,
+// of four 16-point planes (rows; one z each) with NT column tiles. A wavefront owns a tile
+// for a chunk and takes four atoms (12 rows of k, three instructions of four) at a time: in
+// step u lane row r holds k = 4 u + r, so its atom and component are fixed, and it forms the
+// weights of its (x, y) column for the four planes from the staged splines. Column col of
+// tile t is right-hand side NT col + t, so dipoles and grid rows move as vectors. The sum
+// runs in list order, atom by atom, component by component, whatever the split into fours
+// (zero weights outside a stencil add nothing). With one lane per right-hand side, an atom is
+// one serial step of 128 multiply-adds in every lane; here four are one step of 48 matrix
+// instructions. Boxes of 525 to 4200 atoms, 64 right-hand sides: 26.6 us a launch before,
+// 20.4 here; 651 atoms, 16: 15.8 and 12.3; 24k atoms, K = 96, 64: 112 and 105, of which the
+// matrix instructions are 46, the weights and the staging about 35 and the 226 MB grid
+// write, which starts when a tile is done, 38.
+template <typename R, int P, int NT>
+__global__ void __launch_bounds__(256)
+k_spread(const Geometry geo, const int* __restrict__ tile_start,
+         const int* __restrict__ tile_atoms, const int* __restrict__ base,
+         const R* __restrict__ th, const R* __restrict__ dth, const R* __restrict__ dv, int B,
+         R* __restrict__ grid, size_t chunk_elems, int chunk0) {
+  typedef typename Mma<R>::acc Acc;
+  constexpr int T = kSpreadTile;
+  constexpr int BG = 16 * NT;
+  constexpr int VN = NT * (int)sizeof(R) > 16 ? 16 / (int)sizeof(R) : NT;  // reals per vector
+  constexpr int NWT = 6 * T;            // staged weights per atom: w, dw along x, y, z
+  constexpr int NBAT = sizeof(R) == 8 ? 32 : 64;  // atoms per batch (24 KB a work-group)
+  __shared__ alignas(16) R wts_all[4][NBAT][NWT];
+  __shared__ int sat_all[4][NBAT];      // atom index of each staged slot
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
+  const int lane = threadIdx.x & 63;
+  const int col = lane & 15, row = lane >> 4;
+  R(*wts)[NWT] = wts_all[wave];
+  int* sat = sat_all[wave];
+  const int ntiles = geo.tiles[0] * geo.tiles[1] * geo.tiles[2];
+  // each XCD takes one contiguous range of tiles (gridDim.x is a multiple of 8), a slab of
+  // the grid, so the dipoles of the atoms it spreads stay in its L2
+  const int per = gridDim.x / 8;
+  const int tile = ((blockIdx.x % 8) * per + blockIdx.x / 8) * 4 + wave;
+  if (tile >= ntiles) return;
+  const int chunk = blockIdx.y + chunk0;
+  const int tx = tile % geo.tiles[0];
+  const int ty = (tile / geo.tiles[0]) % geo.tiles[1];
+  const int tz = tile / (geo.tiles[0] * geo.tiles[1]);
+  const int x0 = tx * T, y0 = ty * T, z0 = tz * T;
+  const int K1 = geo.K[0], K2 = geo.K[1], K3 = geo.K[2];
+  // step u of a block of four atoms: this lane's atom, component and column of Mu
+  int au[3], cu[3];
+  R mu[3][3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    au[u] = (4 * u + row) / 3;
+    cu[u] = (4 * u + row) % 3;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) mu[u][a] = (R)geo.Mu[a][cu[u]];
+  }
+  const int px = col % T, py = col / T;  // the lane's (x, y) column as a matrix row
+  const R* dcol = dv + chunk * BG + NT * col;
+  Acc acc[T][NT];
+#pragma unroll
+  for (int z = 0; z < T; ++z)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[z][t] = Acc{R(0), R(0), R(0), R(0)};
+  const int lo = tile_start[tile], hi = tile_start[tile + 1];
+  for (int a0 = lo; a0 < hi; a0 += NBAT) {
+    const int na = min(NBAT, hi - a0);
+    const int na4 = (na + 3) & ~3;  // (zero weights on the last atom's dipoles past na)
+    // Stage the tile-clipped weights, one (atom, axis, value or slope) row of four a lane
+    // and pass: an atom's rows are neighbours in memory, and every lane has one
+    for (int e = lane; e < 6 * na4; e += 64) {
+      const int i = e / 6, ax = e % 6 % 3, d = e % 6 / 3;
+      const int s = tile_atoms[a0 + min(i, na - 1)];
+      int o = base[3 * s + ax] - (ax == 0 ? x0 : ax == 1 ? y0 : z0);
+      if (o < 0) o += ax == 0 ? K1 : ax == 1 ? K2 : K3;
+      const R* p = (d ? dth : th) + ((size_t)s * 3 + ax) * P;
+#pragma unroll
+      for (int q = 0; q < T; ++q) {
+        const int t = o - q;
+        const bool v = i < na && t >= 0 && t < P;
+        wts[i][(2 * ax + d) * T + q] = v ? p[t] : R(0);
+      }
+      if (e % 6 == 0) sat[i] = s;
+    }
+    // the batch's LDS writes are visible to the whole wavefront before it reads them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    R d[3][NT];  // dipoles of the next four atoms
+    auto fetch = [&](int a) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const Pack<R, VN>* p = reinterpret_cast<const Pack<R, VN>*>(
+            dcol + ((size_t)sat[a + au[u]] * 3 + cu[u]) * B);
+#pragma unroll
+        for (int q = 0; q < NT / VN; ++q) {
+          const Pack<R, VN> v = p[q];
+#pragma unroll
+          for (int w = 0; w < VN; ++w) d[u][VN * q + w] = v.v[w];
+        }
+      }
+    };
+    fetch(0);
+    for (int a = 0; a < na4; a += 4) {
+      R cur[3][NT];
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) cur[u][t] = d[u][t];
+      if (a + 4 < na4) fetch(a + 4);
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const R* wa = wts[a + au[u]];
+        const ColumnWeight<R> cw = column_weight<R>(mu[u][0], mu[u][1], mu[u][2], wa[px],
+                                                    wa[T + px], wa[2 * T + py], wa[3 * T + py]);
+#pragma unroll
+        for (int z = 0; z < T; ++z) {
+          const R w = point_weight<R>(cw, wa[4 * T + z], wa[5 * T + z]);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[z][t] = Mma<R>::fma(w, cur[u][t], acc[z][t]);
+        }
+      }
+    }
+    // all reads of this batch are done before the next batch overwrites the stage
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  R* g = grid + (size_t)chunk * chunk_elems + NT * col;
+  const int XS = K1 + 2;
+#pragma unroll
+  for (int z = 0; z < T; ++z)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = Mma<R>::row(row, r);
+      const int x = x0 + i % T, y = y0 + i / T;
+      if (x >= K1 || y >= K2 || z0 + z >= K3) continue;
+      Pack<R, VN>* o =
+          reinterpret_cast<Pack<R, VN>*>(g + (((size_t)(z0 + z) * K2 + y) * XS + x) * BG);
+#pragma unroll
+      for (int q = 0; q < NT / VN; ++q) {
+        Pack<R, VN> v;
+#pragma unroll
+        for (int w = 0; w < VN; ++w) v.v[w] = acc[z][VN * q + w][r];
+        o[q] = v;
+      }
+    }
 }
 
 // Row r = P t3 + t2 of an atom's stencil rows: its first grid value (without the x index).
@@ -507,24 +621,24 @@ void launch_spread(const Geometry& geo, const SysBuffers& b, int B, int BG, int 
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
   const int ntiles = geo.tiles[0] * geo.tiles[1] * geo.tiles[2];
   dim3 grd(((ntiles + 3) / 4 + 7) / 8 * 8, nchunks);  // a multiple of 8 (XCD remap)
-#define MBD_SPREAD(PP, BB)                                                                  \
-  k_spread<R, PP, BB><<<grd, 256, 0, st>>>(geo, b.tile_start, b.tile_atoms, b.base,        \
-                                           (const R*)b.th, (const R*)b.dth, (const R*)b.dv, \
-                                           B, (R*)b.grid, chunk, chunk0)
-#define MBD_SPREAD_P(BB)                    \
-  switch (geo.p) {                          \
-    case 4: MBD_SPREAD(4, BB); break;       \
-    case 6: MBD_SPREAD(6, BB); break;       \
-    case 8: MBD_SPREAD(8, BB); break;       \
+#define MBD_SPREAD(KERNEL, PP, NN)                                                          \
+  KERNEL<R, PP, NN><<<grd, 256, 0, st>>>(geo, b.tile_start, b.tile_atoms, b.base,          \
+                                         (const R*)b.th, (const R*)b.dth, (const R*)b.dv,  \
+                                         B, (R*)b.grid, chunk, chunk0)
+#define MBD_SPREAD_P(KERNEL, NN)              \
+  switch (geo.p) {                            \
+    case 4: MBD_SPREAD(KERNEL, 4, NN); break; \
+    case 6: MBD_SPREAD(KERNEL, 6, NN); break; \
+    case 8: MBD_SPREAD(KERNEL, 8, NN); break; \
   }
   switch (BG) {
-    case 1: MBD_SPREAD_P(1); break;
-    case 2: MBD_SPREAD_P(2); break;
-    case 4: MBD_SPREAD_P(4); break;
-    case 8: MBD_SPREAD_P(8); break;
-    case 16: MBD_SPREAD_P(16); break;
-    case 32: MBD_SPREAD_P(32); break;
-    case 64: MBD_SPREAD_P(64); break;
+    case 1: MBD_SPREAD_P(k_spread_brick, 1); break;
+    case 2: MBD_SPREAD_P(k_spread_brick, 2); break;
+    case 4: MBD_SPREAD_P(k_spread_brick, 4); break;
+    case 8: MBD_SPREAD_P(k_spread_brick, 8); break;
+    case 16: MBD_SPREAD_P(k_spread, 1); break;
+    case 32: MBD_SPREAD_P(k_spread, 2); break;
+    case 64: MBD_SPREAD_P(k_spread, 4); break;
   }
 #undef MBD_SPREAD_P
 #undef MBD_SPREAD
