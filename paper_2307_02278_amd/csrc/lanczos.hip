@@ -116,8 +116,10 @@ k_update(int n, int B, int nb, int k, int m, int probe0, const double* __restric
   double dot = 0.0, sq = 0.0;
   if (ng > 0) {
     if (b < B) {
+#pragma unroll 8
       for (int i = threadIdx.x / RB; i < ng; i += ROWS) dot += part[(size_t)i * kPartSlots * B + b];
       if (k > 0)
+#pragma unroll 8
         for (int i = threadIdx.x / RB; i < nu; i += ROWS)
           sq += part[((size_t)i * kPartSlots + norm_slot(k)) * B + b];
     }

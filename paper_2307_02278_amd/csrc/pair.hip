@@ -244,19 +244,19 @@ k_pair_nbr(const Geometry geo, const int* __restrict__ cell_start,
 // Tensor list: build (once per device setup) and apply (every matvec).
 // ---------------------------------------------------------------------------
 
-// One work-group (256 threads) per group of kGroup consecutive sorted targets.
+// One work-group (BT threads) per group of kGroup consecutive sorted targets.
 // Candidate sources are the atoms of the cells around the group whose distance to
 // the group's bounding box is below r_pair; those within r_pair of at least one
 // target are appended with their tensors, in the order of the cell scan (z, y, x,
 // then atom index). The cells are taken in chunks: their atom counts are prefix-summed
-// in LDS, every thread tests one candidate of a 256-candidate round, the hits are
-// compacted in order (wavefront ballots plus a prefix over the four wavefronts), and
+// in LDS, every thread tests one candidate of a BT-candidate round, the hits are
+// compacted in order (wavefront ballots plus a prefix over the wavefronts), and
 // the tensors of a round are then written with one thread per (candidate, target)
 // pair, so that consecutive threads store consecutive tensor words. With cap == 0
 // only the counts are produced (plan sizing).
 constexpr int kBuildCells = 256;  // cells per chunk of the scan
-template <typename R>
-__global__ void __launch_bounds__(256)
+template <typename R, int BT>
+__global__ void __launch_bounds__(BT)
 k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
              const int* __restrict__ scell, const R* __restrict__ loc, int cap,
              int2* __restrict__ hdr, R* __restrict__ Tg, R* __restrict__ Fg,
@@ -268,10 +268,10 @@ k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
   __shared__ int c_pre[kBuildCells + 1];   // prefix of the chunk's cell atom counts
   __shared__ int c_first[kBuildCells];     // first atom of each cell
   __shared__ int c_off[kBuildCells];       // packed (dx, dy, dz) cell offsets
-  __shared__ int wcnt[4];
-  __shared__ R s_p[256][4];                // compacted hits of a round: position, radius
-  __shared__ int s_m[256];                 // their target masks
-  __shared__ int s_o[256];                 // their packed cell offsets
+  __shared__ int wcnt[BT / 64];
+  __shared__ R s_p[BT][4];                // compacted hits of a round: position, radius
+  __shared__ int s_m[BT];                  // their target masks
+  __shared__ int s_o[BT];                 // their packed cell offsets
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -358,7 +358,7 @@ k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
     if (tid == 0) c_pre[0] = 0;
     __syncthreads();
     const int total = c_pre[ncc];
-    for (int r0 = 0; r0 < total; r0 += 256) {
+    for (int r0 = 0; r0 < total; r0 += BT) {
       const int c = r0 + tid;
       uint32_t mask = 0;
       R px = R(0), py = R(0), pz = R(0), ps = R(0);
@@ -401,7 +401,9 @@ k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
       __syncthreads();
       int wpre = 0;
       for (int w = 0; w < wave; ++w) wpre += wcnt[w];
-      const int nloc = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+      int nloc = 0;
+#pragma unroll
+      for (int w = 0; w < BT / 64; ++w) nloc += wcnt[w];
       if (mask != 0u) {
         const int li = wpre + below;
         s_p[li][0] = px; s_p[li][1] = py; s_p[li][2] = pz; s_p[li][3] = ps;
@@ -413,7 +415,7 @@ k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
       __syncthreads();
       if (cap > 0) {
         // tensors of the round's hits: thread <-> (hit, target)
-        for (int p = tid; p < nloc * kGroup; p += 256) {
+        for (int p = tid; p < nloc * kGroup; p += BT) {
           const int li = p / kGroup, t = p % kGroup;
           const int slot = count + li;
           if (slot >= cap) continue;
@@ -455,7 +457,7 @@ k_pair_build(const Geometry geo, const int* __restrict__ cell_start,
   if (cap > 0 && count < cap) {
     const int pad = (count + kListBlock - 1) / kListBlock * kListBlock;
     R* o = Tg + (size_t)group * cap * kCandStride;
-    for (int w = count * kCandStride + tid; w < pad * kCandStride; w += 256) o[w] = R(0);
+    for (int w = count * kCandStride + tid; w < pad * kCandStride; w += BT) o[w] = R(0);
   }
   if (tid == 0) {
     gcount[group] = count;
@@ -1466,9 +1468,14 @@ template <typename R>
 void launch_pair_build(const Geometry& g, const SysBuffers& b, bool count_only, hipStream_t st) {
   const int ngroups = (g.n + kGroup - 1) / kGroup;
   fill_int(b.pg_max, 0, 1, st);
-  k_pair_build<R><<<ngroups, 256, 0, st>>>(
-      g, b.cell_start, b.scell, (const R*)b.loc, count_only ? 0 : b.pg_cap, b.pg_hdr,
-      (R*)b.pg_T, count_only ? nullptr : (R*)b.pg_F, b.pg_count, b.pg_max);
+#define MBD_PB(BT)                                                                        \
+  k_pair_build<R, BT><<<ngroups, BT, 0, st>>>(                                            \
+      g, b.cell_start, b.scell, (const R*)b.loc, count_only ? 0 : b.pg_cap, b.pg_hdr,     \
+      (R*)b.pg_T, count_only ? nullptr : (R*)b.pg_F, b.pg_count, b.pg_max)
+  // below four work-groups per CU a group's scan is a latency chain: four times the threads
+  // (648 atoms, 41 groups: 89 us a launch with 256, 55 us with 1024)
+  if (ngroups < 1024) MBD_PB(1024); else MBD_PB(256);
+#undef MBD_PB
 }
 
 template <typename R>

@@ -38,31 +38,37 @@ __global__ void k_wrap_count(const Geometry geo, const double* __restrict__ pos,
   atomicAdd(&count[cell], 1);
 }
 
-// Exclusive scan of count[0..m) into start[0..m]; one block.
-__global__ void k_scan(int m, const int* __restrict__ count, int* __restrict__ start) {
-  __shared__ int chunk_sums[1024];
-  const int T = blockDim.x;
+// Exclusive scan of count[0..m) into start[0..m], one work-group of 1024 threads; the counts
+// are cleared on the way (the fill that follows uses them as cursors). The chunk sums are
+// scanned across lanes, then across the 16 wavefronts.
+__global__ void __launch_bounds__(1024)
+k_scan(int m, int* __restrict__ count, int* __restrict__ start) {
+  __shared__ int wsum[16];
+  const int T = 1024, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int per = (m + T - 1) / T;
-  const int lo = threadIdx.x * per;
-  const int hi = min(m, lo + per);
+  const int lo = min(m, t * per), hi = min(m, lo + per);
   int s = 0;
   for (int i = lo; i < hi; ++i) s += count[i];
-  chunk_sums[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int t = 0; t < T; ++t) {
-      int v = chunk_sums[t];
-      chunk_sums[t] = acc;
-      acc += v;
-    }
-    start[m] = acc;
+  int v = s;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o);
+    if (lane >= o) v += u;
   }
+  if (lane == 63) wsum[wave] = v;
   __syncthreads();
-  int acc = chunk_sums[threadIdx.x];
+  int acc = v - s, total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int x = wsum[w];
+    if (w < wave) acc += x;
+    total += x;
+  }
+  if (t == 0) start[m] = total;
   for (int i = lo; i < hi; ++i) {
+    const int c = count[i];
+    count[i] = 0;
     start[i] = acc;
-    acc += count[i];
+    acc += c;
   }
 }
 
@@ -75,22 +81,25 @@ __global__ void k_scatter(int n, const int* __restrict__ cell_of, const int* __r
   perm[start[c] + slot] = i;
 }
 
-// Deterministic order inside each cell: by sub-cell (Morton), then caller index.
-__global__ void k_sort_cells(int ncell, const int* __restrict__ start,
-                             const uint32_t* __restrict__ subkey, int* __restrict__ perm) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncell) return;
-  int lo = start[c], hi = start[c + 1];
-  for (int i = lo + 1; i < hi; ++i) {
-    const int v = perm[i];
-    const unsigned long long kv = ((unsigned long long)subkey[v] << 32) | (unsigned)v;
-    int j = i - 1;
-    while (j >= lo && (((unsigned long long)subkey[perm[j]] << 32) | (unsigned)perm[j]) > kv) {
-      perm[j + 1] = perm[j];
-      --j;
-    }
-    perm[j + 1] = v;
+// Deterministic order inside each cell, by sub-cell (Morton), then caller index: every atom
+// counts the cell's atoms before it (an insertion sort per cell is one thread's serial chain,
+// 300 us for 96 atoms in one cell).
+__global__ void k_rank_cells(int n, const int* __restrict__ cell_of,
+                             const int* __restrict__ start, const uint32_t* __restrict__ subkey,
+                             const int* __restrict__ unsorted, int* __restrict__ perm) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= n) return;
+  const int i = unsorted[s];
+  const int c = cell_of[i];
+  const int lo = start[c], hi = start[c + 1];
+  const unsigned long long key = ((unsigned long long)subkey[i] << 32) | (unsigned)i;
+  int rank = 0;
+#pragma unroll 4
+  for (int q = lo; q < hi; ++q) {
+    const int j = unsorted[q];
+    rank += (((unsigned long long)subkey[j] << 32) | (unsigned)j) < key ? 1 : 0;
   }
+  perm[lo + rank] = i;
 }
 
 template <typename R, int P>
@@ -164,11 +173,14 @@ __global__ void k_sorted_tables(Geometry geo, const int* __restrict__ perm,
       }
 }
 
+// Tile lists, one lane per (atom, touched tile): an atom's up to 64 returning atomics are in
+// flight together.
 template <int P>
 __global__ void k_tile_fill(Geometry geo, const int* __restrict__ base,
                             const int* __restrict__ tile_start, int* __restrict__ cursor,
                             int* __restrict__ tile_atoms) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
+  const int s = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & 63;
   if (s >= geo.n) return;
   int tl[3][4], nt[3];
   for (int a = 0; a < 3; ++a) {
@@ -182,13 +194,11 @@ __global__ void k_tile_fill(Geometry geo, const int* __restrict__ base,
       if (!seen) tl[a][nt[a]++] = tt;
     }
   }
-  for (int z = 0; z < nt[2]; ++z)
-    for (int y = 0; y < nt[1]; ++y)
-      for (int xx = 0; xx < nt[0]; ++xx) {
-        int tile = (tl[2][z] * geo.tiles[1] + tl[1][y]) * geo.tiles[0] + tl[0][xx];
-        int slot = atomicAdd(&cursor[tile], 1);
-        tile_atoms[tile_start[tile] + slot] = s;
-      }
+  if (lane >= nt[0] * nt[1] * nt[2]) return;
+  const int x = lane % nt[0], y = lane / nt[0] % nt[1], z = lane / (nt[0] * nt[1]);
+  const int tile = (tl[2][z] * geo.tiles[1] + tl[1][y]) * geo.tiles[0] + tl[0][x];
+  const int slot = atomicAdd(&cursor[tile], 1);
+  tile_atoms[tile_start[tile] + slot] = s;
 }
 
 // x-lines (y, z) covered by the y-z stencil of each atom: y = base_y - t_y, z = base_z - t_z
@@ -213,19 +223,40 @@ __global__ void k_line_lists(Geometry geo, const int* __restrict__ base, int* __
   }
 }
 
-// Deterministic order inside each tile's list.
-__global__ void k_sort_tiles(int ntiles, const int* __restrict__ start, int* __restrict__ list) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
+// Deterministic order inside each list, one wavefront per list: every entry (all distinct)
+// counts the smaller ones in an LDS copy. Lists longer than that (none at the densities of
+// condensed matter: about 20 entries) are insertion-sorted by one lane.
+constexpr int kSortLds = 512;
+__global__ void __launch_bounds__(256)
+k_sort_tiles(int ntiles, const int* __restrict__ start, int* __restrict__ list) {
+  __shared__ int copy_all[4][kSortLds];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int* copy = copy_all[wave];
+  const int c = blockIdx.x * 4 + wave;
   if (c >= ntiles) return;
-  int lo = start[c], hi = start[c + 1];
-  for (int i = lo + 1; i < hi; ++i) {
-    int v = list[i];
-    int j = i - 1;
-    while (j >= lo && list[j] > v) {
-      list[j + 1] = list[j];
-      --j;
+  const int lo = start[c], len = start[c + 1] - lo;
+  if (len <= kSortLds) {
+    for (int i = lane; i < len; i += 64) copy[i] = list[lo + i];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int i = lane; i < len; i += 64) {
+      const int v = copy[i];
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < len; ++j) rank += copy[j] < v ? 1 : 0;
+      list[lo + rank] = v;
     }
-    list[j + 1] = v;
+  } else if (lane == 0) {
+    for (int i = lo + 1; i < lo + len; ++i) {
+      const int v = list[i];
+      int j = i - 1;
+      while (j >= lo && list[j] > v) {
+        list[j + 1] = list[j];
+        --j;
+      }
+      list[j + 1] = v;
+    }
   }
 }
 
@@ -252,10 +283,11 @@ void launch_setup(const Geometry& g, SysBuffers& b, const double* pos, const dou
   k_wrap_count<<<blocks_for(g.n, 256), 256, 0, st>>>(g, pos, b.wpos, b.cell_of, b.subkey,
                                                       b.cell_cursor);
   k_scan<<<1, 1024, 0, st>>>(ncell, b.cell_cursor, b.cell_start);
-  fill_int(b.cell_cursor, 0, ncell, st);
+  // (the tile lists, not yet built, hold the unsorted order)
   k_scatter<<<blocks_for(g.n, 256), 256, 0, st>>>(g.n, b.cell_of, b.cell_start, b.cell_cursor,
-                                                   b.perm);
-  k_sort_cells<<<blocks_for(ncell, 128), 128, 0, st>>>(ncell, b.cell_start, b.subkey, b.perm);
+                                                   b.tile_atoms);
+  k_rank_cells<<<blocks_for(g.n, 64), 64, 0, st>>>(g.n, b.cell_of, b.cell_start, b.subkey,
+                                                    b.tile_atoms, b.perm);
   fill_int(b.tile_count, 0, ntiles + 1, st);
 #define MBD_TABLES(PP)                                                                        \
   k_sorted_tables<R, PP><<<blocks_for(g.n, 128), 128, 0, st>>>(                               \
@@ -268,19 +300,18 @@ void launch_setup(const Geometry& g, SysBuffers& b, const double* pos, const dou
   }
 #undef MBD_TABLES
   k_scan<<<1, 1024, 0, st>>>(ntiles, b.tile_count, b.tile_start);
-  fill_int(b.tile_count, 0, ntiles + 1, st);
   switch (g.p) {
-    case 4: k_tile_fill<4><<<blocks_for(g.n, 256), 256, 0, st>>>(g, b.base, b.tile_start,
+    case 4: k_tile_fill<4><<<blocks_for(g.n, 4), 256, 0, st>>>(g, b.base, b.tile_start,
                                                                   b.tile_count, b.tile_atoms);
       break;
-    case 6: k_tile_fill<6><<<blocks_for(g.n, 256), 256, 0, st>>>(g, b.base, b.tile_start,
+    case 6: k_tile_fill<6><<<blocks_for(g.n, 4), 256, 0, st>>>(g, b.base, b.tile_start,
                                                                   b.tile_count, b.tile_atoms);
       break;
-    case 8: k_tile_fill<8><<<blocks_for(g.n, 256), 256, 0, st>>>(g, b.base, b.tile_start,
+    case 8: k_tile_fill<8><<<blocks_for(g.n, 4), 256, 0, st>>>(g, b.base, b.tile_start,
                                                                   b.tile_count, b.tile_atoms);
       break;
   }
-  k_sort_tiles<<<blocks_for(ntiles, 128), 128, 0, st>>>(ntiles, b.tile_start, b.tile_atoms);
+  k_sort_tiles<<<blocks_for(ntiles, 4), 256, 0, st>>>(ntiles, b.tile_start, b.tile_atoms);
   if (g.line_lists) launch_line_lists(g, b, st);
 }
 
@@ -292,10 +323,9 @@ void launch_line_lists(const Geometry& g, SysBuffers& b, hipStream_t st) {
     k_line_lists<6><<<blocks_for(g.n, 256), 256, 0, st>>>(g, b.base, b.line_count, nullptr,
                                                           nullptr);
     k_scan<<<1, 1024, 0, st>>>(nlines, b.line_count, b.line_start);
-    fill_int(b.line_count, 0, nlines + 1, st);
     k_line_lists<6><<<blocks_for(g.n, 256), 256, 0, st>>>(g, b.base, b.line_count,
                                                           b.line_start, b.line_atoms);
-    k_sort_tiles<<<blocks_for(nlines, 128), 128, 0, st>>>(nlines, b.line_start, b.line_atoms);
+    k_sort_tiles<<<blocks_for(nlines, 4), 256, 0, st>>>(nlines, b.line_start, b.line_atoms);
   }
 }
 

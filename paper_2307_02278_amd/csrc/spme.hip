@@ -26,14 +26,16 @@ namespace mbd {
 
 namespace {
 
-// Lanes of a gather wavefront: BG right-hand sides x NS sub-lanes that share one atom's
-// stencil rows (the P^2 (y, z) rows of P points) x AW atoms. Narrow chunks keep NS at 16 or
+// Lanes of a gather wavefront: BL right-hand sides x NS sub-lanes that share one atom's
+// stencil rows (the P^2 (y, z) rows of P points) x AW atoms. BL is the chunk width BG, or 16
+// in small systems: a chunk is then BG / 16 slices of the launch, each wavefront's chain of
+// rows is that much shorter and there are that many more wavefronts. Narrow chunks keep NS at 16 or
 // less, because 36 rows over 64 sub-lanes leave 28 of them idle, and take several atoms per
 // wavefront instead.
-template <int BG>
+template <int BL>
 struct Lanes {
-  static constexpr int NS = BG >= 8 ? 64 / BG : (BG == 4 ? 8 : 16);
-  static constexpr int LA = BG * NS;   // lanes per atom
+  static constexpr int NS = BL >= 8 ? 64 / BL : (BL == 4 ? 8 : 16);
+  static constexpr int LA = BL * NS;   // lanes per atom
   static constexpr int AW = 64 / LA;   // atoms per wavefront
 };
 
@@ -339,7 +341,7 @@ __device__ __forceinline__ const R* stencil_row(const R* gr, int by, int bz, int
   return gr + ((size_t)k3 * K2 + k2) * XS * BG;
 }
 
-template <typename R, int P, int BG>
+template <typename R, int P, int BG, int BL>
 __global__ void __launch_bounds__(512)
 k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __restrict__ th,
                   const R* __restrict__ dth, const R* __restrict__ grid, size_t chunk_elems,
@@ -347,14 +349,15 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
                   const double* __restrict__ g, const double* __restrict__ om2, int B,
                   uint32_t comps, double self_coef, double* __restrict__ lt,
                   double* __restrict__ part, int chunk0) {
-  constexpr int NS = Lanes<BG>::NS, LA = Lanes<BG>::LA, AW = Lanes<BG>::AW;
-  __shared__ double red[8 * BG];
+  constexpr int NS = Lanes<BL>::NS, LA = Lanes<BL>::LA, AW = Lanes<BL>::AW;
+  __shared__ double red[8 * BL];
   const int nw = blockDim.x >> 6;  // wavefronts per work-group (4 or 8)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int lane = threadIdx.x & 63;
-  const int b = lane % BG;
-  const int sub = lane % LA / BG;
-  const int chunk = blockIdx.y + chunk0;
+  const int slice = blockIdx.y % (BG / BL);  // of the chunk's right-hand sides
+  const int b = slice * BL + lane % BL;
+  const int sub = lane % LA / BL;
+  const int chunk = blockIdx.y / (BG / BL) + chunk0;
   const int bg = chunk * BG + b;
   const R* gr = grid + (size_t)chunk * chunk_elems;
   const int K1 = geo.K[0], K2 = geo.K[1], K3 = geo.K[2];
@@ -431,7 +434,7 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
       }
       // combine the sub-lanes that split the stencil rows
 #pragma unroll
-      for (int off = BG; off < LA; off <<= 1) {
+      for (int off = BL; off < LA; off <<= 1) {
         e0 += __shfl_xor(e0, off);
         e1 += __shfl_xor(e1, off);
         e2 += __shfl_xor(e2, off);
@@ -454,8 +457,15 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
         double E = (a == 0) ? (double)e0 : (a == 1) ? (double)e1 : (double)e2;
         if (comps & MBD_C_DIR) {
           E += (double)Ed[idx];
-          for (int q = 1; q < ed_parts; ++q)
-            E += (double)Ed[(size_t)q * 3 * geo.n * B + idx];
+          // the parts in order, five loads in flight (past the last part: a zero)
+          const size_t pstride = (size_t)3 * geo.n * B;
+          for (int q0 = 1; q0 < ed_parts; q0 += 5) {
+            R x[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) x[i] = Ed[min(q0 + i, ed_parts - 1) * pstride + idx];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) E += q0 + i < ed_parts ? (double)x[i] : 0.0;
+          }
         }
         if (comps & MBD_C_SELF) E += self_coef * gs * wv;
         double l = gs * E;
@@ -467,13 +477,13 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
   }
   // per-RHS sum over the lanes of a right-hand side, then the work-group's wavefronts
 #pragma unroll
-  for (int off = BG; off < 64; off <<= 1) dot += __shfl_xor(dot, off);
-  if (lane < BG) red[wave * BG + lane] = dot;
+  for (int off = BL; off < 64; off <<= 1) dot += __shfl_xor(dot, off);
+  if (lane < BL) red[wave * BL + lane] = dot;
   __syncthreads();
-  if (threadIdx.x < BG) {
+  if (threadIdx.x < BL) {
     double t = 0.0;
-    for (int wv = 0; wv < nw; ++wv) t += red[wv * BG + threadIdx.x];
-    part[((size_t)blockIdx.x * kPartSlots + 0) * B + chunk * BG + threadIdx.x] = t;
+    for (int wv = 0; wv < nw; ++wv) t += red[wv * BL + threadIdx.x];
+    part[((size_t)blockIdx.x * kPartSlots + 0) * B + chunk * BG + slice * BL + threadIdx.x] = t;
   }
 }
 
@@ -648,26 +658,30 @@ template <typename R>
 void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, int B, int BG,
                      int chunk0, int nchunks, uint32_t comps, hipStream_t st) {
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
-  dim3 grd(gather_blocks(geo, BG), nchunks);
+  // slices of 16 while whole chunks would leave fewer than four wavefronts per SIMD (648
+  // atoms, chunks of 32: 20 us a launch whole, 11.4 us in slices)
+  const bool sliced = geo.n < 4096;
+  const dim3 grd(gather_blocks(geo, BG), nchunks * (sliced && BG > 16 ? BG / 16 : 1));
   const double self_coef = -4.0 * geo.tau * geo.tau * geo.tau / (3.0 * sqrt(M_PI));
-#define MBD_GATHER(PP, BB)                                                                  \
-  k_gather_epilogue<R, PP, BB><<<grd, 64 * gather_waves(geo), 0, st>>>(                   \
+#define MBD_GATHER(PP, BB, LL)                                                              \
+  k_gather_epilogue<R, PP, BB, LL><<<grd, 64 * gather_waves(geo), 0, st>>>(               \
       geo, b.base, (const R*)b.th, (const R*)b.dth, (const R*)b.grid, chunk,               \
-      (const R*)b.Ed, pair_parts(geo, b, B), w, b.g, b.om2, B, comps, self_coef, b.Lt, b.part, chunk0)
-#define MBD_GATHER_P(BB)                    \
+      (const R*)b.Ed, pair_parts(geo, b, B), w, b.g, b.om2, B, comps, self_coef, b.Lt,     \
+      b.part, chunk0)
+#define MBD_GATHER_P(BB, LL)                \
   switch (geo.p) {                          \
-    case 4: MBD_GATHER(4, BB); break;       \
-    case 6: MBD_GATHER(6, BB); break;       \
-    case 8: MBD_GATHER(8, BB); break;       \
+    case 4: MBD_GATHER(4, BB, LL); break;   \
+    case 6: MBD_GATHER(6, BB, LL); break;   \
+    case 8: MBD_GATHER(8, BB, LL); break;   \
   }
   switch (BG) {
-    case 1: MBD_GATHER_P(1); break;
-    case 2: MBD_GATHER_P(2); break;
-    case 4: MBD_GATHER_P(4); break;
-    case 8: MBD_GATHER_P(8); break;
-    case 16: MBD_GATHER_P(16); break;
-    case 32: MBD_GATHER_P(32); break;
-    case 64: MBD_GATHER_P(64); break;
+    case 1: MBD_GATHER_P(1, 1); break;
+    case 2: MBD_GATHER_P(2, 2); break;
+    case 4: MBD_GATHER_P(4, 4); break;
+    case 8: MBD_GATHER_P(8, 8); break;
+    case 16: MBD_GATHER_P(16, 16); break;
+    case 32: if (sliced) MBD_GATHER_P(32, 16) else MBD_GATHER_P(32, 32) break;
+    case 64: if (sliced) MBD_GATHER_P(64, 16) else MBD_GATHER_P(64, 64) break;
   }
 #undef MBD_GATHER_P
 #undef MBD_GATHER
