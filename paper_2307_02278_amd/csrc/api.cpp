@@ -368,8 +368,8 @@ int spread_chunk(Plan& plan, System& S, const SysBuffers& b, int c, hipStream_t 
 
 // The adjoint matvec C lbar_k (into Lt) together with the bilinear force terms
 // lbar_k^T dC/dR y_k of one reverse step: the pair part, then per grid chunk the
-// reciprocal part with phi of p = g lbar_k (left by the matvec) and with phi of
-// q = g y_k. q is c9 g y_k with a per-right-hand-side factor c9 (b.adj[16 rhs + 9]), so
+// reciprocal part with phi of p = g lbar_k (the matvec's own, gathered in the same pass) and
+// with phi of q = g y_k. q is c9 g y_k with a per-right-hand-side factor c9 (b.adj[16 rhs + 9]), so
 // when the forward sweep kept its grids phi of q is c9 times the kept phi of step k,
 // and the factor moves onto p; otherwise q is spread and transformed once more. The
 // pair kernel and the pair force (into the direct half of fsum) run on the side stream
@@ -382,11 +382,14 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
   SysBuffers& b = S.buf;
   SysBuffers bq = b;
   bq.dv = b.dq;
+  // nothing reads ybar_0 (the probes are fixed), so step 0 has force terms only
+  const bool adjoint = k > 0;
   SideStream* sd = nullptr;
   auto pair_work = [&] {
     sd = S.overlap ? fork_side(plan, st) : nullptr;
     const hipStream_t ss = sd ? sd->side : st;
-    staged_on(plan, MBD_STAGE_PAIR, ss, [&] { launch_pair<R>(S.geo, b, plan.B, ss); });
+    if (adjoint)
+      staged_on(plan, MBD_STAGE_PAIR, ss, [&] { launch_pair<R>(S.geo, b, plan.B, ss); });
     if (sd) check(hipEventRecord(sd->pair_done, ss), "side join");
     staged_on(plan, MBD_STAGE_FORCE, ss, [&] { launch_pair_force<R>(S.geo, b, plan.B, ss); });
   };
@@ -400,11 +403,9 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
              [&] { launch_fft_pass<R>(S.geo, b, plan.B, BG, c, 1, pass, st); });
   if (sd) check(hipStreamWaitEvent(st, sd->pair_done, 0), "side join");
   for (int c = 0; c < nch; ++c) {
-    staged(plan, MBD_STAGE_GATHER, [&] {
-      launch_epilogue<R>(S.geo, b, b.lbar, plan.B, BG, c, 1, MBD_C_ALL, st);
+    staged(plan, MBD_STAGE_FORCE, [&] {
+      launch_spme_force<R>(S.geo, b, b.dq, plan.B, BG, c, st, nullptr, adjoint ? b.lbar : nullptr);
     });
-    staged(plan, MBD_STAGE_FORCE,
-           [&] { launch_spme_force<R>(S.geo, b, b.dq, plan.B, BG, c, st); });
     if (b.phi) {
       SysBuffers bk = b;
       bk.grid = (R*)b.phi +
@@ -430,16 +431,12 @@ void run_backward(Plan& plan, System& S, int l0, int nb) {
   const hipStream_t st = plan.stream;
   const int B = plan.B, m = plan.prm.n_steps;
   const bool fl = sizeof(R) == 4;
-  const size_t vs = 3 * (size_t)S.geo.n * B;
-  staged(plan, MBD_STAGE_ADJOINT, [&] {
-    launch_tridiag_adjoint(S.buf, nb, m, l0, plan.status, st);
-    fill_double(S.buf.ybar, 0.0, 3 * vs, st);
-  });
+  staged(plan, MBD_STAGE_ADJOINT,
+         [&] { launch_tridiag_adjoint(S.buf, nb, m, l0, plan.status, st); });
   for (int k = m - 1; k >= 0; --k) {
     staged(plan, MBD_STAGE_ADJOINT,
            [&] { launch_adjoint_step(S.geo, S.buf, B, nb, k, m, l0, fl, st); });
     adjoint_matvec_forces<R>(plan, S, k);
-    staged(plan, MBD_STAGE_ADJOINT, [&] { launch_adjoint_accumulate(S.geo, S.buf, B, k, st); });
   }
 }
 

@@ -325,13 +325,12 @@ template <typename R>
 void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_t st);
 template <typename R>
 void launch_spme_force(const Geometry& g, const SysBuffers& b, const void* h, int B, int BG,
-                       int chunk0, hipStream_t st, const double* hscale = nullptr);
+                       int chunk0, hipStream_t st, const double* hscale = nullptr,
+                       const double* w = nullptr);
 void launch_tridiag_adjoint(const SysBuffers& b, int nb, int m, int probe0, uint32_t* status,
                             hipStream_t st);
 void launch_adjoint_step(const Geometry& g, const SysBuffers& b, int B, int nb, int k, int m,
                          int probe0, bool use_float, hipStream_t st);
-void launch_adjoint_accumulate(const Geometry& g, const SysBuffers& b, int B, int k,
-                               hipStream_t st);
 void launch_forces_finish(const Geometry& g, const SysBuffers& b, int R, double* forces,
                           hipStream_t st);
 void fill_double(double* p, double v, size_t n, hipStream_t st);

@@ -603,12 +603,14 @@ k_tridiag_adjoint(int m, int probe0, const double* __restrict__ a,
   }
 }
 
+// The reverse sweep keeps ybar_{k+1} as two addends, yn and the previous step's adjoint
+// matvec lt = C lbar_{k+1}; both readers below add them up, so no pass writes the sum.
 // Five dot products per right-hand side into partial slots 0..4:
 //   ybar_{k+1}.w_{k+1}, ybar_{k+1}.w_k, ybar_{k+1}.w_{k-1}, w_{k+1}.w_k, w_{k+1}.w_{k-1}.
 template <int RB>
 __global__ void __launch_bounds__(256)
-k_adj_dots(int n, int B, const double* __restrict__ yn, const double* __restrict__ wn,
-           const double* __restrict__ wk, const double* __restrict__ wkm1, int has_km1,
+k_adj_dots(int n, int B, const double* __restrict__ yn, const double* __restrict__ lt,
+           const double* __restrict__ wn, const double* __restrict__ wk, const double* __restrict__ wkm1, int has_km1,
            double* __restrict__ part) {
   constexpr int ROWS = 256 / RB;
   __shared__ double red[256];
@@ -619,7 +621,7 @@ k_adj_dots(int n, int B, const double* __restrict__ yn, const double* __restrict
   if (b < B)
     for (int row = row0; row < 3 * n; row += gridDim.x * ROWS) {
       const size_t o = (size_t)row * B + b;
-      const double y = yn[o], w1 = wn[o], w0 = wk[o];
+      const double y = yn[o] + lt[o], w1 = wn[o], w0 = wk[o];
       const double wm = has_km1 ? wkm1[o] : 0.0;
       s[0] += y * w1;
       s[1] += y * w0;
@@ -637,18 +639,34 @@ k_adj_dots(int n, int B, const double* __restrict__ yn, const double* __restrict
   }
 }
 
-// Per-probe scalars of step k from the dot sums (sums[q * B + b]); updates abar_k and
-// bbar_k in place and writes the coefficients of the element-wise update:
+// Per-probe scalars of step k, one work-group per right-hand side: the five dot sums over the
+// nblk work-groups of k_adj_dots (none at k = m - 1: zeros), in a fixed order, then abar_k and
+// bbar_k in place and the coefficients of the element-wise update:
 //   c[0] ybar_{k+1} + c[1] w_{k+1} = wbar;  lbar = wbar + c[2] w_k;
 //   l_k = w_{k+1} + c[3] w_k + c[4] w_{k-1} (k < m-1) or c[5] Lt (k = m-1);
-//   ybar_k += c[6] wbar + c[7] l_k;  ybar_{k-1} += c[8] wbar;  q = g c[9] w_k.
-__global__ void k_adj_scalars(int B, int nb, int k, int m, int probe0,
-                              const double* __restrict__ sums, const double* __restrict__ a,
-                              const double* __restrict__ nrm, const int* __restrict__ meff,
-                              double* __restrict__ abar, double* __restrict__ bbar,
-                              double* __restrict__ coef) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
+//   ybar_k += c[6] wbar + c[7] l_k;  ybar_{k-1} = c[8] wbar;  q = g c[9] w_k.
+__global__ void __launch_bounds__(256)
+k_adj_scalars(int B, int nb, int k, int m, int probe0, int nblk,
+              const double* __restrict__ part, const double* __restrict__ a,
+              const double* __restrict__ nrm, const int* __restrict__ meff,
+              double* __restrict__ abar, double* __restrict__ bbar, double* __restrict__ coef) {
+  __shared__ double red[5][256];
+  const int b = blockIdx.x;
+  double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < nblk; i += 256)
+#pragma unroll
+    for (int q = 0; q < 5; ++q) s[q] += part[((size_t)i * kPartSlots + q) * B + b];
+#pragma unroll
+  for (int q = 0; q < 5; ++q) red[q][threadIdx.x] = s[q];
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (threadIdx.x < h)
+#pragma unroll
+      for (int q = 0; q < 5; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  const double sums[5] = {red[0][0], red[1][0], red[2][0], red[3][0], red[4][0]};
   double* c = coef + (size_t)b * 16;
   for (int q = 0; q < 16; ++q) c[q] = 0.0;
   if (b >= nb) return;
@@ -660,11 +678,11 @@ __global__ void k_adj_scalars(int B, int nb, int k, int m, int probe0,
   double c0 = 0.0, c1 = 0.0, wy_k = 0.0, wy_km1 = 0.0;
   if (k + 1 < me) {
     const double beta = nrm[l * m + k + 1];
-    const double sa = sums[0 * B + b] / beta;
-    const double sb = sums[1 * B + b] / nk;
-    const double sc = k > 0 ? sums[2 * B + b] / nkm1 : 0.0;
-    const double sd = sums[3 * B + b] / (beta * nk);
-    const double se = k > 0 ? sums[4 * B + b] / (beta * nkm1) : 0.0;
+    const double sa = sums[0] / beta;
+    const double sb = sums[1] / nk;
+    const double sc = k > 0 ? sums[2] / nkm1 : 0.0;
+    const double sd = sums[3] / (beta * nk);
+    const double se = k > 0 ? sums[4] / (beta * nkm1) : 0.0;
     const double al1 = 1.0 / beta;
     const double al2 = bbar[(size_t)b * m + k + 1] - sa / beta;
     c0 = al1;
@@ -693,7 +711,7 @@ __global__ void __launch_bounds__(256)
 k_adj_update(int n, int B, int k, int m, const double* __restrict__ coef,
              const double* __restrict__ wn, const double* __restrict__ wk,
              const double* __restrict__ wkm1, const double* __restrict__ lt,
-             const double* __restrict__ g, double* __restrict__ yn, double* __restrict__ yc,
+             const double* __restrict__ g, const double* __restrict__ yn, double* __restrict__ yc,
              double* __restrict__ yp, double* __restrict__ lbar, double* __restrict__ pd,
              float* __restrict__ pf, double* __restrict__ qd, float* __restrict__ qf,
              int use_float) {
@@ -710,16 +728,18 @@ k_adj_update(int n, int B, int k, int m, const double* __restrict__ coef,
     const size_t o = (size_t)row * B + b;
     const double w0 = wk[o];
     double wbar = 0.0, lk;
+    double y0 = 0.0;
     if (!last) {
       const double w1 = wn[o];
-      wbar = c0 * yn[o] + c1 * w1;
+      wbar = c0 * (yn[o] + lt[o]) + c1 * w1;
       lk = w1 + c3 * w0 + (k > 0 ? c4 * wkm1[o] : 0.0);
+      y0 = yc[o];
     } else {
       lk = c5 * lt[o];
     }
     const double lb = wbar + c2 * w0;
-    yc[o] += c6 * wbar + c7 * lk;
-    if (k > 0) yp[o] += c8 * wbar;
+    yc[o] = y0 + (c6 * wbar + c7 * lk);
+    if (k > 0) yp[o] = c8 * wbar;
     lbar[o] = lb;
     const double gs = g[row / 3];
     if (use_float) {
@@ -730,11 +750,6 @@ k_adj_update(int n, int B, int k, int m, const double* __restrict__ coef,
       qd[o] = gs * c9 * w0;
     }
   }
-}
-
-__global__ void k_axpy_vec(size_t count, const double* __restrict__ x, double* __restrict__ y) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < count) y[t] += x[t];
 }
 
 __global__ void k_fill_double(double* __restrict__ p, double v, size_t count) {
@@ -875,6 +890,10 @@ void launch_tridiag_adjoint(const SysBuffers& b, int nb, int m, int probe0, uint
 
 // One reverse step k: dots, scalars and the element-wise update, which leaves lbar_k in
 // b.lbar, g * lbar_k in b.dv and g * y_k in b.dq for the adjoint matvec and force terms.
+// Three launches; with separate sums, fills and the matvec's accumulation it was eleven (651
+// atoms, 16 right-hand sides: 37 us a step, 16 us now). b.Lt holds the forward sweep's last
+// matvec at k = m - 1, and C lbar_{k+1} after that. No buffer has to start from zero: each
+// one of the three ybar is written before its first read.
 void launch_adjoint_step(const Geometry& geo, const SysBuffers& b, int B, int nb, int k, int m,
                          int probe0, bool use_float, hipStream_t st) {
   const size_t vs = (size_t)geo.n * 3 * B;
@@ -884,33 +903,19 @@ void launch_adjoint_step(const Geometry& geo, const SysBuffers& b, int B, int nb
   double* yn = Y0 + (size_t)((k + 1) % 3) * vs;
   double* yc = Y0 + (size_t)(k % 3) * vs;
   double* yp = Y0 + (size_t)((k + 2) % 3) * vs;
-  // ybar_{k-1} starts from zero (its buffer last held ybar_{k+2})
-  fill_double(yp, 0.0, vs, st);
   const double* wk = b.W + (size_t)k * vs;
   const double* wn = (k + 1 < m) ? b.W + (size_t)(k + 1) * vs : wk;
   const double* wkm1 = k > 0 ? b.W + (size_t)(k - 1) * vs : wk;
   if (k + 1 < m) {
-    MBD_RB_SWITCH(rb, (k_adj_dots<RB><<<grd, 256, 0, st>>>(geo.n, B, yn, wn, wk, wkm1,
+    MBD_RB_SWITCH(rb, (k_adj_dots<RB><<<grd, 256, 0, st>>>(geo.n, B, yn, b.Lt, wn, wk, wkm1,
                                                            k > 0 ? 1 : 0, b.part)));
-    for (int q = 0; q < 5; ++q)
-      k_sum_slot<<<B, 256, 0, st>>>(B, q, (int)grd.x, b.part, b.coef + (size_t)q * B);
-  } else {
-    fill_double(b.coef, 0.0, (size_t)5 * B, st);
   }
-  k_adj_scalars<<<(B + 63) / 64, 64, 0, st>>>(B, nb, k, m, probe0, b.coef, b.a, b.b, b.meff,
-                                              b.abar, b.bbar, b.adj);
+  k_adj_scalars<<<B, 256, 0, st>>>(B, nb, k, m, probe0, k + 1 < m ? (int)grd.x : 0, b.part, b.a,
+                                   b.b, b.meff, b.abar, b.bbar, b.adj);
   MBD_RB_SWITCH(rb, (k_adj_update<RB><<<grd, 256, 0, st>>>(
                          geo.n, B, k, m, b.adj, wn, wk, wkm1, b.Lt, b.g, yn, yc, yp, b.lbar,
                          (double*)b.dv, (float*)b.dv, (double*)b.dq, (float*)b.dq,
                          use_float ? 1 : 0)));
-}
-
-// ybar_k += C lbar_k (the adjoint matvec's output in b.Lt).
-void launch_adjoint_accumulate(const Geometry& geo, const SysBuffers& b, int B, int k,
-                               hipStream_t st) {
-  const size_t vs = (size_t)geo.n * 3 * B;
-  k_axpy_vec<<<(unsigned)((vs + 255) / 256), 256, 0, st>>>(vs, b.Lt,
-                                                          b.ybar + (size_t)(k % 3) * vs);
 }
 
 void launch_forces_finish(const Geometry& geo, const SysBuffers& b, int R, double* forces,

@@ -341,14 +341,60 @@ __device__ __forceinline__ const R* stencil_row(const R* gr, int by, int bz, int
   return gr + ((size_t)k3 * K2 + k2) * XS * BG;
 }
 
+// The rest of one application of C for one atom and right-hand side: from the gathered field
+// of the reciprocal part (in u) to lt = g (E_rec + E_dir + E_self) + om2 w.
+template <typename R>
+struct Epilogue {
+  const R* Ed;        // direct field, ed_parts partial sums
+  int ed_parts;
+  const double* w;    // the vector C is applied to
+  const double* g;
+  const double* om2;
+  uint32_t comps;
+  double self_coef;
+  double* lt;
+};
+
+// One component per sub-lane where there are at least three, else all by the first. Returns
+// this lane's share of w . lt.
+template <typename R, int NS>
+__device__ __forceinline__ double finish_field(const Epilogue<R>& ep, int n, int s, int sub,
+                                               int bg, int B, R e0, R e1, R e2) {
+  double dot = 0.0;
+  const double gs = ep.g[s];
+  const double o2 = ep.om2[s];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (NS >= 4 ? a != sub : sub != 0) continue;
+    const size_t idx = ((size_t)s * 3 + a) * B + bg;
+    const double wv = ep.w[idx];
+    double E = (a == 0) ? (double)e0 : (a == 1) ? (double)e1 : (double)e2;
+    if (ep.comps & MBD_C_DIR) {
+      E += (double)ep.Ed[idx];
+      // the parts in order, five loads in flight (past the last part: a zero)
+      const size_t pstride = (size_t)3 * n * B;
+      for (int q0 = 1; q0 < ep.ed_parts; q0 += 5) {
+        R x[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) x[i] = ep.Ed[min(q0 + i, ep.ed_parts - 1) * pstride + idx];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) E += q0 + i < ep.ed_parts ? (double)x[i] : 0.0;
+      }
+    }
+    if (ep.comps & MBD_C_SELF) E += ep.self_coef * gs * wv;
+    double l = gs * E;
+    if (ep.comps & MBD_C_DIAG) l += o2 * wv;
+    ep.lt[idx] = l;
+    dot += wv * l;
+  }
+  return dot;
+}
+
 template <typename R, int P, int BG, int BL>
 __global__ void __launch_bounds__(512)
 k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __restrict__ th,
                   const R* __restrict__ dth, const R* __restrict__ grid, size_t chunk_elems,
-                  const R* __restrict__ Ed, int ed_parts, const double* __restrict__ w,
-                  const double* __restrict__ g, const double* __restrict__ om2, int B,
-                  uint32_t comps, double self_coef, double* __restrict__ lt,
-                  double* __restrict__ part, int chunk0) {
+                  const Epilogue<R> ep, int B, double* __restrict__ part, int chunk0) {
   constexpr int NS = Lanes<BL>::NS, LA = Lanes<BL>::LA, AW = Lanes<BL>::AW;
   __shared__ double red[8 * BL];
   const int nw = blockDim.x >> 6;  // wavefronts per work-group (4 or 8)
@@ -378,7 +424,7 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
     const int s = AW == 1 ? s0 : min(s0 + lane / LA, x_hi - 1);
     const bool valid = AW == 1 || s0 + lane / LA < x_hi;
     R e0 = R(0), e1 = R(0), e2 = R(0);
-    if (comps & MBD_C_REC) {
+    if (ep.comps & MBD_C_REC) {
       const R* thp = th + s * 3 * P;
       const R* dthp = dth + s * 3 * P;
       R mx[P], dmx[P];
@@ -445,35 +491,8 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
       e1 = (R)geo.Mu[0][1] * g0 + (R)geo.Mu[1][1] * g1 + (R)geo.Mu[2][1] * g2;
       e2 = (R)geo.Mu[0][2] * g0 + (R)geo.Mu[1][2] * g1 + (R)geo.Mu[2][2] * g2;
     }
-    // one component per sub-lane where there are at least three
-    if (valid && sub < 3) {
-      const double gs = g[s];
-      const double o2 = om2[s];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        if (NS >= 4 ? a != sub : sub != 0) continue;
-        const size_t idx = ((size_t)s * 3 + a) * B + bg;
-        const double wv = w[idx];
-        double E = (a == 0) ? (double)e0 : (a == 1) ? (double)e1 : (double)e2;
-        if (comps & MBD_C_DIR) {
-          E += (double)Ed[idx];
-          // the parts in order, five loads in flight (past the last part: a zero)
-          const size_t pstride = (size_t)3 * geo.n * B;
-          for (int q0 = 1; q0 < ed_parts; q0 += 5) {
-            R x[5];
-#pragma unroll
-            for (int i = 0; i < 5; ++i) x[i] = Ed[min(q0 + i, ed_parts - 1) * pstride + idx];
-#pragma unroll
-            for (int i = 0; i < 5; ++i) E += q0 + i < ed_parts ? (double)x[i] : 0.0;
-          }
-        }
-        if (comps & MBD_C_SELF) E += self_coef * gs * wv;
-        double l = gs * E;
-        if (comps & MBD_C_DIAG) l += o2 * wv;
-        lt[idx] = l;
-        dot += wv * l;
-      }
-    }
+    if (valid && sub < 3)
+      dot += finish_field<R, NS>(ep, geo.n, s, sub, bg, B, e0, e1, e2);
   }
   // per-RHS sum over the lanes of a right-hand side, then the work-group's wavefronts
 #pragma unroll
@@ -493,13 +512,17 @@ k_gather_epilogue(const Geometry geo, const int* __restrict__ base, const R* __r
 // the Hessian of the atom's weight product (d^2/du^2 along one axis: ddth; mixed
 // axes: dth dth). One call adds sum_k H_a(k) h_a phi(k) for one grid (phi) and the
 // other dipole set h, summed over the chunk's right-hand sides, to fsum (wavefront
-// per atom, lanes over right-hand sides and stencil rows as in the gather).
-template <typename R, int P, int BG>
+// per atom, lanes over right-hand sides and stencil rows as in the gather). With EPI the
+// grid is also that of the adjoint matvec, whose gather is the same pass over the same rows
+// (its two row sums are the Hessian's first two): one read of the grid instead of two. 12k
+// atoms, 64 right-hand sides: gather 61 us and force 55 before, 64 us together.
+template <typename R, int P, int BG, bool EPI>
 __global__ void __launch_bounds__(512)
 k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restrict__ th,
              const R* __restrict__ dth, const R* __restrict__ ddth, const R* __restrict__ grid,
              size_t chunk_elems, const R* __restrict__ hv, int B, int chunk0,
-             double* __restrict__ fsum, const double* __restrict__ hscale) {
+             double* __restrict__ fsum, const double* __restrict__ hscale,
+             const Epilogue<R> ep) {
   constexpr int NS = Lanes<BG>::NS, LA = Lanes<BG>::LA, AW = Lanes<BG>::AW;
   const int nw = blockDim.x >> 6;  // wavefronts per work-group (4 or 8)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
@@ -537,6 +560,7 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
       kxs[t1] = k1 * BG + b;
     }
     R hxx = R(0), hyy = R(0), hzz = R(0), hxy = R(0), hxz = R(0), hyz = R(0);
+    R e0 = R(0), e1 = R(0), e2 = R(0);
     auto row = [&](const R* line, R my, R dmy, R ddmy, R mz3, R dmz3, R ddmz3) {
       R s0 = R(0), s1 = R(0), s2 = R(0);
 #pragma unroll
@@ -552,6 +576,11 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
       hxy += s1 * dmy * mz3;
       hxz += s1 * my * dmz3;
       hyz += s0 * dmy * dmz3;
+      if constexpr (EPI) {
+        e0 += s1 * my * mz3;
+        e1 += s0 * dmy * mz3;
+        e2 += s0 * my * dmz3;
+      }
     };
     if constexpr (NS == 1) {
       R my[P], dmy[P], ddmy[P];
@@ -581,6 +610,20 @@ k_spme_force(const Geometry geo, const int* __restrict__ base, const R* __restri
             ddp[P + t2], own ? tp[2 * P + t3] : R(0), own ? dp[2 * P + t3] : R(0),
             own ? ddp[2 * P + t3] : R(0));
       }
+    }
+    if constexpr (EPI) {
+#pragma unroll
+      for (int off = BG; off < LA; off <<= 1) {
+        e0 += __shfl_xor(e0, off);
+        e1 += __shfl_xor(e1, off);
+        e2 += __shfl_xor(e2, off);
+      }
+      if (valid && sub < 3)
+        finish_field<R, NS>(
+            ep, geo.n, s, sub, bg, B,
+            (R)geo.Mu[0][0] * e0 + (R)geo.Mu[1][0] * e1 + (R)geo.Mu[2][0] * e2,
+            (R)geo.Mu[0][1] * e0 + (R)geo.Mu[1][1] * e1 + (R)geo.Mu[2][1] * e2,
+            (R)geo.Mu[0][2] * e0 + (R)geo.Mu[1][2] * e1 + (R)geo.Mu[2][2] * e2);
     }
     const size_t o = (size_t)s * 3 * B + bg;
     // h, times a per-right-hand-side factor when the grid belongs to a scaled dipole set
@@ -655,6 +698,13 @@ void launch_spread(const Geometry& geo, const SysBuffers& b, int B, int BG, int 
 }
 
 template <typename R>
+static Epilogue<R> epilogue_of(const Geometry& geo, const SysBuffers& b, const double* w, int B,
+                               uint32_t comps) {
+  return {(const R*)b.Ed, pair_parts(geo, b, B), w, b.g, b.om2, comps,
+          -4.0 * geo.tau * geo.tau * geo.tau / (3.0 * sqrt(M_PI)), b.Lt};
+}
+
+template <typename R>
 void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, int B, int BG,
                      int chunk0, int nchunks, uint32_t comps, hipStream_t st) {
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
@@ -662,11 +712,10 @@ void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, 
   // atoms, chunks of 32: 20 us a launch whole, 11.4 us in slices)
   const bool sliced = geo.n < 4096;
   const dim3 grd(gather_blocks(geo, BG), nchunks * (sliced && BG > 16 ? BG / 16 : 1));
-  const double self_coef = -4.0 * geo.tau * geo.tau * geo.tau / (3.0 * sqrt(M_PI));
+  const Epilogue<R> ep = epilogue_of<R>(geo, b, w, B, comps);
 #define MBD_GATHER(PP, BB, LL)                                                              \
   k_gather_epilogue<R, PP, BB, LL><<<grd, 64 * gather_waves(geo), 0, st>>>(               \
-      geo, b.base, (const R*)b.th, (const R*)b.dth, (const R*)b.grid, chunk,               \
-      (const R*)b.Ed, pair_parts(geo, b, B), w, b.g, b.om2, B, comps, self_coef, b.Lt,     \
+      geo, b.base, (const R*)b.th, (const R*)b.dth, (const R*)b.grid, chunk, ep, B,        \
       b.part, chunk0)
 #define MBD_GATHER_P(BB, LL)                \
   switch (geo.p) {                          \
@@ -687,21 +736,23 @@ void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, 
 #undef MBD_GATHER
 }
 
+// With w, also the gather of the matvec of w over the same grid (into Lt; no dot products).
 template <typename R>
 void launch_spme_force(const Geometry& geo, const SysBuffers& b, const void* h, int B, int BG,
-                       int chunk0, hipStream_t st, const double* hscale) {
+                       int chunk0, hipStream_t st, const double* hscale, const double* w) {
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
   dim3 grd(gather_blocks(geo, BG), 1);
-#define MBD_SF(PP, BB)                                                                      \
-  k_spme_force<R, PP, BB><<<grd, 64 * gather_waves(geo), 0, st>>>(                       \
-      geo, b.base, (const R*)b.th, (const R*)b.dth,                                         \
-                                               (const R*)b.ddth, (const R*)b.grid, chunk,     \
-                                               (const R*)h, B, chunk0, b.fsum, hscale)
-#define MBD_SF_P(BB)                 \
-  switch (geo.p) {                   \
-    case 4: MBD_SF(4, BB); break;    \
-    case 6: MBD_SF(6, BB); break;    \
-    case 8: MBD_SF(8, BB); break;    \
+  const Epilogue<R> ep = epilogue_of<R>(geo, b, w, B, MBD_C_ALL);
+#define MBD_SF(PP, BB, EE)                                                                 \
+  k_spme_force<R, PP, BB, EE><<<grd, 64 * gather_waves(geo), 0, st>>>(                     \
+      geo, b.base, (const R*)b.th, (const R*)b.dth, (const R*)b.ddth, (const R*)b.grid,    \
+      chunk, (const R*)h, B, chunk0, b.fsum, hscale, ep)
+#define MBD_SF_E(PP, BB) if (w) MBD_SF(PP, BB, true); else MBD_SF(PP, BB, false)
+#define MBD_SF_P(BB)                   \
+  switch (geo.p) {                     \
+    case 4: MBD_SF_E(4, BB); break;    \
+    case 6: MBD_SF_E(6, BB); break;    \
+    case 8: MBD_SF_E(8, BB); break;    \
   }
   switch (BG) {
     case 1: MBD_SF_P(1); break;
@@ -712,14 +763,15 @@ void launch_spme_force(const Geometry& geo, const SysBuffers& b, const void* h, 
     case 32: MBD_SF_P(32); break;
     case 64: MBD_SF_P(64); break;
   }
+#undef MBD_SF_E
 #undef MBD_SF_P
 #undef MBD_SF
 }
 
 template void launch_spme_force<float>(const Geometry&, const SysBuffers&, const void*, int, int,
-                                       int, hipStream_t, const double*);
+                                       int, hipStream_t, const double*, const double*);
 template void launch_spme_force<double>(const Geometry&, const SysBuffers&, const void*, int,
-                                        int, int, hipStream_t, const double*);
+                                        int, int, hipStream_t, const double*, const double*);
 
 template void launch_spread<float>(const Geometry&, const SysBuffers&, int, int, int, int,
                                    hipStream_t);
