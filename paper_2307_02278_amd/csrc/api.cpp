@@ -182,9 +182,15 @@ void allocate_system(Plan& plan, System& S, int R_probes, int m) {
   b.Lt = dalloc<double>(plan, vec, by);
   b.dv = dalloc<R>(plan, vec, by);
   // small systems split each group's candidates over several work-groups, until a launch
-  // has about 1024 of them (four wavefronts each: 4 per SIMD)
+  // has about 1024 of them (four wavefronts each: 4 per SIMD), over all systems of a batch
+  // that run side by side. Float parts cost more (a work-group splits the targets into
+  // planes first) and each adds a field that the gather reads, so there are at most 6:
+  // direct sum, force and gather of 651 atoms, 64 right-hand sides, 55 us with 16 parts, 48
+  // with 6; 3000 atoms, 98 us with 5, 113 with 1; six boxes of 525 to 4200 atoms at once,
+  // 36.0 ms a pass with 1024 work-groups each, 33.2 with 256.
   const int ngroups = (n + kGroup - 1) / kGroup;
-  const int parts = std::max(1, std::min(16, 1024 / ngroups));
+  const int side_by_side = std::min<int>(4, (int)plan.sys.size());
+  const int parts = std::max(1, std::min(sizeof(R) == 4 ? 6 : 16, 1024 / side_by_side / ngroups));
   b.ed_parts = B >= 16 ? parts : 1;
   b.fs_parts = parts;
   b.pg_real = (int)sizeof(R);
