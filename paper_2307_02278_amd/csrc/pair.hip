@@ -1066,11 +1066,13 @@ k_pair_force(const Geometry geo, const int2* __restrict__ hdr, const R* __restri
 // and adds their terms (in-range pairs only) to its float64 partial forces; the 16 candidate
 // lanes, then the four wavefronts of the group are summed in a fixed order and the group's
 // forces added to this part's fsum (each group owns its targets: no atomics). 12k atoms,
-// B = 64, beside the grid stages: 447 us a launch with float products, 369 us here.
+// B = 64, beside the grid stages: 447 us a launch with float products, 369 us here. At most
+// 168 registers, so that three work-groups fit on a CU: 752 of them are one round on the
+// GPU's 768 places, not two on 512 (alone: 255 us with two a CU, 195 with three).
 constexpr int kForceChunk = 512;  // candidates per LDS chunk (a multiple of 16)
 inline size_t force_lds(int B) { return (size_t)3 * 3 * kGroup * (2 * B + 8) * 2; }
 
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, 3)
 k_pair_force_split(const Geometry geo, const int2* __restrict__ hdr,
                    const float* __restrict__ Fg, const int* __restrict__ gcount, int cap,
                    const float* __restrict__ pv, const float* __restrict__ qv,
