@@ -46,9 +46,9 @@ def log(*a):
 # chunks); the pair stage's instance depends on the shape (pair_kernel_name).
 STAGE_KERNEL = {
     "spread": "k_spread<float, 6, 4>",
-    "fft_x": "k_fft_x_real<96, true>", "fft_y": "k_fft_reg<96, 1>",
+    "fft_x": "k_fft_x_real<96, true, false>", "fft_y": "k_fft_reg<96, 1>",
     "fft_z_conv": "k_fft_reg<96, 2>", "ifft_y": "k_fft_reg<96, 3>",
-    "ifft_x": "k_fft_x_real<96, false>", "gather": "k_gather_epilogue<float, 6, 64, 64>",
+    "ifft_x": "k_fft_x_real<96, false, false>", "gather": "k_gather_epilogue<float, 6, 64, 64>",
 }
 
 

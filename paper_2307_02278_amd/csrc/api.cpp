@@ -196,6 +196,12 @@ void allocate_system(Plan& plan, System& S, int R_probes, int m) {
   b.pg_real = (int)sizeof(R);
   b.Ed = dalloc<R>(plan, vec * b.ed_parts, by);
   b.grid = dalloc<R>(plan, (size_t)g.K[2] * g.K[1] * (g.K[0] + 2) * B, by);
+  // the transforms by planes work on one chunk at a time (at most 64 right-hand sides)
+  if (sizeof(R) == 4) {
+    int bg = std::min(B, 64);
+    while (bg >= 16 && fft_plane_floats(g, bg) == 0) bg /= 2;
+    if (bg >= 16) b.spec = dalloc<R>(plan, fft_plane_floats(g, bg), by);
+  }
   b.part = dalloc<double>(plan, (size_t)kRedBlocks * kPartSlots * B, by);
   b.coef = dalloc<double>(plan, (size_t)kMaxSteps * B, by);
   b.a = dalloc<double>(plan, (size_t)R_probes * m, by);
@@ -357,6 +363,12 @@ void create_pair_list(Plan& plan, System& S) {
   launch_pair_build<R>(S.geo, b, false, plan.stream);
 }
 
+// Whether the transforms after a tile spread run by planes (the line spread leaves its
+// spectrum in the grid's own layout).
+inline bool fft_by_planes(const System& S) {
+  return S.buf.spec && fft_plane_floats(S.geo, S.BG) > 0;
+}
+
 // Spread of grid chunk c of the dipoles in b.dv, fused with the forward x pass when the
 // system's shape selects the line spread; returns the first transform pass still to run
 // (1 after the fused spread, else 0).
@@ -390,6 +402,7 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
   bq.dv = b.dq;
   // nothing reads ybar_0 (the probes are fixed), so step 0 has force terms only
   const bool adjoint = k > 0;
+  const bool planes = fft_by_planes(S);
   SideStream* sd = nullptr;
   auto pair_work = [&] {
     sd = S.overlap ? fork_side(plan, st) : nullptr;
@@ -406,7 +419,7 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
   for (int c = 0; c < nch; ++c)
     for (int pass = first; pass < 5; ++pass)
       staged(plan, MBD_STAGE_FFT_X + pass,
-             [&] { launch_fft_pass<R>(S.geo, b, plan.B, BG, c, 1, pass, st); });
+             [&] { launch_fft_pass<R>(S.geo, b, plan.B, BG, c, 1, pass, first == 0 && planes, st); });
   if (sd) check(hipStreamWaitEvent(st, sd->pair_done, 0), "side join");
   for (int c = 0; c < nch; ++c) {
     staged(plan, MBD_STAGE_FORCE, [&] {
@@ -424,7 +437,7 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
     const int fq = spread_chunk<R>(plan, S, bq, c, st);
     for (int pass = fq; pass < 5; ++pass)
       staged(plan, MBD_STAGE_FFT_X + pass,
-             [&] { launch_fft_pass<R>(S.geo, bq, plan.B, BG, c, 1, pass, st); });
+             [&] { launch_fft_pass<R>(S.geo, bq, plan.B, BG, c, 1, pass, fq == 0 && planes, st); });
     staged(plan, MBD_STAGE_FORCE,
            [&] { launch_spme_force<R>(S.geo, b, b.dv, plan.B, BG, c, st); });
   }
@@ -461,6 +474,7 @@ void matvec_block(Plan& plan, System& S, const double* w, uint32_t comps,
   const int nch = plan.B / BG;
   // replica method: Omega w + g (sum over images of f T) g w; no Ewald split
   if (S.geo.replica_cut > 0.0) comps &= (MBD_C_DIAG | MBD_C_DIR);
+  const bool planes = fft_by_planes(S);
   SideStream* sd = nullptr;
   auto pair_work = [&] {
     sd = S.overlap ? fork_side(plan, st) : nullptr;
@@ -483,7 +497,7 @@ void matvec_block(Plan& plan, System& S, const double* w, uint32_t comps,
     for (int c = 0; c < nch; ++c)
       for (int pass = first; pass < 5; ++pass)
         staged(plan, MBD_STAGE_FFT_X + pass,
-               [&] { launch_fft_pass<R>(S.geo, bb, plan.B, BG, c, 1, pass, st); });
+               [&] { launch_fft_pass<R>(S.geo, bb, plan.B, BG, c, 1, pass, first == 0 && planes, st); });
   if (sd) join_side(st, sd->side, sd->pair_done);
   for (int c = 0; c < nch; ++c)
     staged(plan, MBD_STAGE_GATHER,

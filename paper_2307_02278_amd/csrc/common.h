@@ -155,6 +155,8 @@ struct SysBuffers {
   void* dv = nullptr;          // Real [n][3][B] generalized dipoles g * w_k
   void* Ed = nullptr;          // Real [ed_parts][n][3][B] direct-space field, in parts
   int ed_parts = 1;            // parts the matrix-core list kernel splits a group's list into
+  void* spec = nullptr;        // Real [K1/2+1][BG][K3][K2] complex: half spectrum of one chunk
+                               // by padded planes (float, small grids; else unset)
   void* grid = nullptr;        // Real [B / BG][K3][K2][K1 + 2][BG]
   double* part = nullptr;      // [kRedBlocks][kPartSlots][B] partial sums
   double* coef = nullptr;      // [B][kMaxSteps] reorthogonalization coefficients
@@ -281,9 +283,10 @@ template <typename R>
 void launch_spread(const Geometry& g, const SysBuffers& b, int B, int BG, int chunk0, int nchunks,
                    hipStream_t st);
 
+size_t fft_plane_floats(const Geometry& g, int BG);
 template <typename R>
 void launch_fft_pass(const Geometry& g, const SysBuffers& b, int B, int BG, int chunk0,
-                     int nchunks, int pass, hipStream_t st);
+                     int nchunks, int pass, bool planes, hipStream_t st);
 // Spread fused with the forward x pass (float, 64-wide chunks, p = 6); false when this
 // case is not compiled (then k_spread and pass 0 run instead).
 bool launch_spread_xline(const Geometry& g, const SysBuffers& b, int B, int BG, int chunk0,

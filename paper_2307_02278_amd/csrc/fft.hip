@@ -411,6 +411,19 @@ __device__ __forceinline__ void st_line(__amdgpu_buffer_rsrc_t r, float v, uint3
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, vbyte, sbyte, 0);
 }
 
+// The same for a complex point.
+__device__ __forceinline__ float2 ld_point(__amdgpu_buffer_rsrc_t r, uint32_t vbyte,
+                                           uint32_t sbyte) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, vbyte, sbyte, 0);
+  return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+}
+__device__ __forceinline__ void st_point(__amdgpu_buffer_rsrc_t r, float re, float im,
+                                         uint32_t vbyte, uint32_t sbyte) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 v = {__float_as_uint(re), __float_as_uint(im)};
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, vbyte, sbyte, 0);
+}
+
 // Gz (the z pass with the convolution only): the influence function with kz innermost,
 // [K2][K1/2 + 1][K3].
 template <int K, int MODE>
@@ -538,6 +551,12 @@ k_fft_reg(float* __restrict__ grid, GridDims gd, const float* __restrict__ Gz) {
   }
 }
 
+// Points from one y-z plane to the next in the layout by planes: an odd number of 256-byte
+// units, so that the planes a wavefront writes at once fall on different memory channels.
+__host__ __device__ inline uint32_t plane_stride(int K2, int K3) {
+  return ((uint32_t)(K2 * K3 + 31) / 32 | 1u) * 32;
+}
+
 // x passes with one lane per column (K even, M = K/2). A real line of K points is packed
 // as M complex points z[n] = x[2n] + i x[2n+1] and transformed with one M-point FFT:
 //   forward:  X[k] = (Z[k] + conj Z[M-k]) / 2 + W_K^k (Z[k] - conj Z[M-k]) / 2i,
@@ -548,28 +567,59 @@ k_fft_reg(float* __restrict__ grid, GridDims gd, const float* __restrict__ Gz) {
 // The imaginary parts of X[0] and X[M] are taken as zero, as in the real part of a full
 // inverse transform. A wavefront covers 64 consecutive columns, so every load and store
 // is one contiguous 256-byte row; no lane exchange is needed.
-template <int K, bool FWD>
+// With PLANES the half spectrum goes to (comes from) spec as one y-z plane per (kx, b),
+// [kx][b][K3][K2] complex, for k_fft_plane. A wavefront then covers 8 right-hand sides x 8
+// consecutive lines: 64-byte runs on the spectrum side, 32-byte runs of the grid.
+template <int K, bool FWD, bool PLANES>
 __global__ void __launch_bounds__(64)
-k_fft_x_real(float* __restrict__ grid, GridDims gd) {
+k_fft_x_real(float* __restrict__ grid, GridDims gd, float2* __restrict__ spec) {
   constexpr int M = K / 2;
   constexpr TwTable<K> T{};
   float* g = grid + (size_t)(blockIdx.y + gd.chunk0) * gd.chunk_elems;
-  const long col = (long)blockIdx.x * 64 + threadIdx.x;
   const int BG = gd.BG;
-  const int b = (int)(col % BG);
-  const long line = col / BG;
-  if (line >= (long)gd.K2 * gd.K3) return;
+  const int lines = gd.K2 * gd.K3;
+  const long col = (long)blockIdx.x * 64 + threadIdx.x;
+  // (each XCD takes a contiguous range of lines, all right-hand sides of 8 lines in a row:
+  // its L2 then completes the 128-byte lines)
+  const int part = BG / 8;
+  const long blk = (long)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int b = PLANES ? (int)(blk % part) * 8 + threadIdx.x % 8 : (int)(col % BG);
+  const long own = PLANES ? blk / part * 8 + threadIdx.x / 8 : col / BG;
+  if (PLANES ? blk / part * 8 >= lines : own >= lines) return;
+  const long line = own < lines ? own : lines - 1;  // past the end: the last line again
   const size_t base = (size_t)line * gd.XS * BG + b;
   const size_t wbase = (size_t)__builtin_amdgcn_readfirstlane((unsigned)(base >> 32)) << 32 |
                        (size_t)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)base);
   float* gw = g + wbase;
   const uint32_t lo = (uint32_t)(base - wbase);
   const uint32_t stride = (uint32_t)BG;
+  // point j of the half spectrum
+  const __amdgpu_buffer_rsrc_t srs = wave_rsrc(reinterpret_cast<float*>(spec));
+  const uint32_t ps = plane_stride(gd.K2, gd.K3);
+  const uint32_t so = ((uint32_t)b * ps + (uint32_t)line) * 8;
+  const uint32_t sstride = (uint32_t)BG * ps * 8;
+  auto put = [&](int j, uint32_t l, float re, float im) {
+    if constexpr (PLANES) {
+      st_point(srs, re, im, so, (uint32_t)j * sstride);
+    } else {
+      at(gw, l + (uint32_t)(2 * j) * stride) = re;
+      at(gw, l + (uint32_t)(2 * j + 1) * stride) = im;
+    }
+  };
   float zr[M], zi[M];
+  if constexpr (PLANES && !FWD) {
 #pragma unroll
-  for (int n = 0; n < M; ++n) {
-    zr[n] = at(gw, lo + (uint32_t)(2 * n) * stride);
-    zi[n] = at(gw, lo + (uint32_t)(2 * n + 1) * stride);
+    for (int n = 0; n < M; ++n) {
+      const float2 v = ld_point(srs, so, (uint32_t)n * sstride);
+      zr[n] = v.x;
+      zi[n] = v.y;
+    }
+  } else {
+#pragma unroll
+    for (int n = 0; n < M; ++n) {
+      zr[n] = at(gw, lo + (uint32_t)(2 * n) * stride);
+      zi[n] = at(gw, lo + (uint32_t)(2 * n + 1) * stride);
+    }
   }
   // an opaque copy of the lane offset for the stores: otherwise the compiler keeps the
   // load addresses live through the transform to reuse them
@@ -577,10 +627,8 @@ k_fft_x_real(float* __restrict__ grid, GridDims gd) {
   if constexpr (FWD) {
     reg_stages<M, 0, true>(zr, zi);
     asm volatile("" : "+v"(lo_st));
-    at(gw, lo_st) = zr[0] + zi[0];
-    at(gw, lo_st + stride) = 0.f;
-    at(gw, lo_st + (uint32_t)(2 * M) * stride) = zr[0] - zi[0];
-    at(gw, lo_st + (uint32_t)(2 * M + 1) * stride) = 0.f;
+    put(0, lo_st, zr[0] + zi[0], 0.f);
+    put(M, lo_st, zr[0] - zi[0], 0.f);
     // bins k and M - k read the same two points, so they are formed together and both
     // points die at once (in plain k order every point stayed live until its mirror bin)
 #pragma unroll
@@ -593,13 +641,14 @@ k_fft_x_real(float* __restrict__ grid, GridDims gd) {
         const float forr = 0.5f * (zi[j] + zi[M - j]), foi = -0.5f * (zr[j] - zr[M - j]);
         // W_K^j = cos - i sin
         const float wr = T.c[j] * forr + T.s[j] * foi, wi = T.c[j] * foi - T.s[j] * forr;
-        at(gw, lo_st + (uint32_t)(2 * j) * stride) = fer + wr;
-        at(gw, lo_st + (uint32_t)(2 * j + 1) * stride) = fei + wi;
+        put(j, lo_st, fer + wr, fei + wi);
       }
     }
   } else {
     // zr, zi hold X[0..M); X[M] is the last complex pair of the half spectrum
-    const float xmr = at(gw, lo + (uint32_t)(2 * M) * stride);
+    float xmr;
+    if constexpr (PLANES) xmr = ld_point(srs, so, (uint32_t)M * sstride).x;
+    else xmr = at(gw, lo + (uint32_t)(2 * M) * stride);
     const float x0r = zr[0];
     zr[0] = x0r + xmr;
     zi[0] = x0r - xmr;
@@ -623,6 +672,15 @@ k_fft_x_real(float* __restrict__ grid, GridDims gd) {
     }
     reg_stages<M, 0, false>(zr, zi);
     asm volatile("" : "+v"(lo_st));
+    if constexpr (PLANES) {
+      const __amdgpu_buffer_rsrc_t rs = wave_rsrc(gw);
+#pragma unroll
+      for (int n = 0; n < M; ++n) {
+        st_line(rs, zr[n], lo_st << 2, ((uint32_t)(2 * n) * stride) << 2);
+        st_line(rs, zi[n], lo_st << 2, ((uint32_t)(2 * n + 1) * stride) << 2);
+      }
+      return;
+    }
 #pragma unroll
     for (int n = 0; n < M; ++n) {
       at(gw, lo_st + (uint32_t)(2 * n) * stride) = zr[n];
@@ -631,13 +689,110 @@ k_fft_x_real(float* __restrict__ grid, GridDims gd) {
   }
 }
 
+// y and z transforms with the convolution, one y-z plane of the half spectrum (fixed kx and
+// right-hand side) at a time in LDS: forward y, forward z, the product with the influence
+// function, inverse z, inverse y, with k_fft_reg's lane pairs and arithmetic. As separate
+// passes over the grid these are three reads and three writes of it; here it is read and
+// written once. K2 = K3 = K; NP planes per work-group so that small planes fill
+// wavefronts; rows are padded by two points, so that a half wavefront's row accesses (16
+// lines x 2) fall into all 64 banks. Only for grids that stay in the L2 caches
+// (fft_plane_floats): there the launches and passes saved count.
+template <int K>
+struct PlaneShape {
+  static constexpr int NP = K >= 64 ? 1 : K >= 44 ? 2 : K >= 32 ? 4 : 8;
+  static constexpr int T = (2 * K * NP + 63) / 64 * 64;
+  static constexpr int PY = K + 2;
+  static constexpr size_t lds = (size_t)NP * K * PY * sizeof(float2);
+  static_assert(lds <= 65536 && 16 % NP == 0, "planes of one work-group");
+};
+
+template <int K>
+__global__ void __launch_bounds__(PlaneShape<K>::T)
+k_fft_plane(float2* __restrict__ spec, const float* __restrict__ Gz, int KX, int BG) {
+  constexpr int H = K / 2, NP = PlaneShape<K>::NP, T = PlaneShape<K>::T, PY = PlaneShape<K>::PY;
+  extern __shared__ unsigned char smem_raw[];
+  float2* pl = reinterpret_cast<float2*>(smem_raw);
+  // each XCD takes a contiguous range of planes: those of one kx share its factors in L2
+  const int item = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  if (item >= KX * BG / NP) return;
+  const uint32_t ps = plane_stride(K, K);
+  spec += (size_t)item * NP * ps;
+  auto at2 = [&](int e) -> float4& {  // points 2 e, 2 e + 1 of the planes
+    return *reinterpret_cast<float4*>(spec + e / (K * H) * ps + 2 * (e % (K * H)));
+  };
+  const int kx = item * NP / BG;
+  constexpr int words = NP * K * H;  // pairs of points
+#pragma unroll 8
+  for (int e = threadIdx.x; e < words; e += T)
+    *reinterpret_cast<float4*>(pl + e / H * PY + 2 * (e % H)) = at2(e);
+  __syncthreads();
+  const int pair = threadIdx.x >> 1, h = threadIdx.x & 1;
+  const bool active = pair < NP * K;  // both lanes of a pair
+  float xr[H], xi[H];
+  float2* row = pl + pair * PY;       // row z of a plane
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < H; ++m) {
+      const float2 v = row[2 * m + h];
+      xr[m] = v.x;
+      xi[m] = v.y;
+    }
+    reg_stages<H, 0, true>(xr, xi);
+    pair_dit<K, true>(xr, xi, h);
+#pragma unroll
+    for (int k = 0; k < H; ++k) row[h * H + k] = make_float2(xr[k], xi[k]);
+  }
+  __syncthreads();
+  if (active) {
+    const int y = pair % K;
+    float2* col = pl + (pair - y) * PY + y;
+#pragma unroll
+    for (int m = 0; m < H; ++m) {
+      const float2 v = col[(2 * m + h) * PY];
+      xr[m] = v.x;
+      xi[m] = v.y;
+    }
+    reg_stages<H, 0, true>(xr, xi);
+    pair_dit<K, true>(xr, xi, h);
+    const float* gl = Gz + ((size_t)y * KX + kx) * K + h * H;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      const float w = gl[k];
+      xr[k] *= w;
+      xi[k] *= w;
+      asm("" : "+v"(xr[k]), "+v"(xi[k]));
+    }
+    pair_dif<K, false>(xr, xi, h);
+    reg_stages<H, 0, false>(xr, xi);
+#pragma unroll
+    for (int k = 0; k < H; ++k) col[(2 * k + h) * PY] = make_float2(xr[k], xi[k]);
+  }
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < H; ++m) {
+      const float2 v = row[2 * m + h];
+      xr[m] = v.x;
+      xi[m] = v.y;
+    }
+    reg_stages<H, 0, false>(xr, xi);
+    pair_dit<K, false>(xr, xi, h);
+#pragma unroll
+    for (int k = 0; k < H; ++k) row[h * H + k] = make_float2(xr[k], xi[k]);
+  }
+  __syncthreads();
+#pragma unroll 8
+  for (int e = threadIdx.x; e < words; e += T)
+    at2(e) = *reinterpret_cast<const float4*>(pl + e / H * PY + 2 * (e % H));
+}
+
 // Spread along whole x-lines fused with the forward real x transform (float, 64
 // right-hand sides per chunk, order P): one wavefront per (y, z) line of one chunk, lane
 // = right-hand side. Each lane keeps its right-hand side's K line points in registers and
 // adds, from every atom whose y-z stencil covers the line (the setup's line lists, in atom
 // order), the atom's P x-points with the weights and in the per-point order of k_spread, so
 // the real line equals k_spread's. The lane then packs the line as K/2 complex points, runs the
-// transform of k_fft_x_real<K, true> in registers and stores the half spectrum: the real
+// transform of k_fft_x_real<K, true, false> in registers and stores the half spectrum: the real
 // grid is never written and the separate x pass is not needed. A line-list entry packs the
 // atom and its stencil offsets along y and z: (s << 8) | (t_y << 4) | t_z.
 template <int K, int P>
@@ -726,7 +881,7 @@ k_spread_xline(float* __restrict__ grid, GridDims gd, const Geometry geo,
     }
   }
   // the lane's real line, packed as K/2 complex points, and the transform of
-  // k_fft_x_real<K, true>
+  // k_fft_x_real<K, true, false>
   float zr[M], zi[M];
 #pragma unroll
   for (int n = 0; n < M; ++n) {
@@ -788,7 +943,8 @@ void launch_pass(int K, R* grid, const GridDims& gd, int nchunks, const R* twc, 
         switch (K) {
 #define MBD_REGX(KK)                                                                    \
           case KK:                                                                      \
-            k_fft_x_real<KK, MODE == kXFwd><<<g1, 64, 0, st>>>((float*)grid, gd);       \
+            k_fft_x_real<KK, MODE == kXFwd, false>                                       \
+                <<<g1, 64, 0, st>>>((float*)grid, gd, nullptr);                         \
             return;
           MBD_REG_SIZES(MBD_REGX)
 #undef MBD_REGX
@@ -823,7 +979,66 @@ void launch_pass(int K, R* grid, const GridDims& gd, int nchunks, const R* twc, 
   }
 }
 
+// Lengths of k_fft_plane.
+#define MBD_PLANE_SIZES(X) \
+  X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) X(60) X(64) X(72)
+
+// The three passes by planes: x to planes (0), y and z (2), x from planes (4); the separate y
+// passes (1, 3) are part of the second.
+void launch_planes(float* grid, float2* spec, const GridDims& gd, const float* Gt, int pass,
+                   hipStream_t st) {
+  if (pass == 0 || pass == 4) {
+    const unsigned blk = (unsigned)((gd.K2 * gd.K3 + 7) / 8 * (gd.BG / 8) + 7) / 8 * 8;
+    switch (gd.K1) {
+#define MBD_XT(KK)                                                                       \
+      case KK:                                                                           \
+        if (pass == 0) k_fft_x_real<KK, true, true><<<blk, 64, 0, st>>>(grid, gd, spec); \
+        else k_fft_x_real<KK, false, true><<<blk, 64, 0, st>>>(grid, gd, spec);         \
+        break;
+      MBD_REG_SIZES(MBD_XT)
+#undef MBD_XT
+      default:
+        break;
+    }
+  } else if (pass == 2) {
+    switch (gd.K2) {
+#define MBD_PLANE(KK)                                                                    \
+      case KK: {                                                                         \
+        const int items = gd.KX * gd.BG / PlaneShape<KK>::NP;                            \
+        k_fft_plane<KK><<<(unsigned)((items + 7) / 8 * 8), PlaneShape<KK>::T,            \
+                          PlaneShape<KK>::lds, st>>>(spec, Gt, gd.KX, gd.BG);            \
+        break;                                                                           \
+      }
+      MBD_PLANE_SIZES(MBD_PLANE)
+#undef MBD_PLANE
+      default:
+        break;
+    }
+  }
+}
+
 }  // namespace
+
+// Floats of the layout by planes for chunks of BG right-hand sides; 0 where the transforms
+// run pass by pass: fewer than 16 right-hand sides, K2 != K3, a length not listed, or a chunk
+// of more than 24 MB. The chunk and its planes then no longer stay in the 32 MB of the L2
+// caches, the x passes, which cannot run in place by planes, fall back to the copy rate, and
+// the three launches lose what they save. Five passes against three, us, without the launch
+// gaps: K = 24, 64 right-hand sides (3.5 MB) 13 and 11, K = 32 (8.4 MB) 26 and 18, K = 40 (16
+// MB) 44 and 35, K = 48 (28 MB) 50 and 49, K = 60 (55 MB) 92 and 95, K = 96 (226 MB) 388 and 443;
+// K = 64, 16 right-hand sides (17 MB) 52 and 35, K = 80 (33 MB) 65 and 65.
+size_t fft_plane_floats(const Geometry& geo, int BG) {
+  if (BG < 16 || geo.K[1] != geo.K[2]) return 0;
+  if ((size_t)4 * BG * geo.K[0] * geo.K[1] * geo.K[2] > 24000000) return 0;
+  switch (geo.K[1]) {
+#define MBD_CASE(KK) \
+    case KK: return (size_t)2 * BG * (geo.K[0] / 2 + 1) * plane_stride(geo.K[1], geo.K[2]);
+    MBD_PLANE_SIZES(MBD_CASE)
+#undef MBD_CASE
+    default:
+      return 0;
+  }
+}
 
 bool fft_supported(int k) {
   switch (k) {
@@ -836,10 +1051,11 @@ bool fft_supported(int k) {
 }
 
 // One pass (0 forward x, 1 forward y, 2 z with convolution, 3 inverse y, 4 inverse x)
-// over every grid chunk.
+// over every grid chunk; with planes (one chunk, b.spec set) the transforms of y and z are
+// all part of pass 2.
 template <typename R>
 void launch_fft_pass(const Geometry& geo, const SysBuffers& b, int B, int BG, int chunk0,
-                     int nchunks, int pass, hipStream_t st) {
+                     int nchunks, int pass, bool planes, hipStream_t st) {
   GridDims gd;
   gd.K1 = geo.K[0];
   gd.K2 = geo.K[1];
@@ -858,6 +1074,12 @@ void launch_fft_pass(const Geometry& geo, const SysBuffers& b, int B, int BG, in
   const R* c2 = tw + geo.K[0] + geo.K[1];
   const R* G = (const R*)b.G;
   const R* Gt = (const R*)b.Gt;
+  if constexpr (sizeof(R) == 4) {
+    if (planes) {
+      launch_planes(grid, (float2*)b.spec, gd, Gt, pass, st);
+      return;
+    }
+  }
   switch (pass) {
     case 0: launch_pass<R, kXFwd>(geo.K[0], grid, gd, nchunks, c0, c0 + Ksum, G, Gt, st); break;
     case 1: launch_pass<R, kYFwd>(geo.K[1], grid, gd, nchunks, c1, c1 + Ksum, G, Gt, st); break;
@@ -899,8 +1121,8 @@ bool launch_spread_xline(const Geometry& geo, const SysBuffers& b, int B, int BG
 }
 
 template void launch_fft_pass<float>(const Geometry&, const SysBuffers&, int, int, int, int, int,
-                                     hipStream_t);
+                                     bool, hipStream_t);
 template void launch_fft_pass<double>(const Geometry&, const SysBuffers&, int, int, int, int, int,
-                                      hipStream_t);
+                                      bool, hipStream_t);
 
 }  // namespace mbd
