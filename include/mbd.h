@@ -84,7 +84,8 @@ typedef struct {
  * unchanged; grid_chunk changes the summation order inside the spread and the gather,
  * gather_waves the grouping of the partial sums of a_k, and pair_mode (with pair_subsets
  * under it) the order of the direct-space sums, so results agree to rounding across
- * those. A plan is bitwise reproducible for its shape. */
+ * those. A plan is bitwise reproducible for its shape, and a system's results for its shape
+ * (and probes) are the same bits whatever other systems the plan holds. */
 typedef struct {
   int32_t pair_wg_per_cu; /* work-groups per compute unit of the direct-space list kernel;
                              0 => one work-group per 16-atom target group (all resident)  */
