@@ -182,18 +182,19 @@ void allocate_system(Plan& plan, System& S, int R_probes, int m) {
   b.Lt = dalloc<double>(plan, vec, by);
   b.dv = dalloc<R>(plan, vec, by);
   // small systems split each group's candidates over several work-groups, until a launch
-  // has about 1024 of them in float64 and 512 in float (four wavefronts each). Float parts
-  // cost more (a work-group splits the targets into planes first) and each adds a field that
-  // the gather reads, so there are at most 6. The rule sees this system alone, not how many
-  // run beside it: the parts decide the order of the sums, and a system's bits do not depend
-  // on the rest of its plan. Work-groups aimed at, 256 / 512 / 1024, us: C v of 3000 atoms,
-  // float64, 16 right-hand sides, 139 / 129 / 125; float, 64 right-hand sides, 137 / 136 /
-  // 144; energy of four boxes of 3000 at once, float, 64, 15 steps, 7427 / 7428 / 7645; six
-  // boxes of 525 to 4200 atoms, energy and forces, 40.9 / 40.1 / 40.9 ms. Float parts at 651
-  // atoms, 64 right-hand sides (direct sum, force and gather): 55 us with 16, 48 with 6.
+  // has about 1024 of them (four wavefronts each), 512 for float blocks of 64 and more, whose
+  // work-groups split the targets into planes first. Each part adds a field that the gather
+  // reads: in float there are at most 6. The rule sees this system alone, not how many run
+  // beside it: the parts decide the order of the sums, and a system's bits do not depend on
+  // the rest of its plan. Work-groups aimed at, 256 / 512 / 1024, us: C v of 3000 atoms,
+  // float64, 16 right-hand sides, 139 / 129 / 125; float, 16 right-hand sides, 78 at 512 and
+  // 74 at 1024; float, 64 right-hand sides, 137 / 136 / 144; energy of four boxes of 3000 at
+  // once, float, 64, 15 steps, 7427 / 7428 / 7645; six boxes of 525 to 4200 atoms, energy and
+  // forces, 40.9 / 40.1 / 40.9 ms. Float parts at 651 atoms, 64 right-hand sides (direct sum,
+  // force and gather): 55 us with 16, 48 with 6.
   const int ngroups = (n + kGroup - 1) / kGroup;
-  const int parts = std::max(1, sizeof(R) == 4 ? std::min(6, 512 / ngroups)
-                                               : std::min(16, 1024 / ngroups));
+  const int aim = sizeof(R) == 4 && B >= 64 ? 512 : 1024;
+  const int parts = std::max(1, std::min(sizeof(R) == 4 ? 6 : 16, aim / ngroups));
   b.ed_parts = B >= 16 ? parts : 1;
   b.fs_parts = parts;
   b.pg_real = (int)sizeof(R);
