@@ -559,6 +559,77 @@ k_pair_list(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
   }  // groups of this work-group
 }
 
+// The dense products below give every target of a group 0 x d of the candidates out of its
+// range: not a number where d is not finite. The bfloat16 planes of k_pair_split besides turn
+// floats above the largest bfloat16 into infinities, and below 2^-110 the last plane falls
+// under the smallest bfloat16 (2^-133). Where an element of a column's field is not finite
+// or, from planes, smaller than 2^-96 (more than 2^24 times what the planes can lose of
+// it), the work-group sums that column again over the pairs in range alone, in the list's
+// type, as the vector kernel does. Columns of ordinary values keep their bits; testing
+// them costs an LDS flag and two barriers a group.
+template <typename R, bool PLANES>
+__device__ __forceinline__ bool out_of_bounds(R v) {
+  const R a = fabs(v);
+  const R huge = sizeof(R) == 4 ? (R)3.4028235e38f : (R)1.7976931348623157e308;
+  return !(a <= huge) || (PLANES && a < (R)0x1p-96f && a > R(0));
+}
+
+// Columns of a work-group whose field is to be summed again.
+template <int W>
+struct Redo {
+  unsigned bits[(W + 31) / 32];
+  int any;
+  __device__ __forceinline__ void clear() {
+    if (threadIdx.x < (W + 31) / 32) bits[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) any = 0;
+  }
+  // bit t of odd: the lane's column first + step * ST (t / ST) + t % ST
+  __device__ __forceinline__ void mark(unsigned odd, int first, int step, int ST) {
+    any = 1;
+    for (; odd; odd &= odd - 1u) {
+      const int t = __ffs(odd) - 1;
+      const int column = first + step * ST * (t / ST) + t % ST;
+      atomicOr(&bits[column >> 5], 1u << (column & 31));
+    }
+  }
+  __device__ __forceinline__ bool marked(int column) const {
+    return (bits[column >> 5] >> (column & 31)) & 1u;
+  }
+};
+
+// The marked columns (of W, at dv and Ed) of one group over its candidates [lo, hi).
+template <typename R, int W>
+__device__ __forceinline__ void sum_in_range(const Geometry& geo, const Redo<W>& redo, int group,
+                                             const int2* H, const R* T, int lo, int hi,
+                                             const R* dv, R* Ed, size_t Bs) {
+  // (opaque, so that nothing of this is kept in registers across the products)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int c = tid % W;
+  if (!redo.marked(c)) return;
+#pragma unroll 1
+  for (int t = tid / W; t < kGroup; t += 256 / W) {
+    const int i = group * kGroup + t;
+    if (i >= geo.n) break;
+    R e0 = R(0), e1 = R(0), e2 = R(0);
+#pragma unroll 1
+    for (int k = lo; k < hi; ++k) {
+      const int2 h = H[k];
+      if (!(((uint32_t)h.y >> t) & 1u)) continue;
+      const R* q = T + ((size_t)k * kGroup + t) * kTensorWords;
+      const R* d = dv + (size_t)h.x * 3 * Bs + c;
+      const R d0 = d[0], d1 = d[Bs], d2 = d[2 * Bs];
+      e0 = fma(q[4], d2, fma(q[3], d1, fma(q[0], d0, e0)));
+      e1 = fma(q[5], d2, fma(q[1], d1, fma(q[3], d0, e1)));
+      e2 = fma(q[2], d2, fma(q[5], d1, fma(q[4], d0, e2)));
+    }
+    R* o = Ed + (size_t)i * 3 * Bs + c;
+    o[0] = e0;
+    o[Bs] = e1;
+    o[2 * Bs] = e2;
+  }
+}
+
 // E_dir of a group on the matrix cores. For the group's 16 targets t the field is one
 // dense product over k = 3 c + b (candidate c, component b):
 //   E[t][a][rhs] = sum_k T_(c,t)[a][b] d_(j(c))[b][rhs],
@@ -597,6 +668,7 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
   // for the work-group's NN x NK wavefronts (NN column wavefronts)
   __shared__ R red[NK > 1 ? NN * NK * NT * 256 : 1];
   __shared__ int jl[kMfmaChunk];
+  __shared__ Redo<16 * NT * NN> redo;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wk = wave % NK, wn = wave / NK;
@@ -688,10 +760,14 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
         }
       }
     }
+    redo.clear();
+    unsigned odd = 0u;  // column tiles with a value out of bounds
     // component a of the lane's NT right-hand sides for the target of register r
     auto store = [&](int a, int r, const R (&v)[NT]) {
       const int i = group * kGroup + Mma<R>::row(row, r);
       if (i >= geo.n) return;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) odd |= (unsigned)out_of_bounds<R, false>(v[t]) << t;
       Pack<R, VN>* o = reinterpret_cast<Pack<R, VN>*>(Ed + ((size_t)i * 3 + a) * Bs + rhs);
 #pragma unroll
       for (int q = 0; q < NT / VN; ++q) {
@@ -739,6 +815,11 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
         }
       }
     }
+    __syncthreads();
+    if (odd) redo.mark(odd, rhs, 1, NT);
+    __syncthreads();
+    if (redo.any) sum_in_range<R, 16 * NT * NN>(geo, redo, group, H, T, clo, cnt, dv, Ed, Bs);
+    __syncthreads();  // the marks have been read
   }  // groups of this work-group
 }
 
@@ -748,7 +829,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // x = h + m + l in bfloat16, each the rounded remainder of the ones before: 8 bits each with
-// signs, so the 24 bits of a float, over the whole range of its exponents.
+// signs, so the 24 bits of a float between 2^-110 and the largest bfloat16 (3.39e38).
 struct Split8 {
   bf16x8 h, m, l;
 };
@@ -796,6 +877,7 @@ k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __re
   constexpr int NQ = NT / ST;  // column steps of ST tiles
   __shared__ float red[4 * NT * 256];
   __shared__ int jl[kMfmaChunk];
+  __shared__ Redo<16 * NT> redo;
   const int lane = threadIdx.x & 63;
   const int wk = threadIdx.x >> 6;
   const int col = lane & 15, row = lane >> 4;
@@ -896,6 +978,8 @@ k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __re
         }
       }
     }
+    redo.clear();
+    unsigned odd = 0u;  // column tiles with a value out of bounds
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       __syncthreads();  // the previous round's partials have been read
@@ -917,12 +1001,18 @@ k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __re
 #pragma unroll
             for (int k = 1; k < 4; ++k) v += red[((k * NT + t) * 4 + wk) * 64 + lane];
             w.v[u] = v;
+            odd |= (unsigned)out_of_bounds<float, true>(v) << t;
           }
           *reinterpret_cast<Pack<float, ST>*>(Ed + ((size_t)i * 3 + a) * Bs + 16 * ST * q +
                                               ST * col) = w;
         }
       }
     }
+    if (odd) redo.mark(odd, ST * col, 16, ST);
+    __syncthreads();
+    if (redo.any)
+      sum_in_range<float, 16 * NT>(geo, redo, group, H, T, clo, cnt, dv + rhs0, Ed, Bs);
+    __syncthreads();  // the marks have been read
   }
 }
 
