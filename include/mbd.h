@@ -87,8 +87,10 @@ typedef struct {
  * those. A plan is bitwise reproducible for its shape, and a system's results for its shape
  * (and probes) are the same bits whatever other systems the plan holds. */
 typedef struct {
-  int32_t pair_wg_per_cu; /* work-groups per compute unit of the direct-space list kernel;
-                             0 => one work-group per 16-atom target group (all resident)  */
+  int32_t pair_wg_per_cu; /* work-groups per compute unit of the direct-space list kernel,
+                             all parts of a group and slices of right-hand sides counted;
+                             0 => every work-group of every 16-atom target group
+                             resident. Blocks of 8 and less have no such kernel           */
   int32_t pair_subsets;   /* vector list kernel: target subsets per wavefront, 1, 2 or 4
                              (at least 64 / block); 0 => the size rule (4096 wavefronts
                              or more). The matrix-core kernels, whose work-groups are

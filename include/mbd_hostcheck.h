@@ -55,6 +55,11 @@ void mbdh_gauss_legendre(int32_t n, double* x, double* w);
  * sigma_ij^2 = sig2, damping radius S = beta (R_i + R_j) and steepness d. */
 void mbdh_scs_kernel(double r2, double sig2, double S, double d, double* A, double* B);
 
+/* gridDim.x of a direct-space list kernel over ngroups target groups, each split into parts
+ * candidate ranges and slices of right-hand sides, with at most cap work-groups in all
+ * (0: no cap). */
+int32_t mbdh_pair_grid(int32_t ngroups, int32_t parts, int32_t slices, int32_t cap);
+
 #ifdef __cplusplus
 }
 #endif

@@ -153,6 +153,7 @@ HOSTCHECK_SIGNATURES = [
     ("mbdh_gauss_legendre", None, [C.c_int32, C.POINTER(C.c_double), C.POINTER(C.c_double)]),
     ("mbdh_scs_kernel", None, [C.c_double, C.c_double, C.c_double, C.c_double,
                                C.POINTER(C.c_double), C.POINTER(C.c_double)]),
+    ("mbdh_pair_grid", C.c_int32, [C.c_int32] * 4),
 ]
 
 _lib = None

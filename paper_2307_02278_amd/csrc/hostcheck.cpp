@@ -3,6 +3,7 @@
 
 #include <vector>
 
+#include "launch_rules.h"
 #include "mbd_math.h"
 
 extern "C" {
@@ -66,6 +67,10 @@ void mbdh_gauss_legendre(int32_t n, double* x, double* w) { mbd::gauss_legendre(
 
 void mbdh_scs_kernel(double r2, double sig2, double S, double d, double* A, double* B) {
   mbd::scs_kernel(r2, sig2, S, d, *A, *B);
+}
+
+int32_t mbdh_pair_grid(int32_t ngroups, int32_t parts, int32_t slices, int32_t cap) {
+  return mbd::pair_grid_x(ngroups, parts, slices, cap);
 }
 
 }  // extern "C"

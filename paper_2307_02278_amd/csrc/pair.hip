@@ -26,6 +26,7 @@
 
 #include "cells.h"
 #include "common.h"
+#include "launch_rules.h"
 #include "mbd_math.h"
 #include "mfma.h"
 
@@ -1462,14 +1463,6 @@ int pair_subsets(const Geometry& g, int ngroups, int B) {
   return ns;
 }
 
-// Work-groups of a list-kernel launch: one per group (rounded up to a multiple of 8),
-// or g.pair_blocks when that is set and smaller (multiple of 8: each XCD gets the same
-// number of work-groups).
-int pair_blocks(const Geometry& g, int ngroups) {
-  const int all = (ngroups + 7) / 8 * 8;
-  return g.pair_blocks > 0 ? std::min(all, std::max(8, g.pair_blocks / 8 * 8)) : all;
-}
-
 template <typename R>
 void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) {
   const R* loc = (const R*)b.loc;
@@ -1496,13 +1489,11 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
 #undef MBD_NB
     return;
   }
-  // a multiple of 8 work-groups, so that the XCD remap covers every group
   const int ngroups = (g.n + kGroup - 1) / kGroup;
-  const int nblk = pair_blocks(g, ngroups);
   const int2* H = b.pg_hdr;
   const R* T = (const R*)b.pg_T;
   const int nparts = pair_parts(g, b, B);
-  const dim3 grd(nparts > 1 ? (ngroups + 7) / 8 * 8 : nblk, nparts);
+  const dim3 grd(pair_grid_x(ngroups, nparts, 1, g.pair_blocks), nparts);
 #define MBD_PM(NK, NT, NN)                                                                   \
   k_pair_mfma<R, NK, NT, NN><<<grd, 64 * nn * nk, 0, st>>>(g, H, T, (const R*)b.pg_zero,    \
                                                           b.pg_count, b.pg_cap, dv, Ed, B)
@@ -1529,18 +1520,21 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
     }
     // 128 right-hand sides per wavefront, 64 when B = 64 or with pair_mode 2
     if (g.pair_mode == 1 || g.pair_mode == 2) {
-      if (g.pair_mode == 1 && B % 128 == 0)
-        k_pair_split<8, 2><<<dim3(grd.x, nparts, B / 128), 256, 0, st>>>(
-            g, H, (const float*)T, b.pg_count, b.pg_cap, (const float*)dv, (float*)Ed, B);
+      const bool wide = g.pair_mode == 1 && B % 128 == 0;
+      const int slices = B / (wide ? 128 : 64);
+      const dim3 sliced(pair_grid_x(ngroups, nparts, slices, g.pair_blocks), nparts, slices);
+      if (wide)
+        k_pair_split<8, 2><<<sliced, 256, 0, st>>>(g, H, (const float*)T, b.pg_count, b.pg_cap,
+                                                   (const float*)dv, (float*)Ed, B);
       else
-        k_pair_split<4, 4><<<dim3(grd.x, nparts, B / 64), 256, 0, st>>>(
-            g, H, (const float*)T, b.pg_count, b.pg_cap, (const float*)dv, (float*)Ed, B);
+        k_pair_split<4, 4><<<sliced, 256, 0, st>>>(g, H, (const float*)T, b.pg_count, b.pg_cap,
+                                                   (const float*)dv, (float*)Ed, B);
       return;
     }
 #undef MBD_PM
     const int ns = pair_subsets(g, ngroups, B);
 #define MBD_PL(NS, WP) \
-  k_pair_list<R, NS, WP><<<nblk, 64 * WP, 0, st>>>(g, H, T, b.pg_count, b.pg_cap, dv, Ed, B)
+  k_pair_list<R, NS, WP><<<grd.x, 64 * WP, 0, st>>>(g, H, T, b.pg_count, b.pg_cap, dv, Ed, B)
     switch (B * 16 + ns) {
       case 64 * 16 + 1: MBD_PL(1, 1); break;
       case 64 * 16 + 2: MBD_PL(2, 2); break;
