@@ -76,7 +76,10 @@ T* dalloc(Plan& plan, size_t count, size_t& bytes) {
   void* p = nullptr;
   const size_t nb = std::max<size_t>(count, 1) * sizeof(T);
   hipError_t e = hipMalloc(&p, nb);
-  if (e != hipSuccess) throw std::bad_alloc();
+  if (e != hipSuccess) {
+    (void)hipGetLastError();  // reported here, not by the next launch's check
+    throw std::bad_alloc();
+  }
   plan.allocations.push_back(p);
   bytes += nb;
   return static_cast<T*>(p);
@@ -208,6 +211,7 @@ void allocate_system(Plan& plan, System& S, int R_probes, int m) {
   }
   b.part = dalloc<double>(plan, (size_t)kRedBlocks * kPartSlots * B, by);
   b.coef = dalloc<double>(plan, (size_t)kMaxSteps * B, by);
+  if (B < 16 && g.replica_cut <= 0.0) b.nb_count = dalloc<int>(plan, (size_t)n + 1, by);
   b.a = dalloc<double>(plan, (size_t)R_probes * m, by);
   b.b = dalloc<double>(plan, (size_t)R_probes * m, by);
   b.meff = dalloc<int>(plan, R_probes, by);
@@ -307,17 +311,18 @@ void run_setup(Plan& plan, System& S, const double* pos) {
   });
 }
 
-// Largest neighbour list kept for one system; beyond it (or when its allocation fails) the
-// pairs of a narrow block are summed on the fly, as they are for any target whose count
-// outgrows the list at later positions.
+// Largest neighbour list kept for one system.
 constexpr size_t kMaxNbrBytes = (size_t)4 << 30;
 
 // Size and build the neighbour list of a narrow block (B <= 8) for the positions set up
 // last: a counting pass, then a capacity of 1.25 x the largest count plus 16, then the build.
+// The list is optional: without it the pairs are summed on the fly, as they are for any
+// target whose count outgrows it at later positions. So it is made after everything that the
+// plan's systems cannot do without, and only where it leaves as much device memory free as
+// it takes.
 template <typename R>
 void create_nbr_list(Plan& plan, System& S) {
   SysBuffers& b = S.buf;
-  b.nb_count = dalloc<int>(plan, (size_t)S.geo.n + 1, S.bytes);
   int* mx_d = b.nb_count + S.geo.n;
   fill_int(mx_d, 0, 1, plan.stream);
   launch_nbr_build<R>(S.geo, b, mx_d, plan.stream);
@@ -327,7 +332,13 @@ void create_nbr_list(Plan& plan, System& S) {
   check(hipMemcpy(&mx, mx_d, sizeof(int), hipMemcpyDeviceToHost), "neighbour count");
   const size_t cap = (size_t)mx + mx / 4 + 16;
   const size_t ents = cap * (size_t)S.geo.n;
-  if (ents * (sizeof(int2) + 2 * sizeof(R)) > kMaxNbrBytes) return;
+  const size_t bytes = ents * (sizeof(int2) + 2 * sizeof(R));
+  size_t free_bytes = 0, total_bytes = 0;
+  if (bytes > kMaxNbrBytes || hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess ||
+      free_bytes / 2 < bytes) {
+    (void)hipGetLastError();
+    return;
+  }
   void *h = nullptr, *t = nullptr;
   if (hipMalloc(&h, ents * sizeof(int2)) != hipSuccess ||
       hipMalloc(&t, ents * 2 * sizeof(R)) != hipSuccess) {
@@ -337,7 +348,7 @@ void create_nbr_list(Plan& plan, System& S) {
   }
   plan.allocations.push_back(h);
   plan.allocations.push_back(t);
-  S.bytes += ents * (sizeof(int2) + 2 * sizeof(R));
+  S.bytes += bytes;
   b.nb_cap = (int)cap;
   b.nb_hdr = static_cast<int2*>(h);
   b.nb_ab = t;
@@ -1148,15 +1159,31 @@ mbd_status mbd_plan_create(mbd_plan* out, const mbd_system* systems, int32_t n_s
         allocate_system<double>(plan, S, prm.n_probes, prm.n_steps);
         run_setup<double>(plan, S, sy.pos);
         if (plan.B >= 16 || plan.forces) create_pair_list<double>(plan, S);
-        if (plan.B < 16 && g.replica_cut <= 0.0) create_nbr_list<double>(plan, S);
       } else {
         allocate_system<float>(plan, S, prm.n_probes, prm.n_steps);
         run_setup<float>(plan, S, sy.pos);
         if (plan.B >= 16 || plan.forces) create_pair_list<float>(plan, S);
-        if (plan.B < 16 && g.replica_cut <= 0.0) create_nbr_list<float>(plan, S);
       }
       check(hipGetLastError(), "setup launch");
-      // launch shape: built in, given, cached or measured on this system
+    }
+    if (plan.use_graph) {
+      size_t nat = 0, gb = 0;
+      for (const auto& S : plan.sys) nat += (size_t)S.geo.n;
+      plan.e_out = dalloc<double>(plan, n_sys, gb);
+      plan.sd_out = dalloc<double>(plan, n_sys, gb);
+      if (plan.forces) plan.f_out = dalloc<double>(plan, 3 * nat, gb);
+    }
+    // everything the plan needs is allocated: now the lists it can do without
+    for (System& S : plan.sys) {
+      if (!S.buf.nb_count) continue;
+      if (plan.prec == MBD_PREC_FP64) create_nbr_list<double>(plan, S);
+      else create_nbr_list<float>(plan, S);
+      check(hipGetLastError(), "neighbour list");
+    }
+    // launch shapes: built in, given, cached or measured on each system
+    for (int s = 0; s < n_sys; ++s) {
+      System& S = plan.sys[s];
+      const Geometry& g = S.geo;
       if (prm.tune == MBD_TUNE_GIVEN) {
         apply_shape(plan, S, prm.shape);
         S.shape_source = MBD_SHAPE_GIVEN;
@@ -1183,11 +1210,6 @@ mbd_status mbd_plan_create(mbd_plan* out, const mbd_system* systems, int32_t n_s
       add_side(plan, plan.gstream);
       check(hipEventCreateWithFlags(&plan.g_in, hipEventDisableTiming), "event create");
       check(hipEventCreateWithFlags(&plan.g_out, hipEventDisableTiming), "event create");
-      size_t nat = 0, gb = 0;
-      for (const auto& S : plan.sys) nat += (size_t)S.geo.n;
-      plan.e_out = dalloc<double>(plan, n_sys, gb);
-      plan.sd_out = dalloc<double>(plan, n_sys, gb);
-      if (plan.forces) plan.f_out = dalloc<double>(plan, 3 * nat, gb);
     }
     if (n_sys > 1) {
       // Longest-processing-time assignment of systems to up to 4 streams; the cost of
