@@ -341,13 +341,17 @@ enum {
   MBD_STAGE_SPREAD = 1,    /* B-spline spreading of the dipoles               */
   MBD_STAGE_FFT_X = 2,     /* forward real-to-complex transform along x       */
   MBD_STAGE_FFT_Y = 3,     /* forward transform along y                       */
-  MBD_STAGE_FFT_Z = 4,     /* transform along z, convolution, inverse along z */
+  MBD_STAGE_FFT_Z = 4,     /* transform along z, convolution, inverse along z;
+                              small float grids with K2 = K3 run the y transforms in
+                              the same launch, and count it here alone          */
   MBD_STAGE_IFFT_Y = 5,    /* inverse transform along y                       */
   MBD_STAGE_IFFT_X = 6,    /* inverse complex-to-real transform along x       */
-  MBD_STAGE_GATHER = 7,    /* derivative gather + epilogue (l = Omega w + g E*) */
+  MBD_STAGE_GATHER = 7,    /* derivative gather + epilogue (l = Omega w + g E*) of the
+                              forward matvecs                                   */
   MBD_STAGE_LANCZOS = 8,   /* recurrence update, reductions, quadrature        */
   MBD_STAGE_SETUP = 9,     /* position-dependent setup                         */
-  MBD_STAGE_FORCE = 10,    /* pair and reciprocal bilinear force terms         */
+  MBD_STAGE_FORCE = 10,    /* pair and reciprocal bilinear force terms; the reciprocal
+                              one also gathers the adjoint matvec               */
   MBD_STAGE_ADJOINT = 11,  /* tridiagonal adjoint and reverse-sweep vector work */
   MBD_N_STAGES = 12
 };

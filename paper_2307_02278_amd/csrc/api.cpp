@@ -399,6 +399,18 @@ int spread_chunk(Plan& plan, System& S, const SysBuffers& b, int c, hipStream_t 
   return first;
 }
 
+// The transforms of grid chunk c from pass `first` on (the result of its spread), each pass
+// timed as the launch that it is: by planes passes 1 and 3 are part of pass 2.
+template <typename R>
+void transform_chunk(Plan& plan, System& S, const SysBuffers& b, int c, int first,
+                     hipStream_t st) {
+  const bool planes = first == 0 && fft_by_planes(S);
+  for (int pass = first; pass < 5; ++pass)
+    if (!planes || pass % 2 == 0)
+      staged(plan, MBD_STAGE_FFT_X + pass,
+             [&] { launch_fft_pass<R>(S.geo, b, plan.B, S.BG, c, 1, pass, planes, st); });
+}
+
 // The adjoint matvec C lbar_k (into Lt) together with the bilinear force terms
 // lbar_k^T dC/dR y_k of one reverse step: the pair part, then per grid chunk the
 // reciprocal part with phi of p = g lbar_k (the matvec's own, gathered in the same pass) and
@@ -417,7 +429,6 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
   bq.dv = b.dq;
   // nothing reads ybar_0 (the probes are fixed), so step 0 has force terms only
   const bool adjoint = k > 0;
-  const bool planes = fft_by_planes(S);
   SideStream* sd = nullptr;
   auto pair_work = [&] {
     sd = S.overlap ? fork_side(plan, st) : nullptr;
@@ -431,10 +442,7 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
   int first = 0;
   for (int c = 0; c < nch; ++c) first = spread_chunk<R>(plan, S, b, c, st);
   if (S.overlap == 2) pair_work();
-  for (int c = 0; c < nch; ++c)
-    for (int pass = first; pass < 5; ++pass)
-      staged(plan, MBD_STAGE_FFT_X + pass,
-             [&] { launch_fft_pass<R>(S.geo, b, plan.B, BG, c, 1, pass, first == 0 && planes, st); });
+  for (int c = 0; c < nch; ++c) transform_chunk<R>(plan, S, b, c, first, st);
   if (sd) check(hipStreamWaitEvent(st, sd->pair_done, 0), "side join");
   for (int c = 0; c < nch; ++c) {
     staged(plan, MBD_STAGE_FORCE, [&] {
@@ -450,9 +458,7 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
       continue;
     }
     const int fq = spread_chunk<R>(plan, S, bq, c, st);
-    for (int pass = fq; pass < 5; ++pass)
-      staged(plan, MBD_STAGE_FFT_X + pass,
-             [&] { launch_fft_pass<R>(S.geo, bq, plan.B, BG, c, 1, pass, fq == 0 && planes, st); });
+    transform_chunk<R>(plan, S, bq, c, fq, st);
     staged(plan, MBD_STAGE_FORCE,
            [&] { launch_spme_force<R>(S.geo, b, b.dv, plan.B, BG, c, st); });
   }
@@ -489,7 +495,6 @@ void matvec_block(Plan& plan, System& S, const double* w, uint32_t comps,
   const int nch = plan.B / BG;
   // replica method: Omega w + g (sum over images of f T) g w; no Ewald split
   if (S.geo.replica_cut > 0.0) comps &= (MBD_C_DIAG | MBD_C_DIR);
-  const bool planes = fft_by_planes(S);
   SideStream* sd = nullptr;
   auto pair_work = [&] {
     sd = S.overlap ? fork_side(plan, st) : nullptr;
@@ -509,10 +514,7 @@ void matvec_block(Plan& plan, System& S, const double* w, uint32_t comps,
     for (int c = 0; c < nch; ++c) first = spread_chunk<R>(plan, S, bb, c, st);
   if ((comps & MBD_C_DIR) && S.overlap == 2 && rec) pair_work();
   if (rec)
-    for (int c = 0; c < nch; ++c)
-      for (int pass = first; pass < 5; ++pass)
-        staged(plan, MBD_STAGE_FFT_X + pass,
-               [&] { launch_fft_pass<R>(S.geo, bb, plan.B, BG, c, 1, pass, first == 0 && planes, st); });
+    for (int c = 0; c < nch; ++c) transform_chunk<R>(plan, S, bb, c, first, st);
   if (sd) join_side(st, sd->side, sd->pair_done);
   for (int c = 0; c < nch; ++c)
     staged(plan, MBD_STAGE_GATHER,
