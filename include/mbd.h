@@ -176,8 +176,10 @@ typedef struct {
   mbd_shape shape;      /* the shape for MBD_TUNE_GIVEN (ignored otherwise)               */
   const char* tune_cache;/* MBD_TUNE_MEASURE: path of a JSON-lines file of measured shapes,
                            one object per line keyed by device architecture, N, grid,
-                           block, precision and forces; read at plan creation and
-                           appended with each new measurement. NULL => no file.         */
+                           block, precision and forces, for one direct cutoff and one
+                           generation of the library's kernels (other lines are left
+                           alone); read at plan creation and appended with each new
+                           measurement. NULL => no file.                                */
   int32_t store_grids;  /* with want_forces: 1 => keep the real potential grids of every
                            forward Lanczos step of a probe block (n_steps x the grid
                            bytes, e.g. 22.7 GB at N = 24k, K = 96, block 128), so that the

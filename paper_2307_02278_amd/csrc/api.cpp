@@ -705,6 +705,10 @@ std::string shape_key(const Plan& plan, const System& S) {
   return buf;
 }
 
+// Generation of the kernels that shapes are measured for: raised with every change to what a
+// shape launches, so that a file written by another build is not taken for this one's.
+constexpr int kShapeKernels = 2;
+
 // Value of an integer or real field `"name": v` in one JSON line (false if absent).
 bool json_number(const std::string& line, const char* name, double& v) {
   const std::string tag = std::string("\"") + name + "\":";
@@ -716,8 +720,9 @@ bool json_number(const std::string& line, const char* name, double& v) {
   return end != p;
 }
 
-// The last cached shape for key in a JSON-lines file, if any.
-bool cache_lookup(const char* path, const std::string& key, mbd_shape& sh, double& ms) {
+// The last cached shape for key and direct cutoff in a JSON-lines file, if any.
+bool cache_lookup(const char* path, const std::string& key, double r_pair, mbd_shape& sh,
+                  double& ms) {
   if (!path) return false;
   FILE* f = std::fopen(path, "r");
   if (!f) return false;
@@ -727,7 +732,10 @@ bool cache_lookup(const char* path, const std::string& key, mbd_shape& sh, doubl
   while (std::fgets(line, sizeof line, f)) {
     const std::string l(line);
     if (l.find(tag) == std::string::npos) continue;
-    double a, b, c, d, e, f, g = 0.0, t = 0.0;
+    double a, b, c, d, e, f, g = 0.0, t = 0.0, gen = 0.0, rp = 0.0;
+    if (!json_number(l, "kernels", gen) || (int)gen != kShapeKernels ||
+        !json_number(l, "r_pair", rp) || std::fabs(rp - r_pair) > 1e-6 * r_pair)
+      continue;
     if (json_number(l, "pair_wg_per_cu", a) && json_number(l, "pair_subsets", b) &&
         json_number(l, "grid_chunk", c) && json_number(l, "overlap", d) &&
         json_number(l, "gather_waves", e) && json_number(l, "spread_mode", f)) {
@@ -743,16 +751,18 @@ bool cache_lookup(const char* path, const std::string& key, mbd_shape& sh, doubl
   return found;
 }
 
-void cache_store(const char* path, const std::string& key, const mbd_shape& sh, double ms) {
+void cache_store(const char* path, const std::string& key, double r_pair, const mbd_shape& sh,
+                 double ms) {
   if (!path) return;
   FILE* f = std::fopen(path, "a");
   if (!f) return;
   std::fprintf(f,
-               "{\"key\": \"%s\", \"pair_wg_per_cu\": %d, \"pair_subsets\": %d, "
+               "{\"key\": \"%s\", \"kernels\": %d, \"r_pair\": %.9g, "
+               "\"pair_wg_per_cu\": %d, \"pair_subsets\": %d, "
                "\"grid_chunk\": %d, \"overlap\": %d, \"gather_waves\": %d, "
                "\"spread_mode\": %d, \"pair_mode\": %d, \"matvec_ms\": %.5f}\n",
-               key.c_str(), sh.pair_wg_per_cu, sh.pair_subsets, sh.grid_chunk, sh.overlap,
-               sh.gather_waves, sh.spread_mode, sh.pair_mode, ms);
+               key.c_str(), kShapeKernels, r_pair, sh.pair_wg_per_cu, sh.pair_subsets,
+               sh.grid_chunk, sh.overlap, sh.gather_waves, sh.spread_mode, sh.pair_mode, ms);
   std::fclose(f);
 }
 
@@ -1193,14 +1203,14 @@ mbd_status mbd_plan_create(mbd_plan* out, const mbd_system* systems, int32_t n_s
         const std::string key = shape_key(plan, S);
         mbd_shape sh;
         double ms = 0.0;
-        if (cache_lookup(prm.tune_cache, key, sh, ms) && valid_shape(sh, plan.B)) {
+        if (cache_lookup(prm.tune_cache, key, g.r_pair, sh, ms) && valid_shape(sh, plan.B)) {
           apply_shape(plan, S, sh);
           S.shape_source = MBD_SHAPE_CACHED;
           S.tune_ms = ms;
         } else {
           if (plan.prec == MBD_PREC_FP64) tune_system<double>(plan, S, s);
           else tune_system<float>(plan, S, s);
-          cache_store(prm.tune_cache, key, S.shape, S.tune_ms);
+          cache_store(prm.tune_cache, key, g.r_pair, S.shape, S.tune_ms);
         }
       } else {
         apply_shape(plan, S, builtin_shape(plan, S));
