@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "cells.h"
 #include "common.h"
 #include "mbd_math.h"
 
@@ -323,6 +324,8 @@ constexpr size_t kMaxNbrBytes = (size_t)4 << 30;
 template <typename R>
 void create_nbr_list(Plan& plan, System& S) {
   SysBuffers& b = S.buf;
+  for (int r : S.geo.nr)
+    if (r > kPackedRange) return;  // (offsets do not fit a list entry)
   int* mx_d = b.nb_count + S.geo.n;
   fill_int(mx_d, 0, 1, plan.stream);
   launch_nbr_build<R>(S.geo, b, mx_d, plan.stream);

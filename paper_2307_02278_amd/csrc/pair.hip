@@ -67,18 +67,18 @@ k_nbr_build(const Geometry geo, const int* __restrict__ cell_start,
   const R xi = loc[4 * (size_t)s], yi = loc[4 * (size_t)s + 1], zi = loc[4 * (size_t)s + 2],
           si = loc[4 * (size_t)s + 3];
   const R rp2 = (R)(geo.r_pair * geo.r_pair);
-  const int ncells = (2 * geo.nr[0] + 1) * (2 * geo.nr[1] + 1) * (2 * geo.nr[2] + 1);
-  const int home = pack_off(0, 0, 0);
+  const int ncells = scan_cells(geo);
+  const int home = pack_off({0, 0, 0});
   int2* H = hdr + (size_t)s * cap;
   int cnt = 0;
   for (int cc0 = 0; cc0 < ncells; cc0 += 64) {
     int nat = 0;
     if (cc0 + lane < ncells) {
-      int off;
-      const int cc = scan_cell(geo, cx, cy, cz, cc0 + lane, off);
+      CellOffset o;
+      const int cc = scan_cell(geo, cx, cy, cz, cc0 + lane, o);
       first[lane] = cell_start[cc];
       nat = cell_start[cc + 1] - cell_start[cc];
-      offs[lane] = off;
+      offs[lane] = pack_off(o);
     }
     int v = nat;
     for (int o = 1; o < 64; o <<= 1) {
@@ -104,7 +104,7 @@ k_nbr_build(const Geometry geo, const int* __restrict__ cell_start,
         j = first[lo] + (c - pre[lo]);
         off = offs[lo];
         R sx, sy, sz;
-        cell_shift<R>(geo, off, sx, sy, sz);
+        cell_shift<R>(geo, unpack_off(off), sx, sy, sz);
         const R rx = loc[4 * (size_t)j] - xi + sx;
         const R ry = loc[4 * (size_t)j + 1] - yi + sy;
         const R rz = loc[4 * (size_t)j + 2] - zi + sz;
@@ -128,7 +128,7 @@ k_nbr_build(const Geometry geo, const int* __restrict__ cell_start,
   for (int k = lane; k < kept; k += 64) {
     const int2 h = H[k];
     R sx, sy, sz;
-    cell_shift<R>(geo, h.y, sx, sy, sz);
+    cell_shift<R>(geo, unpack_off(h.y), sx, sy, sz);
     const R* lj = loc + 4 * (size_t)h.x;
     const R rx = lj[0] - xi + sx, ry = lj[1] - yi + sy, rz = lj[2] - zi + sz;
     NbrAB<R> t;
@@ -147,7 +147,8 @@ k_nbr_build(const Geometry geo, const int* __restrict__ cell_start,
 // One thread per target instead runs one serial chain of several hundred loads per thread
 // and re-evaluates erfc and exp for every candidate in every matvec.
 // A target with more pairs than the list holds (positions far denser than those the plan
-// was sized for, or a list too large to keep) is summed on the fly over the cells.
+// was sized for, a list too large to keep, or a scan too wide for its packed offsets) is
+// summed on the fly over the cells.
 template <typename R, int NB, int WV>
 __global__ void __launch_bounds__(256)
 k_pair_nbr(const Geometry geo, const int* __restrict__ cell_start,
@@ -184,27 +185,27 @@ k_pair_nbr(const Geometry geo, const int* __restrict__ cell_start,
       const int2 h = H[k];
       const NbrAB<R> t = T[k];
       R sx, sy, sz;
-      cell_shift<R>(geo, h.y, sx, sy, sz);
+      cell_shift<R>(geo, unpack_off(h.y), sx, sy, sz);
       const R* lj = loc + 4 * (size_t)h.x;
       add(h.x, lj[0] - xi + sx, lj[1] - yi + sy, lj[2] - zi + sz, t.A, t.B);
     }
   } else {
     const R si = loc[4 * (size_t)s + 3], tau = (R)geo.tau, dd = (R)geo.damp_d;
     const R rp2 = (R)(geo.r_pair * geo.r_pair);
-    const int ncells = (2 * geo.nr[0] + 1) * (2 * geo.nr[1] + 1) * (2 * geo.nr[2] + 1);
+    const int ncells = scan_cells(geo);
     int cx, cy, cz;
     cell_coords(scell[s], cx, cy, cz);
     for (int ci = 0; ci < ncells; ++ci) {
-      int off;
-      const int cc = scan_cell(geo, cx, cy, cz, ci, off);
+      CellOffset o;
+      const int cc = scan_cell(geo, cx, cy, cz, ci, o);
       R sx, sy, sz;
-      cell_shift<R>(geo, off, sx, sy, sz);
+      cell_shift<R>(geo, o, sx, sy, sz);
       const int j1 = cell_start[cc + 1];
       for (int j = cell_start[cc] + e; j < j1; j += EL) {
         const R* lj = loc + 4 * (size_t)j;
         const R rx = lj[0] - xi + sx, ry = lj[1] - yi + sy, rz = lj[2] - zi + sz;
         const R r2 = rx * rx + ry * ry + rz * rz;
-        if (r2 >= rp2 || (j == s && off == pack_off(0, 0, 0))) continue;
+        if (r2 >= rp2 || (j == s && ci == ncells / 2)) continue;
         R A, Bk;
         direct_kernel<R>(r2, tau, R(1) / (lj[3] + si), dd, A, Bk);
         add(j, rx, ry, rz, A, Bk);

@@ -86,7 +86,8 @@ k_scs_apply(const Geometry geo, const int* __restrict__ cell_start,
   constexpr int SL = 64 / NQP;
   __shared__ ScsPair queue[2][kScsQueue];  // near, far
   __shared__ int qj[2][kScsQueue];
-  __shared__ int pre[65], first[64], offs[64];
+  __shared__ int pre[65], first[64];
+  __shared__ double shift[3][64];
   const int s = blockIdx.x;
   const int lane = threadIdx.x;
   const int f = lane % NQP, sl = lane / NQP;
@@ -100,8 +101,7 @@ k_scs_apply(const Geometry geo, const int* __restrict__ cell_start,
   const double s2i = sig2[(size_t)s * nq + fq], s2i0 = sig2[(size_t)s * nq];
   const double rp2 = geo.r_pair * geo.r_pair;
   const double dd = geo.damp_d;
-  const int home = pack_off(0, 0, 0);
-  const int ncells = (2 * geo.nr[0] + 1) * (2 * geo.nr[1] + 1) * (2 * geo.nr[2] + 1);
+  const int ncells = scan_cells(geo);
   double acc[3][3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) acc[a][0] = acc[a][1] = acc[a][2] = 0.0;
@@ -143,11 +143,11 @@ k_scs_apply(const Geometry geo, const int* __restrict__ cell_start,
   for (int cc0 = 0; cc0 < ncells; cc0 += 64) {
     int nat = 0;
     if (cc0 + lane < ncells) {
-      int off;
-      const int cc = scan_cell(geo, cx, cy, cz, cc0 + lane, off);
+      CellOffset o;
+      const int cc = scan_cell(geo, cx, cy, cz, cc0 + lane, o);
       first[lane] = cell_start[cc];
       nat = cell_start[cc + 1] - cell_start[cc];
-      offs[lane] = off;
+      cell_shift<double>(geo, o, shift[0][lane], shift[1][lane], shift[2][lane]);
     }
     int v = nat;
     for (int o = 1; o < 64; o <<= 1) {
@@ -170,13 +170,11 @@ k_scs_apply(const Geometry geo, const int* __restrict__ cell_start,
           if (pre[mid] <= c) lo = mid; else hi = mid - 1;
         }
         j = first[lo] + (c - pre[lo]);
-        double sx, sy, sz;
-        cell_shift<double>(geo, offs[lo], sx, sy, sz);
-        t.rx = locd[4 * (size_t)j] - xi + sx;
-        t.ry = locd[4 * (size_t)j + 1] - yi + sy;
-        t.rz = locd[4 * (size_t)j + 2] - zi + sz;
+        t.rx = locd[4 * (size_t)j] - xi + shift[0][lo];
+        t.ry = locd[4 * (size_t)j + 1] - yi + shift[1][lo];
+        t.rz = locd[4 * (size_t)j + 2] - zi + shift[2][lo];
         t.r2 = t.rx * t.rx + t.ry * t.ry + t.rz * t.rz;
-        if (t.r2 < rp2 && !(j == s && offs[lo] == home)) {
+        if (t.r2 < rp2 && !(j == s && cc0 + lo == ncells / 2)) {
           hit = !(scs_damped(t.r2, Si + locd[4 * (size_t)j + 3], dd, t.a0, t.b0) > kDampSkip);
           near = t.r2 < 49.0 * (s2i0 + sig2[(size_t)j * nq]);
         }
