@@ -911,10 +911,7 @@ k_spread_xline(float* __restrict__ grid, GridDims gd, const Geometry geo,
   }
 }
 
-#define MBD_REG_SIZES(X) \
-  X(8) X(10) X(12) X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) \
-  X(60) X(64) X(72) X(80) X(90) X(96) X(100) X(108) X(120) X(128)
-
+// Lengths of every transform (fft_supported refuses others at plan creation).
 #define MBD_FFT_SIZES(X) \
   X(8) X(10) X(12) X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) \
   X(60) X(64) X(72) X(80) X(90) X(96) X(100) X(108) X(120) X(128)
@@ -946,10 +943,8 @@ void launch_pass(int K, R* grid, const GridDims& gd, int nchunks, const R* twc, 
             k_fft_x_real<KK, MODE == kXFwd, false>                                       \
                 <<<g1, 64, 0, st>>>((float*)grid, gd, nullptr);                         \
             return;
-          MBD_REG_SIZES(MBD_REGX)
+          MBD_FFT_SIZES(MBD_REGX)
 #undef MBD_REGX
-          default:
-            break;
         }
       }
       dim3 g2((unsigned)((cols + 31) / 32), nchunks);
@@ -958,10 +953,8 @@ void launch_pass(int K, R* grid, const GridDims& gd, int nchunks, const R* twc, 
         case KK:                                                                       \
           k_fft_reg<KK, MODE><<<g2, 64, 0, st>>>((float*)grid, gd, (const float*)Gt);   \
           return;
-        MBD_REG_SIZES(MBD_REG)
+        MBD_FFT_SIZES(MBD_REG)
 #undef MBD_REG
-        default:
-          break;
       }
     }
   }
@@ -974,12 +967,10 @@ void launch_pass(int K, R* grid, const GridDims& gd, int nchunks, const R* twc, 
       break;
     MBD_FFT_SIZES(MBD_CASE)
 #undef MBD_CASE
-    default:
-      break;
   }
 }
 
-// Lengths of k_fft_plane.
+// Lengths of k_fft_plane (fft_plane_floats keeps others off this path).
 #define MBD_PLANE_SIZES(X) \
   X(16) X(18) X(20) X(24) X(30) X(32) X(36) X(40) X(48) X(50) X(54) X(60) X(64) X(72)
 
@@ -995,10 +986,8 @@ void launch_planes(float* grid, float2* spec, const GridDims& gd, const float* G
         if (pass == 0) k_fft_x_real<KK, true, true><<<blk, 64, 0, st>>>(grid, gd, spec); \
         else k_fft_x_real<KK, false, true><<<blk, 64, 0, st>>>(grid, gd, spec);         \
         break;
-      MBD_REG_SIZES(MBD_XT)
+      MBD_FFT_SIZES(MBD_XT)
 #undef MBD_XT
-      default:
-        break;
     }
   } else if (pass == 2) {
     switch (gd.K2) {
@@ -1011,8 +1000,6 @@ void launch_planes(float* grid, float2* spec, const GridDims& gd, const float* G
       }
       MBD_PLANE_SIZES(MBD_PLANE)
 #undef MBD_PLANE
-      default:
-        break;
     }
   }
 }
@@ -1113,7 +1100,7 @@ bool launch_spread_xline(const Geometry& geo, const SysBuffers& b, int B, int BG
                                                b.line_atoms, b.base, (const float*)b.th, \
                                                (const float*)b.dth, (const float*)b.dv, B); \
       return true;
-    MBD_REG_SIZES(MBD_SXL)
+    MBD_FFT_SIZES(MBD_SXL)
 #undef MBD_SXL
     default:
       return false;

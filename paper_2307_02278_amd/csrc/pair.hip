@@ -9,19 +9,19 @@
 // cell shift vectors h_a = a_a / nc_a, so it stays accurate in single precision,
 // works for any cell shape and covers several images when r_pair exceeds half the box.
 //
-// Two variants:
-//  - neighbour list: for B <= 8. Per target the sources within r_pair with A and B of
-//    their tensors (k_nbr_build, once per device setup), applied by one to four
-//    wavefronts per target (k_pair_nbr);
-//  - tensor list: for B >= 16. The positions do not change during a Lanczos run, so
-//    the tensors are evaluated once per device setup (k_pair_build) and kept in
-//    device memory, grouped by 16 consecutive sorted target atoms: for every
-//    source image within r_pair of at least one target of the group, a header
-//    (source, 16-bit target mask) and the 6 independent components of T_dir for
-//    each of the 16 targets (zero where the pair is out of range). Each matvec
-//    (k_pair_list) streams a group's tensors through LDS once and applies them to
-//    all right-hand sides, one lane per right-hand side, so every source dipole
-//    load serves all of the group's targets within range.
+// Which kernel runs:
+//  - B <= 8: a neighbour list. Per target the sources within r_pair with A and B of their
+//    tensors (k_nbr_build, once per device setup), applied by one to four wavefronts per
+//    target (k_pair_nbr), or the same sum over the cells where there is no list;
+//  - B >= 16: a tensor list. The positions do not change during a Lanczos run, so the
+//    tensors are evaluated once per device setup (k_pair_build) and kept in device memory,
+//    grouped by 16 consecutive sorted target atoms: for every source image within r_pair of
+//    at least one target of the group, a header (source index, 16-bit mask of the targets
+//    within range) and the six components of T_dir for each target (zeros outside the mask).
+//    float64 and float blocks of 16 and 32 multiply it on the matrix cores of their own type
+//    (k_pair_mfma), float blocks of 64 and more on the bfloat16 ones in three planes
+//    (k_pair_split, pair_mode 1 and 2) or with one vector lane per right-hand side
+//    (k_pair_list, pair_mode 0).
 #include <algorithm>
 
 #include "cells.h"
@@ -1453,13 +1453,12 @@ int pair_parts(const Geometry& g, const SysBuffers& b, int B) {
   return vec ? 1 : b.ed_parts;
 }
 
-// Target subsets per wavefront for the list kernels: at least 64 / B (every lane
-// busy); g.pair_ns when set and valid (a power of two, at least 64 / B, at most 4);
-// otherwise doubled (up to 4) while the launch would have fewer than 4096 wavefronts
-// (4 per SIMD), so that small systems still fill the GPU.
+// Target subsets per wavefront of the vector list kernel (64 right-hand sides and more):
+// g.pair_ns when set (1, 2 or 4); otherwise doubled (up to 4) while the launch would have
+// fewer than 4096 wavefronts (4 per SIMD), so that small systems still fill the GPU.
 int pair_subsets(const Geometry& g, int ngroups, int B) {
-  int ns = B >= 64 ? 1 : 64 / B;
-  if (g.pair_ns > 0) return std::max(ns, std::min(4, g.pair_ns));
+  if (g.pair_ns > 0) return std::min(4, g.pair_ns);
+  int ns = 1;
   while (ns < 4 && (long)ngroups * B * ns / 64 < 4096) ns *= 2;
   return ns;
 }
@@ -1606,16 +1605,18 @@ void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_
 #define MBD_PF(NS, TWV, RSV, TPV)                                                        \
   k_pair_force<R, NS, TWV, RSV, TPV><<<dim3(nblk, b.fs_parts), 64 * TWV * RSV, 0, st>>>( \
       g, H, F, b.pg_count, b.pg_cap, p, q, b.fsum + 3 * (size_t)g.n, B)
+  // (float blocks of 16 and 32 never come here)
+#define MBD_PF64(...) if constexpr (sizeof(R) == 8) MBD_PF(__VA_ARGS__)
   switch (B * 16 + tw) {
     case 4 * 16 + 1: MBD_PF(16, 1, 1, 1); break;
     case 8 * 16 + 1: MBD_PF(8, 1, 1, 2); break;
     case 8 * 16 + 2: MBD_PF(8, 2, 1, 1); break;
-    case 16 * 16 + 1: MBD_PF(4, 1, 1, 4); break;
-    case 16 * 16 + 2: MBD_PF(4, 2, 1, 2); break;
-    case 16 * 16 + 4: MBD_PF(4, 4, 1, 1); break;
-    case 32 * 16 + 1: MBD_PF(2, 1, 1, 8); break;
-    case 32 * 16 + 2: MBD_PF(2, 2, 1, 4); break;
-    case 32 * 16 + 4: MBD_PF(2, 4, 1, 2); break;
+    case 16 * 16 + 1: MBD_PF64(4, 1, 1, 4); break;
+    case 16 * 16 + 2: MBD_PF64(4, 2, 1, 2); break;
+    case 16 * 16 + 4: MBD_PF64(4, 4, 1, 1); break;
+    case 32 * 16 + 1: MBD_PF64(2, 1, 1, 8); break;
+    case 32 * 16 + 2: MBD_PF64(2, 2, 1, 4); break;
+    case 32 * 16 + 4: MBD_PF64(2, 4, 1, 2); break;
     case 64 * 16 + 1: MBD_PF(1, 1, 1, 8); break;
     case 64 * 16 + 2: MBD_PF(1, 2, 1, 8); break;
     case 64 * 16 + 4: MBD_PF(1, 4, 1, 4); break;
@@ -1626,6 +1627,7 @@ void launch_pair_force(const Geometry& g, const SysBuffers& b, int B, hipStream_
     case 256 * 16 + 2: MBD_PF(1, 2, 4, 8); break;
     default: MBD_PF(1, 4, 4, 4); break;
   }
+#undef MBD_PF64
 #undef MBD_PF
 }
 
