@@ -35,6 +35,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E
 FP32_PEAK_TFLOPS = 157.3         # MI355X published FP32 peak (packed FMA and matrix cores)
 FP32_NONPACKED_TFLOPS = 78.6     # 256 CU x 64 FMA lanes x 2 flop x 2.4 GHz, no packed FP32
+PLANES_PEAK_TFLOPS = 2500.0 / 6  # dense bfloat16 peak over the six products of a float one
 GOLDEN = os.path.join(ROOT, "tests", "golden")
 
 
@@ -60,9 +61,11 @@ def pair_kernel_name(shape, B, n_atoms):
     mode = shape.get("pair_mode", 0)
     if mode in (1, 2) and B % 64 == 0 and B <= 256:
         return "k_pair_split<8, 2>" if mode == 1 and B % 128 == 0 else "k_pair_split<4, 4>"
-    ns = 1 if B >= 64 else 64 // B
+    if B < 64:
+        return f"k_pair_mfma<float, 4, {B // 16}, 1>"
+    ns = 1
     if ns_given > 0:
-        ns = max(ns, min(4, ns_given))
+        ns = min(4, ns_given)
     else:
         while ns < 4 and ngroups * B * ns / 64 < 4096:
             ns *= 2
@@ -509,21 +512,21 @@ def main():
     if dom == "pair":
         flops = 18.0 * n_pairs * B
         achieved = flops / (dom_ms_avg * 1e-3) / 1e12
-        mfma = pair_kernel.startswith("k_pair_split")
-        roof = {"kernel": pair_kernel, "bound": "mfma" if mfma else "alu",
+        planes = pair_kernel.startswith("k_pair_split")
+        peak = PLANES_PEAK_TFLOPS if planes else FP32_PEAK_TFLOPS
+        roof = {"kernel": pair_kernel, "bound": "alu" if "list" in pair_kernel else "mfma",
                 "achieved": round(achieved, 3),
-                "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
+                "peak": round(peak, 1), "unit": "TFLOP/s",
+                "frac": round(achieved / peak, 4),
                 "traffic": measured_traffic(pair_kernel),
                 "avg_launch_ms": round(dom_ms_avg, 4),
                 "algorithmic_per_launch": f"18 flop x {n_pairs} pairs x {B} rhs"}
-        if mfma:
+        if planes:
             # the matrix cores also multiply the list's zero tensors (out-of-range
             # target-candidate pairs of a 16-target group)
-            roof["peak_note"] = ("FP32 matrix-core peak; the kernel forms float products from six "
-                                 "bfloat16 ones (2500 / 6 = 417 TFLOP/s), and algorithmic flops "
-                                 "exclude zero tensors")
-        else:
+            roof["peak_note"] = ("dense bfloat16 peak / 6: the kernel forms a float product from "
+                                 "six bfloat16 ones; algorithmic flops exclude zero tensors")
+        elif roof["bound"] == "alu":
             roof["peak_nonpacked_fp32"] = FP32_NONPACKED_TFLOPS
             roof["frac_of_nonpacked_fp32"] = round(achieved / FP32_NONPACKED_TFLOPS, 4)
     else:
@@ -559,8 +562,8 @@ def main():
         a_ms = pst[0] / pst[1]
         a_tf = 18.0 * n_pairs * B / (a_ms * 1e-3) / 1e12
         alone = {"kernel": pair_kernel_name(sh_alone, B, s.n), "achieved": round(a_tf, 3),
-                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                 "frac": round(a_tf / FP32_PEAK_TFLOPS, 4), "avg_launch_ms": round(a_ms, 4),
+                 "peak": round(PLANES_PEAK_TFLOPS, 1), "unit": "TFLOP/s",
+                 "frac": round(a_tf / PLANES_PEAK_TFLOPS, 4), "avg_launch_ms": round(a_ms, 4),
                  "shape": sh_alone}
         log(f"pair kernel alone: {alone}")
     roof["pair_kernel_alone"] = alone
