@@ -437,7 +437,8 @@ void adjoint_matvec_forces(Plan& plan, System& S, int k) {
     sd = S.overlap ? fork_side(plan, st) : nullptr;
     const hipStream_t ss = sd ? sd->side : st;
     if (adjoint)
-      staged_on(plan, MBD_STAGE_PAIR, ss, [&] { launch_pair<R>(S.geo, b, plan.B, ss); });
+      staged_on(plan, MBD_STAGE_PAIR, ss,
+                [&] { launch_pair<R>(S.geo, b, plan.B, ss, true); });
     if (sd) check(hipEventRecord(sd->pair_done, ss), "side join");
     staged_on(plan, MBD_STAGE_FORCE, ss, [&] { launch_pair_force<R>(S.geo, b, plan.B, ss); });
   };

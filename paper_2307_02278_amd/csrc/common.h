@@ -263,8 +263,10 @@ void launch_setup(const Geometry& g, SysBuffers& b, const double* pos, const dou
 // Parts of the direct-space field that launch_pair leaves in b.Ed.
 int pair_parts(const Geometry& g, const SysBuffers& b, int B);
 
+// reverse: for the adjoint vectors of a reverse sweep (no precision kept for tiny fields).
 template <typename R>
-void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st);
+void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st,
+                 bool reverse = false);
 
 void launch_replica(const Geometry& g, const SysBuffers& b, int B, hipStream_t st);
 

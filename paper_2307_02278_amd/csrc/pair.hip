@@ -564,51 +564,55 @@ k_pair_list(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
 // The dense products below give every target of a group 0 x d of the candidates out of its
 // range: not a number where d is not finite. The bfloat16 planes of k_pair_split besides turn
 // floats above the largest bfloat16 into infinities, and below 2^-110 the last plane falls
-// under the smallest bfloat16 (2^-133). Where an element of a column's field is not finite
-// or, from planes, smaller than 2^-96 (more than 2^24 times what the planes can lose of
-// it), the work-group sums that column again over the pairs in range alone, in the list's
-// type, as the vector kernel does. Columns of ordinary values keep their bits; testing
-// them costs an LDS flag and two barriers a group.
-template <typename R, bool PLANES>
-__device__ __forceinline__ bool out_of_bounds(R v) {
+// under the smallest bfloat16 (2^-133), an error of 2^-134 a dipole and so about as much in
+// the field. Where an element of a column's field is not finite, or smaller than the floor
+// that the caller gives, the work-group sums that column again over the pairs in range alone,
+// in the list's type, as the vector kernel does. Columns of ordinary values keep their bits;
+// testing them costs an LDS flag and a barrier a group.
+// A matvec's floor is 2^-104, 2^24 times that error with a factor of 64 to spare. The reverse
+// sweep has none: the adjoint vectors of the last steps are that small as a matter of course
+// (they fall with the square of the converging Lanczos vectors' weights), and add nothing to
+// forces whose other terms are 10^20 times larger; summed again, they doubled the direct
+// sum's share of a reverse sweep.
+template <typename R>
+__device__ __forceinline__ bool out_of_bounds(R v, R floor) {
   const R a = fabs(v);
   const R huge = sizeof(R) == 4 ? (R)3.4028235e38f : (R)1.7976931348623157e308;
-  return !(a <= huge) || (PLANES && a < (R)0x1p-96f && a > R(0));
+  return !(a <= huge) || (a < floor && a > R(0));
 }
 
-// Columns of a work-group whose field is to be summed again.
+// Columns of a work-group whose field is to be summed again, marked with the number of the
+// group (its turn, from 1): nothing is cleared between groups. A mark of the next group comes
+// after the barriers around that group's candidates, so past every thread's reading here (a
+// group without candidates has nothing to mark).
 template <int W>
 struct Redo {
-  unsigned bits[(W + 31) / 32];
+  int turn[W];
   int any;
   __device__ __forceinline__ void clear() {
-    if (threadIdx.x < (W + 31) / 32) bits[threadIdx.x] = 0u;
+    if (threadIdx.x < W) turn[threadIdx.x] = 0;
     if (threadIdx.x == 0) any = 0;
   }
   // bit t of odd: the lane's column first + step * ST (t / ST) + t % ST
-  __device__ __forceinline__ void mark(unsigned odd, int first, int step, int ST) {
-    any = 1;
+  __device__ __forceinline__ void mark(int now, unsigned odd, int first, int step, int ST) {
+    any = now;
     for (; odd; odd &= odd - 1u) {
       const int t = __ffs(odd) - 1;
-      const int column = first + step * ST * (t / ST) + t % ST;
-      atomicOr(&bits[column >> 5], 1u << (column & 31));
+      turn[first + step * ST * (t / ST) + t % ST] = now;
     }
-  }
-  __device__ __forceinline__ bool marked(int column) const {
-    return (bits[column >> 5] >> (column & 31)) & 1u;
   }
 };
 
 // The marked columns (of W, at dv and Ed) of one group over its candidates [lo, hi).
 template <typename R, int W>
-__device__ __forceinline__ void sum_in_range(const Geometry& geo, const Redo<W>& redo, int group,
-                                             const int2* H, const R* T, int lo, int hi,
+__device__ __forceinline__ void sum_in_range(const Geometry& geo, const Redo<W>& redo, int now,
+                                             int group, const int2* H, const R* T, int lo, int hi,
                                              const R* dv, R* Ed, size_t Bs) {
   // (opaque, so that nothing of this is kept in registers across the products)
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int c = tid % W;
-  if (!redo.marked(c)) return;
+  if (redo.turn[c] != now) return;
 #pragma unroll 1
   for (int t = tid / W; t < kGroup; t += 256 / W) {
     const int i = group * kGroup + t;
@@ -686,6 +690,7 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
   const int ngroups = (geo.n + kGroup - 1) / kGroup;
   const int per = (ngroups + 7) / 8;
   const int nbx = gridDim.x / 8;
+  redo.clear();
   for (int gi = blockIdx.x / 8; gi < per; gi += nbx) {
     const int group = (blockIdx.x % 8) * per + gi;
     if (group >= ngroups) return;  // uniform over the work-group
@@ -762,14 +767,13 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
         }
       }
     }
-    redo.clear();
     unsigned odd = 0u;  // column tiles with a value out of bounds
     // component a of the lane's NT right-hand sides for the target of register r
     auto store = [&](int a, int r, const R (&v)[NT]) {
       const int i = group * kGroup + Mma<R>::row(row, r);
       if (i >= geo.n) return;
 #pragma unroll
-      for (int t = 0; t < NT; ++t) odd |= (unsigned)out_of_bounds<R, false>(v[t]) << t;
+      for (int t = 0; t < NT; ++t) odd |= (unsigned)out_of_bounds<R>(v[t], R(0)) << t;
       Pack<R, VN>* o = reinterpret_cast<Pack<R, VN>*>(Ed + ((size_t)i * 3 + a) * Bs + rhs);
 #pragma unroll
       for (int q = 0; q < NT / VN; ++q) {
@@ -817,11 +821,10 @@ k_pair_mfma(const Geometry geo, const int2* __restrict__ hdr, const R* __restric
         }
       }
     }
+    if (odd) redo.mark(gi + 1, odd, rhs, 1, NT);
     __syncthreads();
-    if (odd) redo.mark(odd, rhs, 1, NT);
-    __syncthreads();
-    if (redo.any) sum_in_range<R, 16 * NT * NN>(geo, redo, group, H, T, clo, cnt, dv, Ed, Bs);
-    __syncthreads();  // the marks have been read
+    if (redo.any == gi + 1)
+      sum_in_range<R, 16 * NT * NN>(geo, redo, gi + 1, group, H, T, clo, cnt, dv, Ed, Bs);
   }  // groups of this work-group
 }
 
@@ -875,7 +878,7 @@ template <int NT, int ST>
 __global__ void __launch_bounds__(256, 2)
 k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __restrict__ Tg,
              const int* __restrict__ gcount, int cap, const float* __restrict__ dv,
-             float* __restrict__ Ed, int B) {
+             float* __restrict__ Ed, int B, float floor) {
   constexpr int NQ = NT / ST;  // column steps of ST tiles
   __shared__ float red[4 * NT * 256];
   __shared__ int jl[kMfmaChunk];
@@ -890,6 +893,7 @@ k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __re
   const int ngroups = (geo.n + kGroup - 1) / kGroup;
   const int per = (ngroups + 7) / 8;
   const int nbx = gridDim.x / 8;
+  redo.clear();
   for (int gi = blockIdx.x / 8; gi < per; gi += nbx) {
     const int group = (blockIdx.x % 8) * per + gi;
     if (group >= ngroups) return;  // uniform over the work-group
@@ -980,7 +984,6 @@ k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __re
         }
       }
     }
-    redo.clear();
     unsigned odd = 0u;  // column tiles with a value out of bounds
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -1003,18 +1006,17 @@ k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __re
 #pragma unroll
             for (int k = 1; k < 4; ++k) v += red[((k * NT + t) * 4 + wk) * 64 + lane];
             w.v[u] = v;
-            odd |= (unsigned)out_of_bounds<float, true>(v) << t;
+            odd |= (unsigned)out_of_bounds<float>(v, floor) << t;
           }
           *reinterpret_cast<Pack<float, ST>*>(Ed + ((size_t)i * 3 + a) * Bs + 16 * ST * q +
                                               ST * col) = w;
         }
       }
     }
-    if (odd) redo.mark(odd, ST * col, 16, ST);
+    if (odd) redo.mark(gi + 1, odd, ST * col, 16, ST);
     __syncthreads();
-    if (redo.any)
-      sum_in_range<float, 16 * NT>(geo, redo, group, H, T, clo, cnt, dv + rhs0, Ed, Bs);
-    __syncthreads();  // the marks have been read
+    if (redo.any == gi + 1)
+      sum_in_range<float, 16 * NT>(geo, redo, gi + 1, group, H, T, clo, cnt, dv + rhs0, Ed, Bs);
   }
 }
 
@@ -1464,7 +1466,7 @@ int pair_subsets(const Geometry& g, int ngroups, int B) {
 }
 
 template <typename R>
-void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) {
+void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st, bool reverse) {
   const R* loc = (const R*)b.loc;
   const R* dv = (const R*)b.dv;
   R* Ed = (R*)b.Ed;
@@ -1522,13 +1524,14 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st) 
     if (g.pair_mode == 1 || g.pair_mode == 2) {
       const bool wide = g.pair_mode == 1 && B % 128 == 0;
       const int slices = B / (wide ? 128 : 64);
+      const float floor = reverse ? 0.f : 0x1p-104f;
       const dim3 sliced(pair_grid_x(ngroups, nparts, slices, g.pair_blocks), nparts, slices);
       if (wide)
         k_pair_split<8, 2><<<sliced, 256, 0, st>>>(g, H, (const float*)T, b.pg_count, b.pg_cap,
-                                                   (const float*)dv, (float*)Ed, B);
+                                                   (const float*)dv, (float*)Ed, B, floor);
       else
         k_pair_split<4, 4><<<sliced, 256, 0, st>>>(g, H, (const float*)T, b.pg_count, b.pg_cap,
-                                                   (const float*)dv, (float*)Ed, B);
+                                                   (const float*)dv, (float*)Ed, B, floor);
       return;
     }
 #undef MBD_PM
@@ -1647,8 +1650,8 @@ void launch_replica(const Geometry& g, const SysBuffers& b, int B, hipStream_t s
   }
 }
 
-template void launch_pair<float>(const Geometry&, const SysBuffers&, int, hipStream_t);
-template void launch_pair<double>(const Geometry&, const SysBuffers&, int, hipStream_t);
+template void launch_pair<float>(const Geometry&, const SysBuffers&, int, hipStream_t, bool);
+template void launch_pair<double>(const Geometry&, const SysBuffers&, int, hipStream_t, bool);
 template void launch_pair_build<float>(const Geometry&, const SysBuffers&, bool, hipStream_t);
 template void launch_pair_build<double>(const Geometry&, const SysBuffers&, bool, hipStream_t);
 
