@@ -1471,9 +1471,13 @@ void launch_pair(const Geometry& g, const SysBuffers& b, int B, hipStream_t st, 
   const R* dv = (const R*)b.dv;
   R* Ed = (R*)b.Ed;
   if (B <= 8) {
-    // four wavefronts per target while one each would leave the GPU with fewer than 8
-    // wavefronts per SIMD
-    const bool wide = g.n < 8192;
+    // four wavefronts per target while that shortens the chain of a target's entries: with
+    // one right-hand side a wavefront takes 64 entries a step, so a target (about 300) is
+    // done in five and the exchange between wavefronts costs more than it saves. One and
+    // four, us, float64: B = 1, 648 atoms 6.9 and 7.0, 1029 7.5 and 8.4, 3000 9.2 and 12.7;
+    // B = 8, 648 atoms 16.2 and 12.3, 5184 56 and 51, 12288 108 and 109; float, B = 8, 8232
+    // atoms 48 and 46
+    const bool wide = g.n < (B == 1 ? 1024 : 8192);
     const int blocks = ((wide ? g.n : (g.n + 3) / 4) + 7) / 8 * 8;
 #define MBD_NB(NBV)                                                                        \
     if (wide)                                                                              \
