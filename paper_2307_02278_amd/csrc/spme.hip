@@ -708,9 +708,12 @@ template <typename R>
 void launch_epilogue(const Geometry& geo, const SysBuffers& b, const double* w, int B, int BG,
                      int chunk0, int nchunks, uint32_t comps, hipStream_t st) {
   const size_t chunk = (size_t)geo.K[2] * geo.K[1] * (geo.K[0] + 2) * BG;
-  // slices of 16 while whole chunks would leave fewer than four wavefronts per SIMD (648
-  // atoms, chunks of 32: 20 us a launch whole, 11.4 us in slices)
-  const bool sliced = geo.n < 4096;
+  // slices of 16 while whole chunks would leave about a wavefront per SIMD; then the sub-lanes
+  // of a slice, which share rows unevenly, cost more. Whole and in slices, us a launch:
+  // chunks of 32, 192 atoms 11.4 and 10.0, 648 11.7 and 10.6, 1029 11.6 and 11.1, 2187 15.5
+  // and 16.9; chunks of 64, 192 atoms 12.3 and 10.3, 648 12.9 and 12.2, 1029 15.4 and 16.0,
+  // 3000 19.9 and 27.1
+  const bool sliced = geo.n < 1024;
   const dim3 grd(gather_blocks(geo, BG), nchunks * (sliced && BG > 16 ? BG / 16 : 1));
   const Epilogue<R> ep = epilogue_of<R>(geo, b, w, B, comps);
 #define MBD_GATHER(PP, BB, LL)                                                              \
