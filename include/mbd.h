@@ -110,17 +110,18 @@ typedef struct {
                              fused with the forward x transform (mixed precision, p = 6,
                              64-wide chunks; otherwise 0 is used). Both give the same
                              real grid; the fused form never writes it                  */
-  int32_t pair_mode;      /* direct-space list kernel: 0 => vector FMA lanes, one lane per
-                             right-hand side, skipping out-of-range pairs; 1 => matrix
-                             cores over the dense per-group product, floats in three
-                             bfloat16 planes (mixed precision, block a multiple of 64 up
-                             to 256; otherwise 0 is used), a wavefront holding 128
-                             right-hand sides where block is a multiple of 128, else 64;
-                             2 => the same with 64 right-hand sides per wavefront (half
-                             the accumulator registers). float64 and blocks below 64 run
-                             on the float matrix cores whatever the mode. With forces, 1 and 2 also compute
-                             the direct force term on the matrix cores when
-                             block <= 128                                                 */
+  int32_t pair_mode;      /* direct-space list kernel of mixed plans with 64 right-hand sides
+                             and more: 0 => vector FMA lanes, one lane per right-hand side,
+                             skipping out-of-range pairs; 1 => matrix cores over the dense
+                             per-group product, floats in three bfloat16 planes, a wavefront
+                             holding 128 right-hand sides where block is a multiple of 128,
+                             else 64; 2 => the same with 64 right-hand sides per wavefront
+                             (half the accumulator registers). With forces, 1 and 2 also
+                             compute the direct force term on the matrix cores when
+                             block <= 128. Every other plan has one direct kernel and
+                             reports 0: a neighbour list for blocks of 8 and less, the
+                             matrix cores of the list's own type for float64 from 16 on
+                             and for mixed blocks of 16 and 32                            */
 } mbd_shape;
 
 enum {
@@ -254,7 +255,9 @@ mbd_status mbd_check(mbd_plan plan);
 /* out = C_sel v for nrhs vectors (test and diagnostic hook). v, out: device
  * [nrhs][N][3] float64 in the caller's atom order; 1 <= nrhs <= block.
  * components selects the parts of C: MBD_C_DIAG (Omega v), MBD_C_DIR
- * (g * E_dir(g v)), MBD_C_REC (g * E_rec(g v)), MBD_C_SELF (g * E_self(g v)). */
+ * (g * E_dir(g v)), MBD_C_REC (g * E_rec(g v)), MBD_C_SELF (g * E_self(g v)). A value of v
+ * that is not finite reaches, in MBD_C_DIR alone, the atoms within r_pair of its own and
+ * its own right-hand side only; through MBD_C_REC it reaches every atom. */
 mbd_status mbd_matvec(mbd_plan plan, int32_t sys, const double* v, double* out,
                       int32_t nrhs, uint32_t components);
 

@@ -648,11 +648,14 @@ double* scratch_of(int device) {
 
 // The built-in shape: every group resident, the default chunk, and the matrix-core list
 // kernel where it applies (24k atoms, 128 right-hand sides, alone: 278 us a launch against
-// 598 us of the vector kernel). The side stream costs each
-// matvec a fork and a join, 10 to 20 us, so it is used where the direct sum it hides takes
-// longer (matvec in us without and with it: 96 atoms, B = 1: 49 and 88; 648 atoms, B = 32,
-// energy: 1626 and 1714; 1501 atoms, B = 64: 135 and 128; 24k atoms, B = 1, energy: 18.8
-// and 18.6 ms).
+// 598 us of the vector kernel). The side stream costs each matvec a fork and a join, so it
+// is used where the direct sum it hides takes longer. C v in us without and with it, by
+// n max(B, 4): 12,000 (3000 atoms, float64, B = 1) 58 and 75; 20,736 (648, float, 32) 65 and
+// 70, (5184, float, 1) 87 and 95; 24,576 (1536, float64, 16) 96 and 97; 41,472 (5184, float,
+// 8) 123 and 115; 48,000 (3000, float64, 16) 128 and 122, (3000, float, 16) 74 and 76;
+// 49,152 (12,288, float, 1) 111 and 119; 65,856 (8232, float, 8) 149 and 138; 82,944 (5184,
+// float64, 16) 178 and 171; 98,304 (1536, float, 64) 103 and 106; 131,712 (8232, float, 16)
+// 144 and 132. Between 20,000 and 100,000 either side is within 8 % of the other.
 mbd_shape builtin_shape(const Plan& plan, const System& S) {
   const int B = plan.B;
   mbd_shape sh = {0, 0, 0, (long)S.geo.n * std::max(B, 4) >= 50000 ? 1 : 0, 0, 0, 0};

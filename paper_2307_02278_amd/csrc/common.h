@@ -50,7 +50,7 @@ struct Geometry {
   double replica_cut;    // > 0: replica method (damped tensor over images within this cutoff)
   int n_images;          // replica image vectors
   // launch shape of the direct-space list kernels (set by the plan or its tuner)
-  int pair_blocks;       // work-groups of a launch; 0 => one per 16-atom group
+  int pair_blocks;       // most work-groups of a list-kernel launch; 0 => all groups resident
   int pair_ns;           // target subsets per wavefront (1, 2, 4); 0 => size rule
   int gather_waves;      // wavefronts per work-group of the gather-type kernels (4 or 8)
   int pair_mode;         // 0 => vector list kernel; 1 => matrix-core list kernel (float);

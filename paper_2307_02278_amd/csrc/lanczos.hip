@@ -826,9 +826,11 @@ void launch_update(const Geometry& geo, const SysBuffers& b, int B, int nb, int 
                          b.part, ng, (int)grd.x, status)));
 }
 
-// Every work-group of k_update then reads the ng + nu partials of its right-hand sides: up
-// to 8 MB of L2 reads over the launch that takes less time than the launch it saves (648
-// atoms, B = 32: 3.6 MB; 24k atoms, B = 128: 2 GB).
+// Every work-group of k_update then reads the ng + nu partials of its right-hand sides. Up to
+// 8 MB of L2 reads over the launch that takes no longer than the launch it saves. Energy of 30
+// steps with the separate launch and without, us: 648 atoms, float, B = 32 (3.6 MB) 2342 and
+// 2364; 1536 atoms, B = 16 (4.2 MB) 2385 and 2331; 3000 atoms, B = 16 (16 MB) 2751 and 2760,
+// B = 32 (75 MB) 3381 and 3487; 3000 atoms, float64, B = 1 (14 KB) 2402 and 2333.
 bool update_finishes(const Geometry& geo, int B, int ng) {
   const size_t nu = (size_t)row_blocks(geo.n, B);
   return (ng + nu) * sizeof(double) * B * nu <= ((size_t)8 << 20);

@@ -874,6 +874,7 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
 // as in k_pair_mfma, gridDim.z slices of the right-hand sides. 24k atoms, B = 128: 417 us a
 // launch with float products, 278 us here, 12k atoms, B = 64: 122 and 78 us. What remains
 // is loads: 1.7 GB of dipoles and 0.42 GB of tensors a launch, half of it from beyond L2.
+// <4, 4> takes 242 registers, <8, 2> all 256 with 27 spilled: two work-groups a CU each.
 template <int NT, int ST>
 __global__ void __launch_bounds__(256, 2)
 k_pair_split(const Geometry geo, const int2* __restrict__ hdr, const float* __restrict__ Tg,
@@ -1565,8 +1566,11 @@ void launch_pair_build(const Geometry& g, const SysBuffers& b, bool count_only, 
   k_pair_build<R, BT><<<ngroups, BT, 0, st>>>(                                            \
       g, b.cell_start, b.scell, (const R*)b.loc, count_only ? 0 : b.pg_cap, b.pg_hdr,     \
       (R*)b.pg_T, count_only ? nullptr : (R*)b.pg_F, b.pg_count, b.pg_max)
-  // below four work-groups per CU a group's scan is a latency chain: four times the threads
-  // (648 atoms, 41 groups: 89 us a launch with 256, 55 us with 1024)
+  // below four work-groups per CU a group's scan is a latency chain: four times the threads.
+  // set_positions with 256 and 1024, us: 648 atoms, float, 134 and 98; 8232 atoms 247 and
+  // 218; 15,798 atoms (988 groups) 367 and 324, in float64 417 and 400. 1024 threads leave 128
+  // registers each, of which the tensors spill 36 to 39: with the force tensors as well,
+  // float64, 3000 atoms, 275 and 219, 14,739 atoms 571 and 568, 15,798 atoms 563 and 615
   if (ngroups < 1024) MBD_PB(1024); else MBD_PB(256);
 #undef MBD_PB
 }

@@ -8,14 +8,15 @@
 // One wavefront owns a 4x4x4 tile of grid points for one chunk of BG right-hand
 // sides, accumulates in registers every atom whose stencil reaches the tile, in a
 // fixed order, and writes the tile once: no atomics, no clearing pass, and a
-// deterministic sum. With one lane per right-hand side the atom's indices and
-// spline weights are wave-uniform.
+// deterministic sum. Chunks of 16 and more multiply the atoms' weights with their dipoles
+// on the matrix cores (k_spread); narrower ones share the tile's points out to the lanes of
+// each right-hand side (k_spread_brick).
 //
 // Gather + epilogue: E_rec,i = sum_k grad_i W_i(k) phi(k) (eq. spme), then the
 // generalized field E* = E_dir + E_rec + E_self and
 //   l~ = Omega w + Diag(g) E*      (eq. lk3, in double precision)
-// with per-block partial sums of w . l~ for a_k (eq. recurs2). Again one wavefront
-// per atom and one lane per right-hand side.
+// with per-block partial sums of w . l~ for a_k (eq. recurs2). The lanes of a wavefront are
+// right-hand sides x sub-lanes that share an atom's stencil rows x atoms (Lanes below).
 #include <algorithm>
 
 #include "common.h"
