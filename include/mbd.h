@@ -87,7 +87,7 @@ typedef struct {
  * those. A plan is bitwise reproducible for its shape, and a system's results for its shape
  * (and probes) are the same bits whatever other systems the plan holds. Blocks of 8 and less
  * keep a neighbour list where it takes no more than half of the device memory left at plan
- * creation (and 4 GiB), and otherwise sum over the cells: the same pairs in another order. */
+ * creation (or 64 MiB, and at most 4 GiB), and otherwise sum over the cells: the same pairs in another order. */
 typedef struct {
   int32_t pair_wg_per_cu; /* work-groups per compute unit of the direct-space list kernel,
                              all parts of a group and slices of right-hand sides counted;

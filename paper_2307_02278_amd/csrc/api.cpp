@@ -312,15 +312,16 @@ void run_setup(Plan& plan, System& S, const double* pos) {
   });
 }
 
-// Largest neighbour list kept for one system.
-constexpr size_t kMaxNbrBytes = (size_t)4 << 30;
+// Largest neighbour list kept for one system, and the largest kept without a look at the free
+// memory.
+constexpr size_t kMaxNbrBytes = (size_t)4 << 30, kSmallNbrBytes = (size_t)64 << 20;
 
 // Size and build the neighbour list of a narrow block (B <= 8) for the positions set up
 // last: a counting pass, then a capacity of 1.25 x the largest count plus 16, then the build.
 // The list is optional: without it the pairs are summed on the fly, as they are for any
 // target whose count outgrows it at later positions. So it is made after everything that the
 // plan's systems cannot do without, and only where it leaves as much device memory free as
-// it takes.
+// it takes (asking costs 0.1 ms: not for small ones).
 template <typename R>
 void create_nbr_list(Plan& plan, System& S) {
   SysBuffers& b = S.buf;
@@ -336,9 +337,10 @@ void create_nbr_list(Plan& plan, System& S) {
   const size_t cap = (size_t)mx + mx / 4 + 16;
   const size_t ents = cap * (size_t)S.geo.n;
   const size_t bytes = ents * (sizeof(int2) + 2 * sizeof(R));
+  if (bytes > kMaxNbrBytes) return;
   size_t free_bytes = 0, total_bytes = 0;
-  if (bytes > kMaxNbrBytes || hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess ||
-      free_bytes / 2 < bytes) {
+  if (bytes > kSmallNbrBytes && (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess ||
+                                 free_bytes / 2 < bytes)) {
     (void)hipGetLastError();
     return;
   }
